@@ -308,6 +308,10 @@ struct CompInfo {
   int lt, ls, a, b;
   double zinf;        // decay length of the density (shortest ray path)
   double sinf;        // its amplitude: sigma(k) e^{k zinf} -> sinf as k -> infinity
+  // what the leading term leaves, as images where nimg >= 0 (-1: by quadrature):
+  // sum over j < nimg of img1 imgq^j e^{-k (zinf + imgd (j + 1))}
+  double img1, imgq, imgd;
+  int nimg;
 };
 int gpu_sommerfeld_tables(const Medium& md, const std::vector<CompInfo>& comps,
                           const std::vector<SommTask>& tasks, int nmax, double* d_out,
@@ -322,9 +326,7 @@ int gpu_density(const Medium& md, const CompInfo& c, int64_t nk, const double* k
                 const double* kim, double* ore, double* oim, hipStream_t st);
 double zeta_inf(const Medium& md, int lt, int ls, int a, int b);
 double sigma_inf(const Medium& md, int lt, int ls, int a, int b);
-inline CompInfo make_comp(const Medium& md, int lt, int ls, int a, int b) {
-  return CompInfo{lt, ls, a, b, zeta_inf(md, lt, ls, a, b), sigma_inf(md, lt, ls, a, b)};
-}
+CompInfo make_comp(const Medium& md, int lt, int ls, int a, int b);
 
 // learned form: image ladder + network, and the trained domain
 struct SurrogateDomain {
