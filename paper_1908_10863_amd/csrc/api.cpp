@@ -1125,7 +1125,7 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
   std::vector<int32_t> pptr(P->nleaves + 1, 0), psrc;
   std::vector<int32_t> rptr(P->nleaves + 1, 0), rsrc;
   std::vector<int64_t> rvoff;
-  std::vector<int32_t> rp_t, rp_s, rp_c;
+  std::vector<int32_t> rtgt, rcomp;  // per entry: the target leaf's first point, the component
   // reaction rows: entry e's target rows have partial sums at rrow[e] + i;
   // work units of kRPUnitRows rows (entry, first row, target count)
   std::vector<int32_t> rrow, runits, runits16;
@@ -1154,12 +1154,8 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
       rsrc.push_back(r.start);
       rsrc.push_back(r.count);
       rvoff.push_back(voff);
-      for (int64_t i = 0; i < B.boxes[b].count; ++i)
-        for (int j = 0; j < r.count; ++j) {
-          rp_t.push_back((int32_t)(B.boxes[b].start + i));
-          rp_s.push_back(r.start + j);
-          rp_c.push_back(r.comp);
-        }
+      rtgt.push_back((int32_t)B.boxes[b].start);
+      rcomp.push_back(r.comp);
       voff += B.boxes[b].count * (int64_t)r.count;
     }
     rptr[li + 1] = (int32_t)(rsrc.size() / 2);
@@ -1424,16 +1420,19 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
   P->stats.n_sommerfeld_tasks = (int64_t)B.tasks.size();
   P->stats.ops_seconds = seconds_since(tphase);
   // ---- reaction near field values
-  const int64_t npairs = (int64_t)rp_t.size();
+  const int64_t npairs = voff;
   if ((rc = dev_alloc(P, &P->rp_val, (size_t)npairs))) return rc;
   if (npairs > 0) {
     int32_t *dt = nullptr, *ds = nullptr, *dc = nullptr;
     FMM_HIP_TRY(hipMalloc(&dt, npairs * 4));
     FMM_HIP_TRY(hipMalloc(&ds, npairs * 4));
     FMM_HIP_TRY(hipMalloc(&dc, npairs * 4));
-    FMM_HIP_TRY(hipMemcpyAsync(dt, rp_t.data(), npairs * 4, hipMemcpyHostToDevice, st));
-    FMM_HIP_TRY(hipMemcpyAsync(ds, rp_s.data(), npairs * 4, hipMemcpyHostToDevice, st));
-    FMM_HIP_TRY(hipMemcpyAsync(dc, rp_c.data(), npairs * 4, hipMemcpyHostToDevice, st));
+    if ((rc = gpu_expand_pairs(P, rtgt, rcomp, dt, ds, dc, st))) {
+      hipFree(dt);
+      hipFree(ds);
+      hipFree(dc);
+      return rc;
+    }
     const auto ts = std::chrono::steady_clock::now();
     if (sur && sur->kind == 1) {
       int64_t nfb = 0;

@@ -2554,6 +2554,52 @@ int gpu_round_f32(const double* a, int64_t n, float* b, hipStream_t st) {
   return FMMLM_OK;
 }
 
+// One wave per work unit of the reaction near field (rows of one entry): the
+// pairs' indices in rp_val's order.  Bound by its 12 bytes a pair of writes;
+// listing 12.1 M pairs on the host and copying the lists (145 MB) took
+// about 65 ms of a plan; the launch takes 0.025 ms.
+__global__ void __launch_bounds__(256)
+expand_pairs_kernel(int64_t nunits, const int32_t* __restrict__ units, const int32_t* __restrict__ rng,
+                    const int64_t* __restrict__ voff, const int32_t* __restrict__ tgt0,
+                    const int32_t* __restrict__ comp, int32_t* __restrict__ tpt, int32_t* __restrict__ spt,
+                    int32_t* __restrict__ cmp) {
+  const int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (u >= nunits) return;
+  const int lane = threadIdx.x & 63;
+  const int e = units[3 * u], r0 = units[3 * u + 1], r1 = min(r0 + kRPUnitRows, units[3 * u + 2]);
+  const int s0 = rng[2 * e], sc = rng[2 * e + 1], t0 = tgt0[e], c = comp[e];
+  for (int i = r0; i < r1; ++i) {
+    const int64_t v = voff[e] + (int64_t)i * sc;
+    for (int j = lane; j < sc; j += 64) {
+      tpt[v + j] = t0 + i;
+      spt[v + j] = s0 + j;
+      cmp[v + j] = c;
+    }
+  }
+}
+
+int gpu_expand_pairs(fmmlm_plan_s* P, const std::vector<int32_t>& tgt0, const std::vector<int32_t>& comp,
+                     int32_t* tpt, int32_t* spt, int32_t* cmp, hipStream_t st) {
+  if (P->n_rp_units == 0) return FMMLM_OK;
+  const size_t n = tgt0.size();
+  int32_t* d = nullptr;
+  FMM_HIP_TRY(hipMalloc(&d, 2 * n * sizeof(int32_t)));
+  hipError_t e = hipMemcpyAsync(d, tgt0.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = hipMemcpyAsync(d + n, comp.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) {
+    expand_pairs_kernel<<<(unsigned)((P->n_rp_units + 3) / 4), 256, 0, st>>>(P->n_rp_units, P->rp_units, P->rp_src,
+                                                                           P->rp_voff, d, d + n, tpt, spt, cmp);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  (void)hipFree(d);
+  if (e != hipSuccess) {
+    set_last_error(std::string("reaction near-field pairs: ") + hipGetErrorString(e));
+    return FMMLM_EDEVICE;
+  }
+  return FMMLM_OK;
+}
+
 int gpu_build_fp32(fmmlm_plan_s* P, hipStream_t st) {
   const int64_t nt = P->nops * (int64_t)P->nrk * (32 * P->mrt);
   if (nt > 0) to_f32_kernel<<<(unsigned)((nt + 255) / 256), 256, 0, st>>>(P->Tfree, nt, P->Tfree32);

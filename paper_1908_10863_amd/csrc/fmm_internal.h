@@ -401,6 +401,10 @@ int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st);
 constexpr int kM2LVariants = 6;  // FP32 M2L tile shapes the autotuner tries
 constexpr int kBatchShapes = 5;  // batched FP32 M2L tile shapes (each also persistent)
 int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st);
+// target point, source point and component of every reaction near-field pair,
+// in the order of rp_val (entry by entry, rows of sources); tgt0, comp: per entry
+int gpu_expand_pairs(fmmlm_plan_s* P, const std::vector<int32_t>& tgt0, const std::vector<int32_t>& comp,
+                     int32_t* tpt, int32_t* spt, int32_t* cmp, hipStream_t st);
 // b[i] = (float)a[i], i < n (the FP32 form's copy of the reaction near-field values)
 int gpu_round_f32(const double* a, int64_t n, float* b, hipStream_t st);
 int gpu_build_fp32(fmmlm_plan_s* P, hipStream_t st);
