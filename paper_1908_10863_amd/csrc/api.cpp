@@ -760,7 +760,7 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
       P->mrt = (mr0 + 1) / 2 * 2;
       if (P->mrt < 2) P->mrt = 2;
       P->nrk = (nr0 + 15) / 16 * 16;
-      P->tile_cols = (P->mrt <= 4) ? 128 : 64;
+      P->tile_cols = (P->fp32 && P->mrt <= 4) ? 128 : 64;
     }
     const int TBc = P->tile_cols;
     const int nfo = (int)P->n_free_ops;

@@ -813,123 +813,140 @@ __global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfre
 }
 
 // M2L as GEMMs (FP64 form).  A step is one real-form operator T_op (nr x nr,
-// free space or a reaction component) applied to up to TB gathered source
+// free space or a reaction component) applied to up to 64 gathered source
 // expansions (a missing source is a zero column); the plan's units are
 // operator-major chunks of a few steps for the same target columns.  A
 // unit writes its product to W, and the slot reduction adds each target's
 // partials in order.
 // FP64 on the matrix cores (v_mfma_f64_16x16x4f64, lane layout as in
-// m2l_batch64_kernel): four waves, 2 x 2 over the tile of 32 MRT rows x TB
-// columns, each owning MRT x TB / 32 blocks of 16 x 16; operator and operand
-// slices of KC columns double-buffered in LDS (one barrier a slice, global loads
-// two slices ahead).  A 16-column block whose two 8-column groups hold no source
-// in a step is skipped (exact).
+// m2l_batch64_kernel): four waves, WR groups of RBW 16-row blocks x 4 / WR
+// groups of WR 16-column blocks.  A wave takes its operator rows straight from
+// global memory into the fragments, batches of kGmKB k-steps one batch ahead; only
+// the gathered sources, which all row groups read, go through LDS (slices of 64
+// coefficients, loads a slice ahead).  A column's source is the same for a whole
+// wave, so its index is a scalar load: a staging loop with per-lane indices
+// waited for them, and by vmcnt's order for every operator load issued before
+// them, in each slice (matrix cores 38 % busy on the million-charge workload).
+// One operand buffer, so that three blocks fit a CU (two buffers, two blocks:
+// 1.42 against 1.30 ms), and the row blocks that (p+1)^2 needs, not a power of two.
+// Alone at p = 10, N = 2^20: 1.95 -> 1.30 ms (matrix cores 62 % busy); p = 8,
+// 16,411 charges: 0.61 -> 0.29 ms.  Measured and not kept: 8 k-steps a batch
+// (2 % to 50 % slower), 2 (the same), an XCD-contiguous unit order (10 % to 35 %
+// slower: units differ in steps).  A 16-column block whose two
+// 8-column groups hold no source in a step is skipped (exact).
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-template <int MRT, int TB>
-__global__ void __launch_bounds__(256)
-m2l_gemm_kernel(int nr, int nrk, int64_t unit0, const int32_t* __restrict__ unit_s,
+constexpr int kGmTB = 64;     // target columns of a unit
+constexpr int kGmKS = 64;     // coefficients of an operand slice
+constexpr int kGmKB = 4;      // k-steps (of 4) of an operator batch
+constexpr int kGmLd = kGmTB + 1;
+template <int RBW, int WR>
+__global__ void __launch_bounds__(256, 2)
+m2l_gemm_kernel(int nr, int nrk, int mr, int64_t unit0, const int32_t* __restrict__ unit_s,
                 const int32_t* __restrict__ step_op, const int32_t* __restrict__ step_kind,
                 const int32_t* __restrict__ step_src, const int32_t* __restrict__ step_mask,
                 const int32_t* __restrict__ unit_mask, unsigned parts, const double* __restrict__ T,
                 const double* __restrict__ M, double* __restrict__ W) {
   far_chain_priority();
-  constexpr int KC = (MRT <= 4) ? 16 : 8;
-  constexpr int MR = 32 * MRT;
-  constexpr int CB = TB / 32;       // 16-column blocks per wave
-  constexpr int TS = MR + 4;        // LDS row strides (doubles), padded against bank conflicts
-  constexpr int BSR = TB + 1;       // (the operand slice is stored transposed)
-  constexpr int NTR = KC * MR / 256;
-  constexpr int NBR = KC * TB / 256;
-  static_assert(NTR * 256 == KC * MR && NBR * 256 == KC * TB, "slice must split evenly over the threads");
-  __shared__ double Ts[2][KC * TS];
-  __shared__ double Bs[2][KC * BSR];
+  constexpr int CBW = WR;            // 16-column blocks of a wave
+  constexpr int COLS = kGmTB / 4;    // columns a wave stages
+  __shared__ double Bs[kGmKS * kGmLd];
   const int64_t unit = unit0 + blockIdx.x;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int row0 = (wave & 1) * (MR / 2), col0 = (wave >> 1) * (TB / 2);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int rb0 = (wave % WR) * RBW, col0 = (wave / WR) * CBW * 16;
   const int li = lane & 15, lk = lane >> 4;
-  doublex4 acc[MRT][CB];
+  doublex4 acc[RBW][CBW];
 #pragma unroll
-  for (int i = 0; i < MRT; ++i)
+  for (int i = 0; i < RBW; ++i)
 #pragma unroll
-    for (int j = 0; j < CB; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < CBW; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
   const int s0 = unit_s[2 * unit], s1 = unit_s[2 * unit + 1];
-  const int nch = nrk / KC;
-  const int total = (s1 - s0) * nch;
-  double rt[NTR], rb[NBR];
-  auto load = [&](int q) {
-    const int s = s0 + q / nch, k0 = (q % nch) * KC;
-    const double* Tc = T + ((int64_t)step_op[s] * nrk + k0) * MR;
+  const int64_t oplen = (int64_t)nrk * mr;
+  // the wave's columns of slice [k0, k0 + 64) of step s (lane = coefficient)
+  double rb[COLS];
+  auto load_b = [&](int s, int k0) {
     const bool on = (parts & (unsigned)step_kind[s]) != 0;
-    const int32_t* src = step_src + (int64_t)s * TB;
+    const int32_t* src = step_src + (int64_t)s * kGmTB + wave * COLS;
+    const int k = k0 + lane;
 #pragma unroll
-    for (int r = 0; r < NTR; ++r) rt[r] = Tc[tid + 256 * r];
-#pragma unroll
-    for (int r = 0; r < NBR; ++r) {
-      const int i = tid + 256 * r, col = i / KC, k = k0 + i % KC;
-      const int sb = on ? src[col] : -1;
-      rb[r] = (sb >= 0 && k < nr) ? M[(int64_t)sb * nr + k] : 0.0;
+    for (int c = 0; c < COLS; ++c) {
+      const int sb = on ? src[c] : -1;
+      rb[c] = 0.0;
+      if (sb >= 0 && k < nr) rb[c] = M[(int64_t)sb * nr + k];
     }
   };
-  auto stash = [&](int buf) {
+  auto stash_b = [&]() {
 #pragma unroll
-    for (int r = 0; r < NTR; ++r) {
-      const int i = tid + 256 * r;
-      Ts[buf][(i / MR) * TS + (i % MR)] = rt[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NBR; ++r) {
-      const int i = tid + 256 * r;
-      Bs[buf][(i % KC) * BSR + i / KC] = rb[r];
-    }
+    for (int c = 0; c < COLS; ++c) Bs[lane * kGmLd + wave * COLS + c] = rb[c];
   };
-  if (total > 0) {
-    load(0);
-    stash(0);
-    if (total > 1) load(1);
+  // operator batch at Tp (columns k .. k + 15 of a step's operator, this lane's row and column)
+  const int64_t tlane = (int64_t)lk * mr + rb0 * 16 + li;
+  double an[kGmKB][RBW];
+  auto load_a = [&](const double* Tp) {
+#pragma unroll
+    for (int t = 0; t < kGmKB; ++t)
+#pragma unroll
+      for (int i = 0; i < RBW; ++i) an[t][i] = Tp[(int64_t)(4 * t) * mr + 16 * i];
+  };
+  if (s0 < s1) {
+    load_a(T + step_op[s0] * oplen + tlane);
+    load_b(s0, 0);
+    stash_b();
   }
   __syncthreads();
-  for (int q = 0; q < total; ++q) {
-    // 16-column blocks of this wave that hold a source in this step
-    const int sq = s0 + q / nch;
-    const unsigned msk = (parts & (unsigned)step_kind[sq]) ? (unsigned)step_mask[sq] : 0u;
-    const unsigned wmsk = msk >> (col0 >> 3);
-    const double* Tb = Ts[q & 1];
-    const double* Bb = Bs[q & 1];
+  for (int s = s0; s < s1; ++s) {
+    const double* Ts = T + step_op[s] * oplen + tlane;
+    const double* Tnext = T + step_op[min(s + 1, s1 - 1)] * oplen + tlane;  // (the last one is not used)
+    const unsigned wmsk =
+        ((parts & (unsigned)step_kind[s]) ? (unsigned)step_mask[s] : 0u) >> (col0 >> 3);
+    for (int k0 = 0; k0 < nrk; k0 += kGmKS) {
+      const int kn = min(nrk, k0 + kGmKS);
+      const bool last = kn == nrk;
+      const bool more = !last || s + 1 < s1;
+      if (more) load_b(last ? s + 1 : s, last ? 0 : kn);
+      const double* Bb = Bs + col0 + li;
+      for (int k = k0; k < kn; k += 4 * kGmKB) {
+        double a[kGmKB][RBW];
 #pragma unroll
-    for (int ks = 0; ks < KC; ks += 4) {
-      // operator columns (and operand rows) from nr on are zero padding
-      if ((q % nch) * KC + ks >= nr) break;
-      double a[MRT];
+        for (int t = 0; t < kGmKB; ++t)
 #pragma unroll
-      for (int i = 0; i < MRT; ++i) a[i] = Tb[(ks + lk) * TS + row0 + 16 * i + li];
+          for (int i = 0; i < RBW; ++i) a[t][i] = an[t][i];
+        const int kb = k + 4 * kGmKB;
+        load_a(kb < nrk ? Ts + (int64_t)kb * mr : Tnext);
 #pragma unroll
-      for (int j = 0; j < CB; ++j) {
-        if (!((wmsk >> (2 * j)) & 3u)) continue;
-        const double bv = Bb[(ks + lk) * BSR + col0 + 16 * j + li];
+        for (int t = 0; t < kGmKB; ++t) {
+          // operator columns (and operand rows) from nr on are zero padding
+          if (k + 4 * t >= nr) break;
 #pragma unroll
-        for (int i = 0; i < MRT; ++i) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bv, acc[i][j], 0, 0, 0);
+          for (int j = 0; j < CBW; ++j) {
+            if (!((wmsk >> (2 * j)) & 3u)) continue;
+            const double bv = Bb[(k - k0 + 4 * t + lk) * kGmLd + 16 * j];
+#pragma unroll
+            for (int i = 0; i < RBW; ++i)
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][i], bv, acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+      if (more) {
+        __syncthreads();
+        stash_b();
+        __syncthreads();
       }
     }
-    if (q + 1 < total) {
-      // the other buffer was last read before the previous barrier
-      stash((q & 1) ^ 1);
-      if (q + 2 < total) load(q + 2);
-    }
-    __syncthreads();
   }
   // 16-column blocks holding a group the unit touches are stored (the reduction
   // reads the touched groups only)
   const unsigned uwm = (unsigned)unit_mask[unit] >> (col0 >> 3);
-  double* Wu = W + unit * (int64_t)TB * MR;
+  double* Wu = W + unit * (int64_t)kGmTB * mr;
 #pragma unroll
-  for (int j = 0; j < CB; ++j) {
+  for (int j = 0; j < CBW; ++j) {
     if (!((uwm >> (2 * j)) & 3u)) continue;
 #pragma unroll
-    for (int i = 0; i < MRT; ++i)
+    for (int i = 0; i < RBW; ++i) {
+      if (16 * (rb0 + i) >= nr) break;
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-        Wu[(int64_t)(col0 + 16 * j + li) * MR + row0 + 16 * i + lk + 4 * v] = acc[i][j][v];
+      for (int v = 0; v < 4; ++v) Wu[(int64_t)(col0 + 16 * j + li) * mr + 16 * (rb0 + i) + lk + 4 * v] = acc[i][j][v];
+    }
   }
 }
 
@@ -2897,28 +2914,34 @@ int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st) {
   return rc;
 }
 
-// The FP64 tile GEMM over units [unit0, unit0 + n) of one tile structure.
-// tb: the tile width of the structure (P->tile_cols for M2L, P->xl_tile_cols
-// for the translations).
-int launch_gemm64(const fmmlm_plan_s* P, int tb, int64_t unit0, int64_t n, const int32_t* unit_s,
-                  const int32_t* step_op, const int32_t* step_kind, const int32_t* step_src,
-                  const int32_t* step_mask, const int32_t* unit_mask, unsigned parts, const double* T,
-                  const double* X, double* W, hipStream_t st) {
+// The FP64 M2L GEMM over the chunk units [unit0, unit0 + n).  The wave grid per
+// number of 16-row blocks: four row groups where they come out even (or nearly),
+// else two, one for three blocks and fewer; an operator's rows have 32 mrt >=
+// 16 RBW WR of them (the blocks past (p+1)^2 are zero rows).
+int launch_gemm64(const fmmlm_plan_s* P, int64_t unit0, int64_t n, unsigned parts, const double* M, double* W,
+                  hipStream_t st) {
   if (n <= 0) return FMMLM_OK;
   const int nr = (P->p + 1) * (P->p + 1);
-#define GEMM_CASE(R, TB)                                                                                     \
-  if (P->mrt == R && tb == TB) {                                                                             \
-    m2l_gemm_kernel<R, TB><<<(unsigned)n, 256, 0, st>>>(nr, P->nrk, unit0, unit_s, step_op, step_kind,        \
-                                                        step_src, step_mask, unit_mask, parts, T, X, W);     \
-    return FMMLM_OK;                                                                                         \
+  if (P->tile_cols != kGmTB) {
+    set_last_error("internal: M2L chunks do not match the FP64 kernel");
+    return FMMLM_EUNSUPPORTED;
   }
-  GEMM_CASE(2, 128)
-  GEMM_CASE(4, 128)
-  GEMM_CASE(6, 64)
-  GEMM_CASE(8, 64)
-  GEMM_CASE(10, 64)
-#undef GEMM_CASE
-  return FMMLM_EUNSUPPORTED;
+#define GM(NB, RBW, WR)                                                                                      \
+  case NB:                                                                                                   \
+    static_assert(16 * RBW * WR <= 32 * (((NB + 1) / 2 + 1) / 2 * 2) && RBW * WR >= NB, "operator rows");     \
+    m2l_gemm_kernel<RBW, WR><<<(unsigned)n, 256, 0, st>>>(nr, P->nrk, 32 * P->mrt, unit0, P->unit_s,           \
+                                                          P->step_op, P->step_kind, P->step_src,             \
+                                                          P->step_mask, P->unit_mask, parts, P->Tfree, M, W); \
+    break;
+  switch ((nr + 15) / 16) {
+    GM(1, 1, 1) GM(2, 2, 1) GM(3, 3, 1) GM(4, 2, 2) GM(6, 3, 2) GM(7, 4, 2) GM(8, 2, 4) GM(9, 5, 2)
+    GM(11, 3, 4) GM(13, 7, 2) GM(15, 4, 4) GM(16, 4, 4) GM(19, 5, 4)
+    default:
+      return FMMLM_EUNSUPPORTED;
+  }
+#undef GM
+  FMM_HIP_TRY(hipGetLastError());
+  return FMMLM_OK;
 }
 
 // M2M (up = true, into M) or L2L (into Lx) of one level through the
@@ -3201,8 +3224,7 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
   const int64_t n64 = P->fp32 ? 0 : P->nunits - P->unit_split;
   const int64_t n32 = P->fp32 ? P->nunits - P->unit_split : 0;
   auto gemm64 = [&]() -> int {
-    return launch_gemm64(P, P->tile_cols, P->unit_split, n64, P->unit_s, P->step_op, P->step_kind, P->step_src,
-                         P->step_mask, P->unit_mask, parts, P->Tfree, M, P->Wm2l, st);
+    return launch_gemm64(P, P->unit_split, n64, parts, M, P->Wm2l, st);
   };
   // the sparse top levels write other boxes than the tiles: on their own
   // stream (unprofiled), joined before L2L
