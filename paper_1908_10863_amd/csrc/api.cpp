@@ -778,11 +778,16 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
       // work items: runs of kSpItemRounds rounds of sp_ne entries (the block's
       // threads hold sp_ne entries x the coefficients (n, m >= 0) in groups of
       // four orders; LDS holds their source expansions and operator tables,
-      // then their sums, at most 60 KiB)
-      const int nc = P->nc, ng = P->ng, nr = (P->p + 1) * (P->p + 1);
-      int tps = 0;
-      for (int n = 0; n <= P->p; ++n) tps += (n + 4) / 4;
-      P->sp_ne = std::max(1, std::min(kSpThreads / tps, 61440 / (std::max(nr + ng, nc) * 16)));
+      // then their sums, at most kSpLds)
+      const int nc = P->nc;
+      int tps = 0, rows = 0;  // threads of an entry; its source rows padded to four orders
+      for (int n = 0; n <= P->p; ++n) {
+        tps += (n + 4) / 4;
+        rows += (n + 4) / 4 * 4;
+      }
+      P->sp_tps = tps;
+      P->sp_bytes = std::max(P->ngs * 8 + rows * 16, nc * 16);
+      P->sp_ne = std::max(1, std::min(kSpThreads / tps, kSpLds / P->sp_bytes));
       P->sp_threads = (P->sp_ne * tps + 63) / 64 * 64;
       const int run = kSpItemRounds * P->sp_ne;
       std::vector<int32_t> items, iptr(1, 0);
@@ -1364,7 +1369,8 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
   P->stats.lists_seconds = seconds_since(tphase);
   tphase = std::chrono::steady_clock::now();
   // ---- operators: free-space harmonics and reaction Sommerfeld tables
-  if ((rc = dev_alloc(P, &P->G, (size_t)std::max<int64_t>(P->nops, 1) * P->ng * 2))) return rc;
+  if ((rc = dev_alloc(P, &P->G, (size_t)std::max<int64_t>(P->nops, 1) * P->ngs))) return rc;
+  if ((rc = dev_alloc(P, &P->E, (size_t)std::max<int64_t>(P->nops, 1) * (2 * p + 1) * 2))) return rc;
   double* tables = nullptr;
   if (!B.tasks.empty()) {
     FMM_HIP_TRY(hipMalloc(&tables, B.tasks.size() * (size_t)P->ng * sizeof(double)));
@@ -1769,6 +1775,8 @@ static int plan_impl(int32_t n_interfaces, const double* z_interfaces, const dou
   P->p = p;
   P->nc = ncoef(p);
   P->ng = ncoef(2 * p);
+  P->ngs = kGPad + (2 * p + 1) * (2 * p + 1) + kGPadEnd;
+  P->ngs += P->ngs & 1;
   P->opts = o;
   P->fp32 = (o.precision == FMMLM_FP32_COMPENSATED);
   try {

@@ -133,33 +133,66 @@ __device__ inline int isqrt_row(int t) {
 }
 
 // ---------------------------------------------------------------- operators
-__global__ void build_free_ops_kernel(const int* __restrict__ off, int nops, int p2, int ng,
-                                      const double* __restrict__ coefA, cplx* __restrict__ G) {
+// An operator's table in the frame turned so that its offset has azimuth 0: the
+// real g(j, k) = G(j, k) e^{-i k phi} of eqs. metole, metoleimage1 for
+// -j <= k <= j (g(j, -k) = (-1)^k g(j, k)) at [kGPad + j j + j + k], j <= 2p, with
+// zeros before and after; its phases e^{i k phi}, k <= 2p, in a table of their own.
+__device__ inline bool g_index(int i, int p2, int* j, int* k) {
+  i -= kGPad;
+  if (i < 0 || i >= (p2 + 1) * (p2 + 1)) return false;
+  int r = (int)sqrt((double)i);
+  while (r * r > i) --r;
+  while ((r + 1) * (r + 1) <= i) ++r;
+  *j = r;
+  *k = i - r * r - r;
+  return true;
+}
+
+__global__ void build_free_ops_kernel(const int* __restrict__ off, int nops, int p2, int ngs,
+                                      const double* __restrict__ coefA, double* __restrict__ G,
+                                      cplx* __restrict__ E) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)nops * ng) return;
-  const int op = (int)(t / ng), c = (int)(t % ng);
-  const int j = isqrt_row(c), k = c - cidx(j, 0);
-  if (j > p2) return;
+  if (t >= (int64_t)nops * ngs) return;
+  const int op = (int)(t / ngs), c = (int)(t % ngs);
   const double dx = off[3 * op], dy = off[3 * op + 1], dz = off[3 * op + 2];
-  const cplx I = irregular_nm(j, k, dx, dy, dz);
-  G[(int64_t)op * ng + c] = (kInv4Pi / coefA[cidx(j, k)]) * I;
+  if (c <= p2) {
+    double s, co;
+    sincos(c * atan2(dy, dx), &s, &co);
+    E[(int64_t)op * (p2 + 1) + c] = cmk(co, s);
+  }
+  int j, k;
+  double g = 0.0;
+  if (g_index(c, p2, &j, &k)) {
+    const int ak = abs(k);
+    g = (kInv4Pi / coefA[cidx(j, ak)]) * irregular_nm(j, ak, sqrt(dx * dx + dy * dy), 0.0, dz).re;
+    if (k < 0) g *= sgn1(k);
+  }
+  G[(int64_t)op * ngs + c] = g;
 }
 
 __global__ void build_reaction_ops_kernel(const int* __restrict__ task, const double* __restrict__ phi,
                                           const double* __restrict__ Sl, int nops, int op0, int p2,
-                                          int ng, const double* __restrict__ coefA,
-                                          const double* __restrict__ tables, cplx* __restrict__ G) {
+                                          int ng, int ngs, const double* __restrict__ coefA,
+                                          const double* __restrict__ tables, double* __restrict__ G,
+                                          cplx* __restrict__ E) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)nops * ng) return;
-  const int op = (int)(t / ng), c = (int)(t % ng);
-  const int j = isqrt_row(c), k = c - cidx(j, 0);
-  if (j > p2) return;
-  const double SI = tables[(int64_t)task[op] * ng + c];
-  const double cj = sqrt((2.0 * j + 1.0) / (4.0 * kPi));
-  double s, co;
-  sincos(k * phi[op], &s, &co);
-  const double f = Sl[op] * cj * SI * kInv4Pi / coefA[cidx(j, k)];
-  G[(int64_t)(op0 + op) * ng + c] = cmk(f * co, f * s);
+  if (t >= (int64_t)nops * ngs) return;
+  const int op = (int)(t / ngs), c = (int)(t % ngs);
+  if (c <= p2) {
+    double s, co;
+    sincos(c * phi[op], &s, &co);
+    E[(int64_t)(op0 + op) * (p2 + 1) + c] = cmk(co, s);
+  }
+  int j, k;
+  double g = 0.0;
+  if (g_index(c, p2, &j, &k)) {
+    const int ak = abs(k);
+    const double SI = tables[(int64_t)task[op] * ng + cidx(j, ak)];
+    const double cj = sqrt((2.0 * j + 1.0) / (4.0 * kPi));
+    g = Sl[op] * cj * SI * kInv4Pi / coefA[cidx(j, ak)];
+    if (k < 0) g *= sgn1(k);
+  }
+  G[(int64_t)(op0 + op) * ngs + c] = g;
 }
 
 // ---------------------------------------------------------------- eval kernels
@@ -600,40 +633,42 @@ __global__ void build_xlate_ops_kernel(int p, int nrk, int mr, const double* __r
 
 // M2L on the sparse top levels (few boxes, many distinct operators).  A work
 // item is a run of at most kSpItemRounds * ne entries of one target box; its
-// block takes ne entries a round.  The operator of eq. metole / eq.
-// metoleimage1 in its Hankel-Toeplitz form reads the compact table G of the
-// entry's operator at (n + n', m' - m) (reaction entries act on the mirrored
-// polarization-source expansion).  Thread (slot, n, mb) applies entry slot of
-// the round to the four outputs (n, 4 mb .. 4 mb + 3).  Along m' the four
-// outputs need G at four consecutive orders, so a window slides by one new LDS
-// read per m' (four steps at a time over seven orders), and each source
-// coefficient read serves four outputs.  The slots' sums meet in LDS in a
-// fixed order and go to the item's partial; a second kernel adds a box's
+// block takes ne entries a round.  In the frame turned to an operator's azimuth
+// its table g is real, so the real parts of the local expansion come from the
+// real parts of the source and the imaginary ones from the imaginary ones
+// (reaction entries act on the mirrored polarization-source expansion):
+//   Re L_nm = sum g(n+n', m'-m) a + (-1)^m sum g(n+n', m'+m) a,   m' >= 0,
+//   Im L_nm = sum g(n+n', m'-m) b - (-1)^m sum g(n+n', m'+m) b,
+// a + i b = e^{i m' phi} M_{n'm'} (a halved at m' = 0), turned back by
+// e^{-i m phi}: 4 multiply-adds an (output, m' >= 0) pair, where the complex sum
+// over all m' takes 4 for each sign of m'.  Thread (slot, n, mb) applies entry
+// slot of the round to the outputs (n, 4 mb .. 4 mb + 3): along m' the four need g
+// in two windows of seven orders (differences, sums) that slide four steps at a
+// time, eight LDS reads for 64 multiply-adds; g holds the negative orders
+// too and source rows are padded with zeros to steps of four, so the loop has no
+// selects and no tail (outputs m > n are dropped).  The slots' sums meet in LDS
+// in a fixed order and go to the item's partial; a second kernel adds a box's
 // partials, in item order, to its local expansion.  FP64 throughout.
-__device__ inline int sp_threads_per_slot(int p) {
-  int t = 0;
-  for (int n = 0; n <= p; ++n) t += (n + 4) / 4;
-  return t;
-}
+// Bound by FP64 issue and LDS bank conflicts; 24,840 pairs at p = 10 alone: 0.166 -> 0.106 ms.
+__device__ inline int sp_row(int n) { return 4 * (n / 4 + 1) * (2 * (n / 4) + (n & 3)); }
 
 __global__ void __launch_bounds__(kSpThreads)
-m2l_sparse_kernel(int p, int nc, int ng, int ne, const int32_t* __restrict__ items,
+m2l_sparse_kernel(int p, int nc, int ngs, int ne, int tps, const int32_t* __restrict__ items,
                   const int32_t* __restrict__ ptr, const int32_t* __restrict__ nfree,
-                  const int32_t* __restrict__ src, const int32_t* __restrict__ opv, const cplx* __restrict__ G,
-                  const double* __restrict__ coefA, const double* __restrict__ M, unsigned parts,
-                  cplx* __restrict__ part) {
+                  const int32_t* __restrict__ src, const int32_t* __restrict__ opv, const double* __restrict__ G,
+                  const cplx* __restrict__ E, const double* __restrict__ coefA, const double* __restrict__ M,
+                  unsigned parts, cplx* __restrict__ part) {
   far_chain_priority();
   extern __shared__ char smem[];
-  const int nr = (p + 1) * (p + 1);
-  cplx* Mf = reinterpret_cast<cplx*>(smem);  // [ne][nr] full source expansions, A and sign folded
-  cplx* Gs = Mf + ne * nr;                   // [ne][ng]
-  cplx* red = Mf;                            // [ne][nc] after the last round (aliases the above)
+  const int nr = (p + 1) * (p + 1), nm = sp_row(p + 1), p2 = 2 * p;
+  cplx* Ms = reinterpret_cast<cplx*>(smem);             // [ne][nm] turned source rows, A and sign folded
+  double* Gs = reinterpret_cast<double*>(Ms + ne * nm);  // [ne][ngs]
+  cplx* red = Ms;                                       // [ne][nc] after the last round (aliases the above)
   const int tid = threadIdx.x;
   const int b = items[3 * blockIdx.x];
   const int ef = ptr[b] + nfree[b];
   const int e0 = max(items[3 * blockIdx.x + 1], (parts & FMMLM_FREE) ? ptr[b] : ef);
   const int e1 = min(items[3 * blockIdx.x + 2], (parts & FMMLM_REACTION) ? ptr[b + 1] : ef);
-  const int tps = sp_threads_per_slot(p);
   const int slot = tid / tps;
   const bool active = slot < ne;
   int n = 0, mb = tid - slot * tps;
@@ -643,97 +678,88 @@ m2l_sparse_kernel(int p, int nc, int ng, int ne, const int32_t* __restrict__ ite
       ++n;
     }
   const int m0 = 4 * mb;
-  double ar[4] = {0.0, 0.0, 0.0, 0.0}, ai[4] = {0.0, 0.0, 0.0, 0.0};
+  double lr[4] = {0.0, 0.0, 0.0, 0.0}, li[4] = {0.0, 0.0, 0.0, 0.0};
   for (int r0 = e0; r0 < e1; r0 += ne) {
     const int cnt = min(ne, e1 - r0);
     __syncthreads();  // the previous round's readers are done
-    for (int i = tid; i < cnt * nr; i += blockDim.x) {
-      const int sl = i / nr, k = i - sl * nr;
-      const int e = r0 + sl;
-      const int n2 = (int)sqrt((double)k);
-      const int m2 = k - n2 * n2 - n2;  // -n2..n2
-      cplx v = rload(M + (int64_t)src[e] * nr, n2, abs(m2));
-      if (m2 < 0) v = (m2 & 1) ? cmk(-v.re, v.im) : cmk(v.re, -v.im);
-      double f = coefA[cidx(n2, abs(m2))];
-      if (opv[e] < 0 && ((n2 + abs(m2)) & 1)) f = -f;  // mirrored (reaction) entry
-      Mf[i] = f * v;
-    }
-    for (int i = tid; i < cnt * ng; i += blockDim.x) {
-      const int sl = i / ng, k = i - sl * ng;
+    for (int i = tid; i < cnt * (ngs / 2); i += blockDim.x) {
+      const int sl = i / (ngs / 2), k = i - sl * (ngs / 2);
       const int op = opv[r0 + sl];
-      Gs[i] = G[(int64_t)(op < 0 ? ~op : op) * ng + k];
+      reinterpret_cast<double2*>(Gs)[i] =
+          reinterpret_cast<const double2*>(G)[(int64_t)(op < 0 ? ~op : op) * (ngs / 2) + k];
+    }
+    for (int i = tid; i < cnt * nc; i += blockDim.x) {
+      const int sl = i / nc, k = i - sl * nc;
+      const int e = r0 + sl, op = opv[e];
+      const int n2 = isqrt_row(k), m2 = k - cidx(n2, 0);
+      const cplx v = rload(M + (int64_t)src[e] * nr, n2, m2);
+      const cplx u = E[(int64_t)(op < 0 ? ~op : op) * (p2 + 1) + m2];
+      double f = coefA[k] * (m2 ? 1.0 : 0.5);
+      if (op < 0 && ((n2 + m2) & 1)) f = -f;  // mirrored (reaction) entry
+      cplx* row = Ms + sl * nm + sp_row(n2);
+      row[m2] = f * (u * v);
+      if (m2 == n2)
+        for (int q = n2 + 1; q & 3; ++q) row[q] = cmk(0.0, 0.0);
     }
     __syncthreads();
     if (active && slot < cnt) {
-      const cplx* Mrow0 = Mf + slot * nr;
-      const cplx* Ge = Gs + slot * ng;
+      double dr[4] = {0.0, 0.0, 0.0, 0.0}, di[4] = {0.0, 0.0, 0.0, 0.0};
+      double sr[4] = {0.0, 0.0, 0.0, 0.0}, si[4] = {0.0, 0.0, 0.0, 0.0};
+      const double* Ge = Gs + slot * ngs + kGPad;
+      const cplx* Me = Ms + slot * nm;
       for (int n2 = 0; n2 <= p; ++n2) {
         const int N = n + n2;
-        const cplx* Grow = Ge + cidx(N, 0);
-        const cplx* Mrow = Mrow0 + n2 * n2 + n2;  // index by m2
-        // G at order kk < 0 is (-1)^kk conj G at |kk| (read at |kk|, signs by
-        // selects); orders beyond N only serve outputs m > n, which are dropped
-        auto gval = [&](int kk, double& gr, double& gi) {
-          const int ak = min(kk < 0 ? -kk : kk, N);
-          const cplx v = Grow[ak];
-          gr = (kk < 0 && (kk & 1)) ? -v.re : v.re;
-          gi = (kk < 0 && !(kk & 1)) ? -v.im : v.im;
-        };
-        auto cmac = [&](int j, double gr, double gi, const cplx& mv) {
-          ar[j] = fma(gr, mv.re, ar[j]);
-          ar[j] = fma(-gi, mv.im, ar[j]);
-          ai[j] = fma(gr, mv.im, ai[j]);
-          ai[j] = fma(gi, mv.re, ai[j]);
-        };
-        // four steps of m2 at a time over a window of seven orders: wr[i], wi[i]
-        // hold G at order m2 - m0 - 3 + i (the first three carried over)
-        double wr[7], wi[7];
+        const double* gd = Ge + N * N + N - m0 - 3;  // order m' - m0 - 3 + i at [m' + i]
+        const double* gs = Ge + N * N + N + m0;      // order m' + m0 + i at [m' + i]
+        const cplx* Mrow = Me + sp_row(n2);
+        double wd[7], ws[7];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) gval(-n2 - m0 - 3 + i, wr[i], wi[i]);
-        int m2 = -n2;
-        for (; m2 + 3 <= n2; m2 += 4) {
+        for (int i = 0; i < 3; ++i) {
+          wd[i] = gd[i];
+          ws[i] = gs[i];
+        }
+        for (int m2 = 0; m2 <= n2; m2 += 4) {
 #pragma unroll
-          for (int i = 3; i < 7; ++i) gval(m2 - m0 - 3 + i, wr[i], wi[i]);
+          for (int i = 3; i < 7; ++i) {
+            wd[i] = gd[m2 + i];
+            ws[i] = gs[m2 + i];
+          }
           cplx mv[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) mv[q] = Mrow[m2 + q];
 #pragma unroll
           for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) cmac(j, wr[q - j + 3], wi[q - j + 3], mv[q]);
+            for (int j = 0; j < 4; ++j) {
+              dr[j] = fma(wd[q - j + 3], mv[q].re, dr[j]);
+              di[j] = fma(wd[q - j + 3], mv[q].im, di[j]);
+              sr[j] = fma(ws[q + j], mv[q].re, sr[j]);
+              si[j] = fma(ws[q + j], mv[q].im, si[j]);
+            }
 #pragma unroll
           for (int i = 0; i < 3; ++i) {
-            wr[i] = wr[i + 4];
-            wi[i] = wi[i + 4];
+            wd[i] = wd[i + 4];
+            ws[i] = ws[i + 4];
           }
         }
-        // the last steps one at a time (order m2 - m0 - j for output j)
-        double gr[4], gi[4];
+      }
+      const int op = opv[r0 + slot];
 #pragma unroll
-        for (int j = 1; j < 4; ++j) {
-          gr[j] = wr[3 - j];
-          gi[j] = wi[3 - j];
-        }
-        gval(m2 - m0, gr[0], gi[0]);
-        for (; m2 <= n2; ++m2) {
-          const cplx mv = Mrow[m2];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) cmac(j, gr[j], gi[j], mv);
-#pragma unroll
-          for (int j = 3; j > 0; --j) {
-            gr[j] = gr[j - 1];
-            gi[j] = gi[j - 1];
-          }
-          gval(m2 + 1 - m0, gr[0], gi[0]);
-        }
+      for (int j = 0; j < 4; ++j) {
+        if (m0 + j > n) break;
+        // (-1)^m with m = 4 mb + j
+        const cplx v = cmk((j & 1) ? dr[j] - sr[j] : dr[j] + sr[j], (j & 1) ? di[j] + si[j] : di[j] - si[j]);
+        const cplx w = cconj(E[(int64_t)(op < 0 ? ~op : op) * (p2 + 1) + m0 + j]) * v;
+        lr[j] += w.re;
+        li[j] += w.im;
       }
     }
   }
-  __syncthreads();  // the last round's readers of Mf and Gs are done (red aliases them)
+  __syncthreads();  // the last round's readers of Ms and Gs are done (red aliases them)
   if (active) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      if (m0 + j <= n) red[slot * nc + cidx(n, m0 + j)] = cmk(ar[j], ai[j]);
+      if (m0 + j <= n) red[slot * nc + cidx(n, m0 + j)] = cmk(lr[j], li[j]);
   }
   __syncthreads();
   for (int c = tid; c < nc; c += blockDim.x) {
@@ -775,8 +801,9 @@ m2l_sparse_reduce_kernel(int p, int nc, const int32_t* __restrict__ boxes, const
 // constant of eq. metole / eq. metoleimage1 and, for reaction operators, the
 // mirror sign (-1)^{n'+m'} of the polarization-source expansion; rows padded to
 // mr and columns to nrk with zeros.
-__global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfree, const cplx* __restrict__ G,
-                                      int ng, const double* __restrict__ coefA, double* __restrict__ T) {
+__global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfree, const double* __restrict__ G,
+                                      const cplx* __restrict__ E, int ngs, const double* __restrict__ coefA,
+                                      double* __restrict__ T) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t per = (int64_t)nrk * mr;
   if (t >= (int64_t)nops * per) return;
@@ -791,13 +818,10 @@ __global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfre
     rsplit(row, &n, &m, &im);
     // unit input in the real layout -> complex M_{n2,m2} and M_{n2,-m2}
     const cplx mp = im2 ? cmk(0.0, 1.0) : cmk(1.0, 0.0);
-    const cplx* Gop = G + (int64_t)op * ng;
     const int j = n + n2;
-    auto gat = [&](int kk) -> cplx {
-      if (kk >= 0) return Gop[cidx(j, kk)];
-      const cplx w = Gop[cidx(j, -kk)];
-      return ((-kk) & 1) ? cmk(-w.re, w.im) : cmk(w.re, -w.im);
-    };
+    const double* Gj = G + (int64_t)op * ngs + kGPad + j * j + j;
+    const cplx* Eop = E + (int64_t)op * (2 * p + 1);
+    auto gat = [&](int kk) -> cplx { return Gj[kk] * (kk >= 0 ? Eop[kk] : cconj(Eop[-kk])); };
     cplx acc = gat(m2 - m) * mp;
     if (m2 > 0) {
       // M_{n2,-m2} = (-1)^m2 conj(M_{n2,m2})
@@ -2511,9 +2535,9 @@ int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_off, const std::
     int* doff = nullptr;
     FMM_HIP_TRY(hipMalloc(&doff, free_off.size() * sizeof(int)));
     FMM_HIP_TRY(hipMemcpyAsync(doff, free_off.data(), free_off.size() * sizeof(int), hipMemcpyHostToDevice, st));
-    const int64_t tot = (int64_t)nfree * P->ng;
-    build_free_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(doff, nfree, p2, P->ng, P->coefA,
-                                                                         reinterpret_cast<cplx*>(P->G));
+    const int64_t tot = (int64_t)nfree * P->ngs;
+    build_free_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(doff, nfree, p2, P->ngs, P->coefA, P->G,
+                                                                         reinterpret_cast<cplx*>(P->E));
     FMM_HIP_TRY(hipGetLastError());
     FMM_HIP_TRY(hipStreamSynchronize(st));
     hipFree(doff);
@@ -2527,9 +2551,9 @@ int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_off, const std::
     FMM_HIP_TRY(hipMemcpyAsync(dtask, reac_task.data(), nreac * sizeof(int), hipMemcpyHostToDevice, st));
     FMM_HIP_TRY(hipMemcpyAsync(dphi, reac_phi.data(), nreac * sizeof(double), hipMemcpyHostToDevice, st));
     FMM_HIP_TRY(hipMemcpyAsync(dS, reac_S.data(), nreac * sizeof(double), hipMemcpyHostToDevice, st));
-    const int64_t tot = (int64_t)nreac * P->ng;
+    const int64_t tot = (int64_t)nreac * P->ngs;
     build_reaction_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
-        dtask, dphi, dS, nreac, nfree, p2, P->ng, P->coefA, d_tables, reinterpret_cast<cplx*>(P->G));
+        dtask, dphi, dS, nreac, nfree, p2, P->ng, P->ngs, P->coefA, d_tables, P->G, reinterpret_cast<cplx*>(P->E));
     FMM_HIP_TRY(hipGetLastError());
     FMM_HIP_TRY(hipStreamSynchronize(st));
     hipFree(dtask);
@@ -2543,8 +2567,8 @@ int gpu_build_real_ops(fmmlm_plan_s* P, hipStream_t st) {
   if (P->nops == 0) return FMMLM_OK;
   const int64_t tot = P->nops * (int64_t)P->nrk * (32 * P->mrt);
   build_real_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
-      P->p, P->nrk, 32 * P->mrt, (int)P->nops, (int)P->n_free_ops, reinterpret_cast<const cplx*>(P->G), P->ng,
-      P->coefA, P->Tfree);
+      P->p, P->nrk, 32 * P->mrt, (int)P->nops, (int)P->n_free_ops, P->G, reinterpret_cast<const cplx*>(P->E),
+      P->ngs, P->coefA, P->Tfree);
   FMM_HIP_TRY(hipGetLastError());
   FMM_HIP_TRY(hipStreamSynchronize(st));
   return FMMLM_OK;
@@ -3127,10 +3151,9 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
     if (ev) (void)hipEventRecord(ev[stage], st);
     ++stage;
   };
-  const int p = P->p, nc = P->nc, ng = P->ng;
+  const int p = P->p, nc = P->nc;
   double* M = P->M;
   double* Lx = P->Lx;
-  const cplx* G = reinterpret_cast<const cplx*>(P->G);
   mark();
   gather_kernel<<<(unsigned)((P->NP + 255) / 256), 256, 0, st>>>(q, P->puser, P->NP, P->qt, P->qt32);
   mark();
@@ -3235,10 +3258,9 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
   }
   if (P->n_sp_boxes > 0) {
     hipStream_t ss = top_side ? P->s_top : st;
-    m2l_sparse_kernel<<<(unsigned)P->n_sp_items, P->sp_threads,
-                        (size_t)P->sp_ne * std::max(nr + ng, nc) * sizeof(cplx),
-                        ss>>>(p, nc, ng, P->sp_ne, P->sp_items, P->m2l_ptr, P->m2l_nfree, P->m2l_src, P->m2l_op, G,
-                              P->coefA, M, parts, reinterpret_cast<cplx*>(P->Psp));
+    m2l_sparse_kernel<<<(unsigned)P->n_sp_items, P->sp_threads, (size_t)P->sp_ne * P->sp_bytes, ss>>>(
+        p, nc, P->ngs, P->sp_ne, P->sp_tps, P->sp_items, P->m2l_ptr, P->m2l_nfree, P->m2l_src, P->m2l_op, P->G,
+        reinterpret_cast<const cplx*>(P->E), P->coefA, M, parts, reinterpret_cast<cplx*>(P->Psp));
     m2l_sparse_reduce_kernel<<<(unsigned)P->n_sp_boxes, 128, 0, ss>>>(
         p, nc, P->sp_boxes, P->sp_item_ptr, reinterpret_cast<const cplx*>(P->Psp), P->blevel, P->sc_levels,
         P->coefA, Lx);

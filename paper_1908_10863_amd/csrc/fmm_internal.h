@@ -19,6 +19,11 @@ constexpr int kMaxLevel = 20;  // 21-bit quantisation per axis
 // sparse top-level M2L: threads of a block, rounds of entries per work item
 constexpr int kSpThreads = 512;
 constexpr int kSpItemRounds = 1;
+// zeros before an operator's table (orders down to -N - 3 are read) and after it (up to N + 6)
+constexpr int kGPad = 3;
+constexpr int kGPadEnd = 6;
+// LDS of a sparse top-level block: three fit a CU
+constexpr int kSpLds = 53248;
 // batched FP32 form, FP64 top levels: entries per work item
 constexpr int kBatchTopItem = 24;
 // reaction P2P: target rows per work unit (one wave, 8 lanes a row)
@@ -152,7 +157,9 @@ struct fmmlm_plan_s {
   int32_t *m2l_ptr = nullptr;      // [NB + 1] ; free entries first, then reaction
   int32_t *m2l_nfree = nullptr;    // [NB] number of free entries per target box
   int32_t *m2l_src = nullptr, *m2l_op = nullptr;  // op < 0 encodes mirrored source: ~op
-  double* G = nullptr;             // operators [nops][ng] complex (re, im interleaved)
+  double* G = nullptr;             // operators at azimuth 0 [nops][ngs] (kGPad zeros, rows j of orders -j..j, zeros)
+  double* E = nullptr;             // their phases e^{i k phi} [nops][2p + 1] complex
+  int ngs = 0;                     // stride of G (even)
   // M2L as GEMMs over operator-major chunks (a chunk is a tile of its own)
   double* Tfree = nullptr;         // [nops][nrk][32 mrt] real-form operators (free space, then reaction)
   int nrk = 0, mrt = 0;            // padded inner dimension, rows per thread / 32
@@ -178,6 +185,8 @@ struct fmmlm_plan_s {
   int64_t n_sp_items = 0;
   int sp_ne = 1;                   // entries per round of an item's block ...
   int sp_threads = 64;             //   ... and its threads (a multiple of 64)
+  int sp_tps = 1;                  //   ... threads of an entry
+  int sp_bytes = 0;                //   ... LDS of an entry
   double* Psp = nullptr;
   // FP32 form: operator-major chunks; per target box its slots (unit * tile_cols + column)
   int32_t *slot_boxes = nullptr, *slot_ptr = nullptr, *slots = nullptr;
