@@ -472,6 +472,204 @@ static int tune_batch_width(fmmlm_plan_s* P, hipStream_t st) {
   return rc;
 }
 
+// An M2L operator as its frame operator (free space: one per (rho^2, dz);
+// reaction: one per Sommerfeld task, after them), its azimuth, and a key that the
+// operators of one column share: free space by (dx, dy), whose operators differ in
+// dz; reaction by (dx, dy, dz), whose operators differ in the component.  Either
+// way they have one azimuth.
+struct OpFrame {
+  int32_t frame, phi;
+  int64_t key;
+};
+
+void op_frames(const Builder& B, int nfree, int64_t nops, std::vector<OpFrame>* out, std::vector<int>* free_r2dz,
+               std::vector<int>* dirs) {
+  out->assign((size_t)nops, OpFrame{0, 0, 0});
+  std::map<std::pair<int, int>, int> fid, did;
+  auto direction = [&](int dx, int dy) {
+    int a = std::abs(dx), b = std::abs(dy);
+    while (b) {
+      const int t = a % b;
+      a = b;
+      b = t;
+    }
+    if (a == 0) a = 1, dx = 1;  // straight above: azimuth 0
+    const auto k = std::make_pair(dx / a, dy / a);
+    const auto it = did.find(k);
+    if (it != did.end()) return it->second;
+    const int id = (int)(dirs->size() / 2);
+    did[k] = id;
+    dirs->push_back(k.first);
+    dirs->push_back(k.second);
+    return id;
+  };
+  auto key = [](int kind, int dx, int dy, int dz) {
+    return ((int64_t)kind << 60) | ((int64_t)(dx + (1 << 18)) << 40) | ((int64_t)(dy + (1 << 18)) << 20) | (int64_t)(dz + (1 << 18));
+  };
+  for (int o = 0; o < nfree; ++o) {
+    const int dx = B.free_off[3 * o], dy = B.free_off[3 * o + 1], dz = B.free_off[3 * o + 2];
+    const auto k = std::make_pair(dx * dx + dy * dy, dz);
+    auto it = fid.find(k);
+    if (it == fid.end()) {
+      it = fid.emplace(k, (int)(free_r2dz->size() / 2)).first;
+      free_r2dz->push_back(k.first);
+      free_r2dz->push_back(k.second);
+    }
+    (*out)[o] = OpFrame{it->second, direction(dx, dy), key(0, dx, dy, 0)};
+  }
+  const int nf = (int)(free_r2dz->size() / 2);
+  for (const auto& kv : B.reac_op_id) {
+    const int dx = std::get<2>(kv.first), dy = std::get<3>(kv.first), dz = std::get<4>(kv.first);
+    (*out)[nfree + kv.second] = OpFrame{nf + B.reac_task[kv.second], direction(dx, dy), key(1, dx, dy, dz)};
+  }
+}
+
+// The units of target boxes [b0, b1).  A target's entries of one key (and so of
+// one azimuth) are cut into columns of at most kM2LGroupOps operators, about
+// equal; columns with the same operators fill the units, targets in box order.
+// Operator lists with fewer than kM2LFewCols columns are cut into columns of one
+// operator, which other targets share more often.
+int build_m2l_units(fmmlm_plan_s* P, int64_t b0, int64_t b1, const std::vector<int32_t>& mptr,
+                    const std::vector<int32_t>& msrc, const std::vector<int32_t>& mop,
+                    const std::vector<OpFrame>& fr, M2LUnits* U, hipStream_t st) {
+  using Sig = std::array<int32_t, kM2LGroupOps>;  // frame operators, -1 past the last
+  struct Hash {
+    size_t operator()(const Sig& s) const {
+      uint64_t h = 0;
+      for (int32_t v : s) h = (h ^ (uint64_t)(uint32_t)v) * 0x9E3779B97F4A7C15ull, h ^= h >> 29;
+      return (size_t)h;
+    }
+  };
+  struct Col {
+    int32_t tgt, phi;
+    std::array<int32_t, kM2LGroupOps> src;
+  };
+  std::unordered_map<Sig, int, Hash> id;
+  std::vector<Sig> sigs;
+  std::vector<std::vector<Col>> cols;
+  auto add = [&](const Sig& s, const Col& c) {
+    const auto it = id.emplace(s, (int)sigs.size());
+    if (it.second) {
+      sigs.push_back(s);
+      cols.emplace_back();
+    }
+    cols[it.first->second].push_back(c);
+  };
+  struct Ent {
+    int64_t key;
+    int32_t frame, src, phi;
+  };
+  std::vector<Ent> ent;
+  for (int64_t b = b0; b < b1; ++b) {
+    ent.clear();
+    for (int32_t e = mptr[b]; e < mptr[b + 1]; ++e) {
+      const OpFrame& f = fr[mop[e] >= 0 ? mop[e] : ~mop[e]];
+      ent.push_back(Ent{f.key, f.frame, msrc[e], f.phi});
+    }
+    std::sort(ent.begin(), ent.end(), [](const Ent& x, const Ent& y) {
+      return x.key != y.key ? x.key < y.key : (x.frame != y.frame ? x.frame < y.frame : x.src < y.src);
+    });
+    for (size_t i0 = 0, i1 = 0; i0 < ent.size(); i0 = i1) {
+      while (i1 < ent.size() && ent[i1].key == ent[i0].key) ++i1;
+      const size_t n = i1 - i0, np = (n + kM2LGroupOps - 1) / kM2LGroupOps;
+      for (size_t k = 0, i = i0; k < np; ++k) {
+        const size_t e = i0 + n * (k + 1) / np;
+        Sig s;
+        Col c{(int32_t)b, ent[i0].phi, {}};
+        s.fill(-1);
+        c.src.fill(-1);
+        for (size_t q = 0; i < e; ++i, ++q) {
+          s[q] = ent[i].frame;
+          c.src[q] = ent[i].src;
+        }
+        add(s, c);
+      }
+    }
+  }
+  const int C = U->cols;
+  for (size_t g = 0, n0 = sigs.size(); g < n0; ++g) {
+    if (sigs[g][1] < 0 || cols[g].size() >= kM2LFewCols) continue;
+    const std::vector<Col> few = std::move(cols[g]);
+    cols[g].clear();
+    const Sig s = sigs[g];
+    for (const Col& c : few)
+      for (int q = 0; q < kM2LGroupOps && s[q] >= 0; ++q) {
+        Sig one;
+        Col oc{c.tgt, c.phi, {}};
+        one.fill(-1);
+        oc.src.fill(-1);
+        one[0] = s[q];
+        oc.src[0] = c.src[q];
+        add(one, oc);
+      }
+  }
+  // longest units first (the launch does not end on them), then by operator
+  auto steps = [&](size_t g) {
+    int n = 0;
+    while (n < kM2LGroupOps && sigs[g][n] >= 0) ++n;
+    return n;
+  };
+  std::vector<int32_t> order;
+  for (size_t g = 0; g < sigs.size(); ++g)
+    if (!cols[g].empty()) order.push_back((int32_t)g);
+  std::sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+    const int nx = steps(x), ny = steps(y);
+    return nx != ny ? nx > ny : sigs[x] < sigs[y];
+  });
+  std::vector<int32_t> step0(1, 0), kind, phi, op, src, frame_op;
+  std::vector<int32_t> fmap((size_t)P->ng_ops, -1);
+  std::vector<std::vector<std::pair<int32_t, int32_t>>> tslots((size_t)(b1 - b0));
+  for (int32_t g : order) {
+    const int ns = steps(g);
+    std::stable_sort(cols[g].begin(), cols[g].end(), [](const Col& x, const Col& y) { return x.tgt < y.tgt; });
+    for (size_t c0 = 0; c0 < cols[g].size(); c0 += C) {
+      const int64_t u = (int64_t)kind.size();
+      if ((u + 1) * C >= ((int64_t)1 << 31)) return FMMLM_ENOMEM;
+      const size_t nc = std::min<size_t>(C, cols[g].size() - c0);
+      U->ncols += (int64_t)nc;
+      kind.push_back(sigs[g][0] < P->ng_free ? (int32_t)FMMLM_FREE : (int32_t)FMMLM_REACTION);
+      for (size_t c = 0; c < (size_t)C; ++c) {
+        phi.push_back(c < nc ? cols[g][c0 + c].phi : 0);
+        if (c < nc)
+          tslots[cols[g][c0 + c].tgt - b0].push_back({(int32_t)(u * C + (int64_t)c), cols[g][c0 + c].phi});
+      }
+      for (int k = 0; k < ns; ++k) {
+        int32_t& f = fmap[sigs[g][k]];
+        if (f < 0) {
+          f = (int32_t)frame_op.size();
+          frame_op.push_back(sigs[g][k]);
+        }
+        op.push_back(f);
+        for (size_t c = 0; c < (size_t)C; ++c) src.push_back(c < nc ? cols[g][c0 + c].src[k] : -1);
+      }
+      step0.push_back((int32_t)op.size());
+    }
+  }
+  std::vector<int32_t> boxes, ptr(1, 0), slots, slot_phi;
+  for (int64_t b = b0; b < b1; ++b) {
+    const auto& t = tslots[b - b0];
+    if (t.empty()) continue;
+    boxes.push_back((int32_t)b);
+    for (const auto& v : t) {
+      slots.push_back(v.first);
+      slot_phi.push_back(v.second);
+    }
+    ptr.push_back((int32_t)slots.size());
+  }
+  U->n = (int64_t)kind.size();
+  U->nsteps = (int64_t)op.size();
+  U->nboxes = (int64_t)boxes.size();
+  U->nops = (int64_t)frame_op.size();
+  int rc;
+  if ((rc = dev_upload(P, &U->step0, step0, st)) || (rc = dev_upload(P, &U->kind, kind, st)) ||
+      (rc = dev_upload(P, &U->phi, phi, st)) || (rc = dev_upload(P, &U->op, op, st)) ||
+      (rc = dev_upload(P, &U->src, src, st)) || (rc = dev_upload(P, &U->boxes, boxes, st)) ||
+      (rc = dev_upload(P, &U->ptr, ptr, st)) || (rc = dev_upload(P, &U->slots, slots, st)) ||
+      (rc = dev_upload(P, &U->slot_phi, slot_phi, st)) || (rc = dev_upload(P, &U->frame_op, frame_op, st)))
+    return rc;
+  return FMMLM_OK;
+}
+
 int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<double>& Y,
                const std::vector<double>& Z, const std::vector<int32_t>& LAY, hipStream_t st) {
   const int L = P->L;
@@ -749,274 +947,42 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     P->n_free_ops = nfreeops;
     P->nops = nfreeops + (int64_t)B.reac_task.size();
   }
-  // ---- M2L steps: the top levels (few boxes, many distinct operators) go to
-  // the sparse FP64 kernel, the levels below them operator-major: chunks of up
-  // to tile_cols targets of a group of operators, each a tile of its own
-  std::vector<int32_t> tptr(1, 0), ttgt, tlev, sop, skind, ssrc, smask, us, umask, tuptr;
+  // ---- M2L units in operator frames (build_m2l_units)
+  std::vector<int> free_r2dz, dirs;
   {
-    {
-      const int nr0 = (P->p + 1) * (P->p + 1);
-      const int mr0 = (nr0 + 31) / 32;
-      P->mrt = (mr0 + 1) / 2 * 2;
-      if (P->mrt < 2) P->mrt = 2;
-      P->nrk = (nr0 + 15) / 16 * 16;
-      P->tile_cols = (P->fp32 && P->mrt <= 4) ? 128 : 64;
-    }
-    const int TBc = P->tile_cols;
-    const int nfo = (int)P->n_free_ops;
-    const int ksp = P->opts.fp64_top_levels;  // levels of the sparse kernel
-    {
-      std::vector<int32_t> spb;
-      for (int l = 0; l < std::min(ksp, P->maxlev + 1); ++l)
-        for (int64_t b = P->lev_off[l]; b < P->lev_off[l + 1]; ++b)
-          if (mptr[b + 1] > mptr[b]) {
-            spb.push_back((int32_t)b);
-            P->stats.m2l_top_pairs += mptr[b + 1] - mptr[b];
-          }
-      P->n_sp_boxes = (int64_t)spb.size();
-      if (int rc0 = dev_upload(P, &P->sp_boxes, spb, st)) return rc0;
-      // work items: runs of kSpItemRounds rounds of sp_ne entries (the block's
-      // threads hold sp_ne entries x the coefficients (n, m >= 0) in groups of
-      // four orders; LDS holds their source expansions and operator tables,
-      // then their sums, at most kSpLds)
-      const int nc = P->nc;
-      int tps = 0, rows = 0;  // threads of an entry; its source rows padded to four orders
-      for (int n = 0; n <= P->p; ++n) {
-        tps += (n + 4) / 4;
-        rows += (n + 4) / 4 * 4;
-      }
-      P->sp_tps = tps;
-      P->sp_bytes = std::max(P->ngs * 8 + rows * 16, nc * 16);
-      P->sp_ne = std::max(1, std::min(kSpThreads / tps, kSpLds / P->sp_bytes));
-      P->sp_threads = (P->sp_ne * tps + 63) / 64 * 64;
-      const int run = kSpItemRounds * P->sp_ne;
-      std::vector<int32_t> items, iptr(1, 0);
-      for (const int32_t b : spb) {
-        for (int32_t e = mptr[b]; e < mptr[b + 1]; e += run) {
-          items.push_back(b);
-          items.push_back(e);
-          items.push_back(std::min<int32_t>(e + run, mptr[b + 1]));
-        }
-        iptr.push_back((int32_t)(items.size() / 3));
-      }
-      P->n_sp_items = (int64_t)(items.size() / 3);
-      if (int rc0 = dev_upload(P, &P->sp_items, items, st)) return rc0;
-      if (int rc0 = dev_upload(P, &P->sp_item_ptr, iptr, st)) return rc0;
-      if (int rc0 = dev_alloc(P, &P->Psp, (size_t)std::max<int64_t>(P->n_sp_items, 1) * nc * 2)) return rc0;
-    }
-    for (int grp = 0; grp <= 4; ++grp) P->tile_grp[grp] = 0;  // no target tiles (M2L is operator-major)
-    // Levels below the sparse ones: operator-major chunks (FP32 products on the
-    // FP32 form's matrix-core kernel, FP64 ones on the FP64 tile GEMM).  The
-    // operators are taken kM2LGroupOps at a time in operator order (in box units
-    // a free-space operator serves every level); the targets that every
-    // operator of the group reaches are taken TBc at a time as one chunk whose
-    // steps are the group's operators, each with its own sources, so the chunk
-    // stores one partial sum per target for all of them.  The rest of each
-    // operator's pairs form one-step chunks.  A target appears at most once per
-    // operator, so a chunk's columns are distinct targets.  Each target's outputs
-    // are then summed over its slots (chunk, column) in chunk order by
-    // m2l_slot_reduce_kernel.
-    {
-      std::vector<std::array<int32_t, 3>> pr;  // (operator, target, source)
-      for (int l = ksp; l <= P->maxlev; ++l)
-        for (int64_t b = P->lev_off[l]; b < P->lev_off[l + 1]; ++b)
-          for (int32_t e = mptr[b]; e < mptr[b + 1]; ++e)
-            pr.push_back({(mop[e] >= 0) ? mop[e] : ~mop[e], (int32_t)b, msrc[e]});
-      std::sort(pr.begin(), pr.end());
-      std::vector<std::pair<size_t, size_t>> oprng;  // each operator's pairs [i0, i1) in pr
-      std::vector<uint64_t> opclass;                 // ... and its class (after the sort below)
-      for (size_t i0 = 0; i0 < pr.size();) {
-        size_t i1 = i0;
-        while (i1 < pr.size() && pr[i1][0] == pr[i0][0]) ++i1;
-        oprng.push_back({i0, i1});
-        i0 = i1;
-      }
-      // operators in classes that reach the same targets, so that a group's
-      // operators share most of them.  Free space: a box meets offset component
-      // +3 (or -3) along an axis only from one child position of its parent, so
-      // the operators of one such class reach the same targets (the boundary
-      // aside).  Reaction operators (after the free ones) by level, offset and
-      // component: the components of one offset often hold the same pairs.
-      {
-        std::vector<uint64_t> rkey((size_t)(P->nops - nfo), 0);
-        for (const auto& kv : B.reac_op_id) {
-          const int comp = std::get<0>(kv.first), lvl = std::get<1>(kv.first);
-          const int dx = std::get<2>(kv.first), dy = std::get<3>(kv.first), dz = std::get<4>(kv.first);
-          rkey[kv.second] = ((uint64_t)lvl << 40) | ((uint64_t)(dz & 0xff) << 32) | ((uint64_t)(dx & 0xff) << 24) |
-                            ((uint64_t)(dy & 0xff) << 16) | (uint64_t)(comp & 0xffff);
-        }
-        auto key = [&](int op) -> uint64_t {
-          if (op >= nfo) return (uint64_t(1) << 63) | rkey[op - nfo];
-          uint64_t c = 0;
-          for (int a = 0; a < 3; ++a) {
-            const int v = B.free_off[3 * op + a];
-            c = 3 * c + (v >= 3 ? 1 : (v <= -3 ? 2 : 0));
-          }
-          return c;
-        };
-        std::stable_sort(oprng.begin(), oprng.end(), [&](const std::pair<size_t, size_t>& x,
-                                                         const std::pair<size_t, size_t>& y) {
-          return key(pr[x.first][0]) < key(pr[y.first][0]);
-        });
-        // a group holds operators of one class (reaction: one offset)
-        for (const auto& r : oprng) {
-          const uint64_t k = key(pr[r.first][0]);
-          opclass.push_back((k >> 63) ? (k & ~(uint64_t)0xffff) : k);
-        }
-      }
-      std::vector<std::vector<int32_t>> tslots(P->NB);
-      std::vector<char> done(pr.size(), 0);
-      std::vector<int32_t> hits(P->NB, 0);
-      // one chunk: columns c < nc_ hold targets tg[c]; step k applies operator
-      // ops[k] to sources src[k][c]
-      auto add_chunk = [&](const std::vector<int32_t>& ops, const std::vector<int32_t>& tg,
-                           const std::vector<std::vector<int32_t>>& src) {
-        const int32_t unit = (int32_t)tlev.size();  // one unit per chunk
-        tlev.push_back(B.boxes[tg[0]].level);
-        uint32_t msk = 0;
-        for (size_t c = 0; c < (size_t)TBc; ++c) {
-          const bool on = c < tg.size();
-          ttgt.push_back(on ? tg[c] : -1);
-          if (on) {
-            msk |= 1u << (c >> 3);
-            tslots[tg[c]].push_back(unit * TBc + (int32_t)c);
-          }
-        }
-        for (size_t k = 0; k < ops.size(); ++k) {
-          for (size_t c = 0; c < (size_t)TBc; ++c) ssrc.push_back(c < tg.size() ? src[k][c] : -1);
-          sop.push_back(ops[k]);
-          skind.push_back(ops[k] < nfo ? (int32_t)FMMLM_FREE : (int32_t)FMMLM_REACTION);
-          smask.push_back((int32_t)msk);
-        }
-        tptr.push_back((int32_t)sop.size());
-      };
-      for (size_t g0 = 0, g1 = 0; g0 < oprng.size(); g0 = g1) {
-        g1 = g0 + 1;
-        while (g1 < oprng.size() && g1 - g0 < (size_t)kM2LGroupOps && opclass[g1] == opclass[g0]) ++g1;
-        // (a group whose operator reaches one target twice is not grouped)
-        bool distinct = true;
-        for (size_t o = g0; o < g1 && distinct; ++o)
-          for (size_t i = oprng[o].first + 1; i < oprng[o].second; ++i)
-            if (pr[i][1] == pr[i - 1][1]) distinct = false;
-        if (g1 - g0 > 1 && distinct) {
-          for (size_t o = g0; o < g1; ++o)
-            for (size_t i = oprng[o].first; i < oprng[o].second; ++i) ++hits[pr[i][1]];
-          // pairs of the group's targets common to all its operators, per
-          // operator in target order (each list is sorted by target)
-          std::vector<std::vector<size_t>> com(g1 - g0);
-          for (size_t o = g0; o < g1; ++o)
-            for (size_t i = oprng[o].first; i < oprng[o].second; ++i)
-              if (hits[pr[i][1]] == (int32_t)(g1 - g0)) com[o - g0].push_back(i);
-          for (size_t o = g0; o < g1; ++o)
-            for (size_t i = oprng[o].first; i < oprng[o].second; ++i) hits[pr[i][1]] = 0;
-          const size_t ncom = com[0].size();
-          if (ncom >= (size_t)kM2LGroupMinTargets) {
-            std::vector<int32_t> ops;
-            for (size_t o = g0; o < g1; ++o) ops.push_back(pr[oprng[o].first][0]);
-            for (size_t c0 = 0; c0 < ncom; c0 += TBc) {
-              const size_t n_ = std::min<size_t>(TBc, ncom - c0);
-              std::vector<int32_t> tg(n_);
-              std::vector<std::vector<int32_t>> src(g1 - g0, std::vector<int32_t>(n_));
-              for (size_t c = 0; c < n_; ++c) {
-                tg[c] = pr[com[0][c0 + c]][1];
-                for (size_t k = 0; k < g1 - g0; ++k) {
-                  const size_t i = com[k][c0 + c];
-                  if (pr[i][1] != tg[c]) {
-                    set_last_error("internal: M2L operator group targets out of step");
-                    return FMMLM_EUNSUPPORTED;
-                  }
-                  src[k][c] = pr[i][2];
-                  done[i] = 1;
-                }
-              }
-              add_chunk(ops, tg, src);
-            }
-          }
-        }
-        // the group's other pairs, operator by operator
-        for (size_t o = g0; o < g1; ++o) {
-          std::vector<size_t> rest;
-          for (size_t i = oprng[o].first; i < oprng[o].second; ++i)
-            if (!done[i]) rest.push_back(i);
-          for (size_t c0 = 0; c0 < rest.size(); c0 += TBc) {
-            const size_t n_ = std::min<size_t>(TBc, rest.size() - c0);
-            std::vector<int32_t> tg(n_);
-            std::vector<std::vector<int32_t>> src(1, std::vector<int32_t>(n_));
-            for (size_t c = 0; c < n_; ++c) {
-              tg[c] = pr[rest[c0 + c]][1];
-              src[0][c] = pr[rest[c0 + c]][2];
-            }
-            add_chunk({pr[oprng[o].first][0]}, tg, src);
-          }
-        }
-      }
-      P->tile_grp[3] = P->tile_grp[4] = (int64_t)tlev.size();
-      std::vector<int32_t> sbox, sptr(1, 0), slots;
-      for (int64_t b = 0; b < P->NB; ++b)
-        if (!tslots[b].empty()) {
-          sbox.push_back((int32_t)b);
-          slots.insert(slots.end(), tslots[b].begin(), tslots[b].end());
-          sptr.push_back((int32_t)slots.size());
-        }
-      P->n_slot_boxes = (int64_t)sbox.size();
-      int rc0;
-      if ((rc0 = dev_upload(P, &P->slot_boxes, sbox, st)) || (rc0 = dev_upload(P, &P->slot_ptr, sptr, st)) ||
-          (rc0 = dev_upload(P, &P->slots, slots, st)))
-        return rc0;
-    }
-    P->ntiles = (int64_t)tlev.size();
-    P->nsteps = (int64_t)sop.size();
-    P->stats.m2l_steps = P->nsteps;
-    P->stats.m2l_chunks = P->ntiles;
-    P->stats.m2l_tile_cols = TBc;
-    // work units: one per chunk (a chunk has at most kM2LGroupOps steps);
-    // unit_split is 0 (no target tiles)
-    constexpr int kStepsPerUnit = 16;
-    tuptr.assign(1, 0);
-    for (int64_t t = 0; t < P->ntiles; ++t) {
-      if (t == P->tile_grp[2]) P->unit_split = (int64_t)(us.size() / 2);
-      for (int32_t a = tptr[t]; a < tptr[t + 1]; a += kStepsPerUnit) {
-        const int32_t b = std::min(a + kStepsPerUnit, tptr[t + 1]);
-        us.push_back(a);
-        us.push_back(b);
-        int32_t um = 0;  // column groups any step of the unit touches
-        for (int32_t q = a; q < b; ++q) um |= smask[q];
-        umask.push_back(um);
-      }
-      tuptr.push_back((int32_t)(us.size() / 2));
-    }
-    if (P->ntiles == P->tile_grp[2]) P->unit_split = (int64_t)(us.size() / 2);
-    P->nunits = (int64_t)(us.size() / 2);
-    // the chunk units in 8 contiguous ranges of about equal steps, one per XCD
-    // (contiguous, so that the chunks of one operator share an XCD's L2)
-    {
-      const int64_t u0 = P->unit_split, n = P->nunits - u0;
-      const int64_t tot = n > 0 ? (int64_t)us[2 * (P->nunits - 1) + 1] - us[2 * u0] : 0;
-      int64_t u = 0, acc = 0;
-      P->m2l_xcd.off[0] = 0;
-      P->m2l_xcd_len = 0;
-      for (int x = 1; x <= 8; ++x) {
-        const int64_t goal = tot * x / 8;
-        while (u < n && acc + (us[2 * (u0 + u) + 1] - us[2 * (u0 + u)]) <= goal) {
-          acc += us[2 * (u0 + u) + 1] - us[2 * (u0 + u)];
-          ++u;
-        }
-        if (x == 8) u = n;
-        P->m2l_xcd.off[x] = (int32_t)u;
-        P->m2l_xcd_len = std::max<int32_t>(P->m2l_xcd_len, P->m2l_xcd.off[x] - P->m2l_xcd.off[x - 1]);
-      }
-    }
-    // each chunk is one unit (the slots index units by chunk)
-    if (P->nunits != P->ntiles || P->unit_split != 0) {
-      set_last_error("internal: M2L chunks and units differ");
-      return FMMLM_EUNSUPPORTED;
-    }
+    const int nr0 = (P->p + 1) * (P->p + 1);
+    P->mrt = ((nr0 + 31) / 32 + 1) / 2 * 2;
+    P->nrk = (nr0 + 15) / 16 * 16;
     // operator tables must fit a budget (FP64 + FP32 copies)
     const double tbytes = (double)P->nops * P->nrk * 32.0 * P->mrt * (P->fp32 ? 12.0 : 8.0);
     if (tbytes > 32.0 * (1 << 30)) {
       set_last_error("M2L operator tables exceed 32 GiB");
       return FMMLM_ENOMEM;
     }
+    const int ksp = P->opts.fp64_top_levels;  // FP32 form: the levels above stay FP64
+    const int64_t top_end = P->lev_off[std::min(ksp, P->maxlev + 1)];
+    for (int64_t b = 0; b < top_end; ++b) P->stats.m2l_top_pairs += mptr[b + 1] - mptr[b];
+    std::vector<OpFrame> fr;
+    op_frames(B, (int)P->n_free_ops, P->nops, &fr, &free_r2dz, &dirs);
+    P->ng_free = (int64_t)(free_r2dz.size() / 2);
+    P->ng_ops = P->ng_free + (int64_t)B.tasks.size();
+    P->n_phi = (int64_t)(dirs.size() / 2);
+    if (P->opts.max_rhs > 1) {
+      std::vector<int32_t> of, op;
+      for (const OpFrame& f : fr) {
+        of.push_back(f.frame);
+        op.push_back(f.phi);
+      }
+      int rc0;
+      if ((rc0 = dev_upload(P, &P->op_frame, of, st)) || (rc0 = dev_upload(P, &P->op_phi, op, st))) return rc0;
+    }
+    int rc0 = build_m2l_units(P, 0, P->fp32 ? top_end : P->NB, mptr, msrc, mop, fr, &P->u64, st);
+    if (rc0 == FMMLM_OK && P->fp32) rc0 = build_m2l_units(P, top_end, P->NB, mptr, msrc, mop, fr, &P->u32, st);
+    if (rc0) return rc0;
+    const M2LUnits& U = P->fp32 ? P->u32 : P->u64;
+    P->stats.m2l_steps = U.nsteps;
+    P->stats.m2l_chunks = U.n;
+    P->stats.m2l_tile_cols = U.cols;
   }
   // ---- M2M / L2L as GEMMs over tiles of up to xl_tile_cols target boxes of one
   // level: M2M tiles hold parents (one step per child octant present, source
@@ -1357,20 +1323,17 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     }
   }
   UP(coefA, coefA); UP(coefR, coefR); UP(sc_levels, scl);
-  UP(tile_ptr, tptr); UP(tile_tgt, ttgt); UP(tile_level, tlev); UP(step_op, sop); UP(step_src, ssrc);
-  UP(unit_s, us); UP(tile_unit_ptr, tuptr); UP(step_kind, skind); UP(step_mask, smask); UP(unit_mask, umask);
-  if (P->fp32) {
-    if ((rc = dev_alloc(P, &P->W32m, (size_t)std::max<int64_t>(P->nunits, 1) * P->tile_cols * 32 * P->mrt)))
-      return rc;
-  } else if ((rc = dev_alloc(P, &P->Wm2l, (size_t)std::max<int64_t>(P->nunits, 1) * P->tile_cols * 32 * P->mrt))) {
-    return rc;
-  }
+  std::vector<int32_t> dec;  // pairs (n, m): orders m >= 1 first, then m = 0
+  for (int n = 1; n <= p; ++n)
+    for (int m = 1; m <= n; ++m) dec.push_back((n * n + 2 * m - 1) | (m << 16));
+  for (int n = 0; n <= p; ++n) dec.push_back(n * n);
+  UP(pair_dec, dec);
 #undef UP
   P->stats.lists_seconds = seconds_since(tphase);
   tphase = std::chrono::steady_clock::now();
   // ---- operators: free-space harmonics and reaction Sommerfeld tables
-  if ((rc = dev_alloc(P, &P->G, (size_t)std::max<int64_t>(P->nops, 1) * P->ngs))) return rc;
-  if ((rc = dev_alloc(P, &P->E, (size_t)std::max<int64_t>(P->nops, 1) * (2 * p + 1) * 2))) return rc;
+  if ((rc = dev_alloc(P, &P->G, (size_t)std::max<int64_t>(P->ng_ops, 1) * P->ngs))) return rc;
+  if ((rc = dev_alloc(P, &P->E, (size_t)std::max<int64_t>(P->n_phi, 1) * (2 * p + 1) * 2))) return rc;
   double* tables = nullptr;
   if (!B.tasks.empty()) {
     FMM_HIP_TRY(hipMalloc(&tables, B.tasks.size() * (size_t)P->ng * sizeof(double)));
@@ -1401,19 +1364,30 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
       return rc;
     }
   }
-  rc = gpu_build_ops(P, B.free_off, B.reac_task, B.reac_phi, B.reac_S, tables, st);
+  rc = gpu_build_ops(P, free_r2dz, B.tasks, dirs, tables, st);
   hipFree(tables);
   if (rc) return rc;
-  if ((rc = dev_alloc(P, &P->Tfree, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt))) return rc;
-  if ((rc = gpu_build_real_ops(P, st))) return rc;
+  for (M2LUnits* U : {&P->u64, &P->u32}) {
+    const bool f32 = U == &P->u32;
+    if (U->n == 0) continue;
+    const size_t size = f32 ? sizeof(float) : sizeof(double);
+    char *A = nullptr, *W = nullptr;
+    if ((rc = dev_alloc(P, &A, (size_t)(U->nops * frame_op_len(p, nullptr)) * size))) return rc;
+    if ((rc = dev_alloc(P, &W, (size_t)(U->n * U->cols * P->nrk) * size))) return rc;
+    U->A = A;
+    U->W = W;
+    if ((rc = gpu_build_frame_ops(P, *U, f32, st))) return rc;
+  }
+  if (P->opts.max_rhs > 1) {  // the batched form's dense operators
+    if ((rc = dev_alloc(P, &P->Tfree, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt))) return rc;
+    if ((rc = gpu_build_real_ops(P, st))) return rc;
+  }
   if ((rc = dev_alloc(P, &P->Txl, (size_t)16 * P->nrk * 32 * P->mrt))) return rc;
   if ((rc = gpu_build_xlate_ops(P, st))) return rc;
   if (P->fp32) {
-    const size_t nr = (size_t)(P->p + 1) * (P->p + 1);
-    if ((rc = dev_alloc(P, &P->Tfree32, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt))) return rc;
-    // single-vector FP32 sources: rows padded to nrk (aligned, zero past nr)
-    if (std::min(P->opts.max_rhs, 64) == 1 && (rc = dev_alloc(P, &P->M32, (size_t)P->NB * P->nrk))) return rc;
-    (void)nr;
+    if (P->opts.max_rhs > 1 &&
+        (rc = dev_alloc(P, &P->Tfree32, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt)))
+      return rc;
     if ((rc = dev_alloc(P, &P->qt32, P->NP))) return rc;
     if ((rc = dev_alloc(P, &P->pxh, P->NP)) || (rc = dev_alloc(P, &P->pxl, P->NP)) ||
         (rc = dev_alloc(P, &P->pyh, P->NP)) || (rc = dev_alloc(P, &P->pyl, P->NP)) ||

@@ -136,7 +136,7 @@ __device__ inline int isqrt_row(int t) {
 // An operator's table in the frame turned so that its offset has azimuth 0: the
 // real g(j, k) = G(j, k) e^{-i k phi} of eqs. metole, metoleimage1 for
 // -j <= k <= j (g(j, -k) = (-1)^k g(j, k)) at [kGPad + j j + j + k], j <= 2p, with
-// zeros before and after; its phases e^{i k phi}, k <= 2p, in a table of their own.
+// zeros before and after.
 __device__ inline bool g_index(int i, int p2, int* j, int* k) {
   i -= kGPad;
   if (i < 0 || i >= (p2 + 1) * (p2 + 1)) return false;
@@ -148,51 +148,52 @@ __device__ inline bool g_index(int i, int p2, int* j, int* k) {
   return true;
 }
 
-__global__ void build_free_ops_kernel(const int* __restrict__ off, int nops, int p2, int ngs,
-                                      const double* __restrict__ coefA, double* __restrict__ G,
-                                      cplx* __restrict__ E) {
+// free operators: r2dz [nops][2]
+__global__ void build_free_ops_kernel(const int* __restrict__ r2dz, int64_t nops, int p2, int ngs,
+                                      const double* __restrict__ coefA, double* __restrict__ G) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)nops * ngs) return;
-  const int op = (int)(t / ngs), c = (int)(t % ngs);
-  const double dx = off[3 * op], dy = off[3 * op + 1], dz = off[3 * op + 2];
-  if (c <= p2) {
-    double s, co;
-    sincos(c * atan2(dy, dx), &s, &co);
-    E[(int64_t)op * (p2 + 1) + c] = cmk(co, s);
-  }
+  if (t >= nops * ngs) return;
+  const int64_t op = t / ngs;
+  const int c = (int)(t % ngs);
   int j, k;
   double g = 0.0;
   if (g_index(c, p2, &j, &k)) {
     const int ak = abs(k);
-    g = (kInv4Pi / coefA[cidx(j, ak)]) * irregular_nm(j, ak, sqrt(dx * dx + dy * dy), 0.0, dz).re;
+    g = (kInv4Pi / coefA[cidx(j, ak)]) * irregular_nm(j, ak, sqrt((double)r2dz[2 * op]), 0.0, r2dz[2 * op + 1]).re;
     if (k < 0) g *= sgn1(k);
   }
-  G[(int64_t)op * ngs + c] = g;
+  G[t] = g;
 }
 
-__global__ void build_reaction_ops_kernel(const int* __restrict__ task, const double* __restrict__ phi,
-                                          const double* __restrict__ Sl, int nops, int op0, int p2,
-                                          int ng, int ngs, const double* __restrict__ coefA,
-                                          const double* __restrict__ tables, double* __restrict__ G,
-                                          cplx* __restrict__ E) {
+// reaction operators: one per Sommerfeld task
+__global__ void build_reaction_ops_kernel(const double* __restrict__ Sl, int64_t nops, int p2, int ng, int ngs,
+                                          const double* __restrict__ coefA, const double* __restrict__ tables,
+                                          double* __restrict__ G) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)nops * ngs) return;
-  const int op = (int)(t / ngs), c = (int)(t % ngs);
-  if (c <= p2) {
-    double s, co;
-    sincos(c * phi[op], &s, &co);
-    E[(int64_t)(op0 + op) * (p2 + 1) + c] = cmk(co, s);
-  }
+  if (t >= nops * ngs) return;
+  const int64_t op = t / ngs;
+  const int c = (int)(t % ngs);
   int j, k;
   double g = 0.0;
   if (g_index(c, p2, &j, &k)) {
     const int ak = abs(k);
-    const double SI = tables[(int64_t)task[op] * ng + cidx(j, ak)];
+    const double SI = tables[op * ng + cidx(j, ak)];
     const double cj = sqrt((2.0 * j + 1.0) / (4.0 * kPi));
     g = Sl[op] * cj * SI * kInv4Pi / coefA[cidx(j, ak)];
     if (k < 0) g *= sgn1(k);
   }
-  G[(int64_t)(op0 + op) * ngs + c] = g;
+  G[t] = g;
+}
+
+// e^{i k phi}, k <= p2, of the directions (dx, dy)
+__global__ void build_phases_kernel(const int* __restrict__ dirs, int64_t n, int p2, cplx* __restrict__ E) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n * (p2 + 1)) return;
+  const int64_t f = t / (p2 + 1);
+  const int k = (int)(t % (p2 + 1));
+  double s, c;
+  sincos(k * atan2((double)dirs[2 * f + 1], (double)dirs[2 * f]), &s, &c);
+  E[t] = cmk(c, s);
 }
 
 // ---------------------------------------------------------------- eval kernels
@@ -631,178 +632,14 @@ __global__ void build_xlate_ops_kernel(int p, int nrk, int mr, const double* __r
 }
 
 
-// M2L on the sparse top levels (few boxes, many distinct operators).  A work
-// item is a run of at most kSpItemRounds * ne entries of one target box; its
-// block takes ne entries a round.  In the frame turned to an operator's azimuth
-// its table g is real, so the real parts of the local expansion come from the
-// real parts of the source and the imaginary ones from the imaginary ones
-// (reaction entries act on the mirrored polarization-source expansion):
-//   Re L_nm = sum g(n+n', m'-m) a + (-1)^m sum g(n+n', m'+m) a,   m' >= 0,
-//   Im L_nm = sum g(n+n', m'-m) b - (-1)^m sum g(n+n', m'+m) b,
-// a + i b = e^{i m' phi} M_{n'm'} (a halved at m' = 0), turned back by
-// e^{-i m phi}: 4 multiply-adds an (output, m' >= 0) pair, where the complex sum
-// over all m' takes 4 for each sign of m'.  Thread (slot, n, mb) applies entry
-// slot of the round to the outputs (n, 4 mb .. 4 mb + 3): along m' the four need g
-// in two windows of seven orders (differences, sums) that slide four steps at a
-// time, eight LDS reads for 64 multiply-adds; g holds the negative orders
-// too and source rows are padded with zeros to steps of four, so the loop has no
-// selects and no tail (outputs m > n are dropped).  The slots' sums meet in LDS
-// in a fixed order and go to the item's partial; a second kernel adds a box's
-// partials, in item order, to its local expansion.  FP64 throughout.
-// Bound by FP64 issue and LDS bank conflicts; 24,840 pairs at p = 10 alone: 0.166 -> 0.106 ms.
-__device__ inline int sp_row(int n) { return 4 * (n / 4 + 1) * (2 * (n / 4) + (n & 3)); }
-
-__global__ void __launch_bounds__(kSpThreads)
-m2l_sparse_kernel(int p, int nc, int ngs, int ne, int tps, const int32_t* __restrict__ items,
-                  const int32_t* __restrict__ ptr, const int32_t* __restrict__ nfree,
-                  const int32_t* __restrict__ src, const int32_t* __restrict__ opv, const double* __restrict__ G,
-                  const cplx* __restrict__ E, const double* __restrict__ coefA, const double* __restrict__ M,
-                  unsigned parts, cplx* __restrict__ part) {
-  far_chain_priority();
-  extern __shared__ char smem[];
-  const int nr = (p + 1) * (p + 1), nm = sp_row(p + 1), p2 = 2 * p;
-  cplx* Ms = reinterpret_cast<cplx*>(smem);             // [ne][nm] turned source rows, A and sign folded
-  double* Gs = reinterpret_cast<double*>(Ms + ne * nm);  // [ne][ngs]
-  cplx* red = Ms;                                       // [ne][nc] after the last round (aliases the above)
-  const int tid = threadIdx.x;
-  const int b = items[3 * blockIdx.x];
-  const int ef = ptr[b] + nfree[b];
-  const int e0 = max(items[3 * blockIdx.x + 1], (parts & FMMLM_FREE) ? ptr[b] : ef);
-  const int e1 = min(items[3 * blockIdx.x + 2], (parts & FMMLM_REACTION) ? ptr[b + 1] : ef);
-  const int slot = tid / tps;
-  const bool active = slot < ne;
-  int n = 0, mb = tid - slot * tps;
-  if (active)
-    while (mb >= (n + 4) / 4) {
-      mb -= (n + 4) / 4;
-      ++n;
-    }
-  const int m0 = 4 * mb;
-  double lr[4] = {0.0, 0.0, 0.0, 0.0}, li[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int r0 = e0; r0 < e1; r0 += ne) {
-    const int cnt = min(ne, e1 - r0);
-    __syncthreads();  // the previous round's readers are done
-    for (int i = tid; i < cnt * (ngs / 2); i += blockDim.x) {
-      const int sl = i / (ngs / 2), k = i - sl * (ngs / 2);
-      const int op = opv[r0 + sl];
-      reinterpret_cast<double2*>(Gs)[i] =
-          reinterpret_cast<const double2*>(G)[(int64_t)(op < 0 ? ~op : op) * (ngs / 2) + k];
-    }
-    for (int i = tid; i < cnt * nc; i += blockDim.x) {
-      const int sl = i / nc, k = i - sl * nc;
-      const int e = r0 + sl, op = opv[e];
-      const int n2 = isqrt_row(k), m2 = k - cidx(n2, 0);
-      const cplx v = rload(M + (int64_t)src[e] * nr, n2, m2);
-      const cplx u = E[(int64_t)(op < 0 ? ~op : op) * (p2 + 1) + m2];
-      double f = coefA[k] * (m2 ? 1.0 : 0.5);
-      if (op < 0 && ((n2 + m2) & 1)) f = -f;  // mirrored (reaction) entry
-      cplx* row = Ms + sl * nm + sp_row(n2);
-      row[m2] = f * (u * v);
-      if (m2 == n2)
-        for (int q = n2 + 1; q & 3; ++q) row[q] = cmk(0.0, 0.0);
-    }
-    __syncthreads();
-    if (active && slot < cnt) {
-      double dr[4] = {0.0, 0.0, 0.0, 0.0}, di[4] = {0.0, 0.0, 0.0, 0.0};
-      double sr[4] = {0.0, 0.0, 0.0, 0.0}, si[4] = {0.0, 0.0, 0.0, 0.0};
-      const double* Ge = Gs + slot * ngs + kGPad;
-      const cplx* Me = Ms + slot * nm;
-      for (int n2 = 0; n2 <= p; ++n2) {
-        const int N = n + n2;
-        const double* gd = Ge + N * N + N - m0 - 3;  // order m' - m0 - 3 + i at [m' + i]
-        const double* gs = Ge + N * N + N + m0;      // order m' + m0 + i at [m' + i]
-        const cplx* Mrow = Me + sp_row(n2);
-        double wd[7], ws[7];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          wd[i] = gd[i];
-          ws[i] = gs[i];
-        }
-        for (int m2 = 0; m2 <= n2; m2 += 4) {
-#pragma unroll
-          for (int i = 3; i < 7; ++i) {
-            wd[i] = gd[m2 + i];
-            ws[i] = gs[m2 + i];
-          }
-          cplx mv[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) mv[q] = Mrow[m2 + q];
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              dr[j] = fma(wd[q - j + 3], mv[q].re, dr[j]);
-              di[j] = fma(wd[q - j + 3], mv[q].im, di[j]);
-              sr[j] = fma(ws[q + j], mv[q].re, sr[j]);
-              si[j] = fma(ws[q + j], mv[q].im, si[j]);
-            }
-#pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            wd[i] = wd[i + 4];
-            ws[i] = ws[i + 4];
-          }
-        }
-      }
-      const int op = opv[r0 + slot];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (m0 + j > n) break;
-        // (-1)^m with m = 4 mb + j
-        const cplx v = cmk((j & 1) ? dr[j] - sr[j] : dr[j] + sr[j], (j & 1) ? di[j] + si[j] : di[j] - si[j]);
-        const cplx w = cconj(E[(int64_t)(op < 0 ? ~op : op) * (p2 + 1) + m0 + j]) * v;
-        lr[j] += w.re;
-        li[j] += w.im;
-      }
-    }
-  }
-  __syncthreads();  // the last round's readers of Ms and Gs are done (red aliases them)
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (m0 + j <= n) red[slot * nc + cidx(n, m0 + j)] = cmk(lr[j], li[j]);
-  }
-  __syncthreads();
-  for (int c = tid; c < nc; c += blockDim.x) {
-    double sr = 0.0, si = 0.0;
-    for (int sl = 0; sl < ne; ++sl) {
-      sr += red[sl * nc + c].re;
-      si += red[sl * nc + c].im;
-    }
-    part[(int64_t)blockIdx.x * nc + c] = cmk(sr, si);
-  }
-}
-
-// A sparse top-level box's partials, in item order, times the coefficient's
-// constants (eq. metole), added to its local expansion.
-__global__ void __launch_bounds__(128)
-m2l_sparse_reduce_kernel(int p, int nc, const int32_t* __restrict__ boxes, const int32_t* __restrict__ iptr,
-                         const cplx* __restrict__ part, const int32_t* __restrict__ blevel,
-                         const double* __restrict__ sc, const double* __restrict__ coefA, double* __restrict__ Lx) {
-  far_chain_priority();
-  const int nr = (p + 1) * (p + 1);
-  const int b = boxes[blockIdx.x];
-  const int i0 = iptr[blockIdx.x], i1 = iptr[blockIdx.x + 1];
-  const double s_l = sc[blevel[b]];
-  for (int t = threadIdx.x; t < nc; t += blockDim.x) {
-    double sr = 0.0, si = 0.0;
-    for (int i = i0; i < i1; ++i) {
-      sr += part[(int64_t)i * nc + t].re;
-      si += part[(int64_t)i * nc + t].im;
-    }
-    const int n = isqrt_row(t), m = t - cidx(n, 0);
-    const double f = sgn1(n + m) * coefA[cidx(n, m)] * (4.0 * kPi / (2.0 * n + 1.0)) * s_l;
-    const cplx old = rload(Lx + (int64_t)b * nr, n, m);
-    rstore(Lx + (int64_t)b * nr, n, m, cmk(old.re + f * sr, old.im + f * si));
-  }
-}
-
 // Real-form M2L operator: T[k][row] maps the real layout of a source expansion
 // (index k) to the real layout of the local expansion (row), including every
 // constant of eq. metole / eq. metoleimage1 and, for reaction operators, the
 // mirror sign (-1)^{n'+m'} of the polarization-source expansion; rows padded to
 // mr and columns to nrk with zeros.
 __global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfree, const double* __restrict__ G,
-                                      const cplx* __restrict__ E, int ngs, const double* __restrict__ coefA,
+                                      const cplx* __restrict__ E, const int32_t* __restrict__ op_frame,
+                                      const int32_t* __restrict__ op_phi, int ngs, const double* __restrict__ coefA,
                                       double* __restrict__ T) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t per = (int64_t)nrk * mr;
@@ -819,8 +656,8 @@ __global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfre
     // unit input in the real layout -> complex M_{n2,m2} and M_{n2,-m2}
     const cplx mp = im2 ? cmk(0.0, 1.0) : cmk(1.0, 0.0);
     const int j = n + n2;
-    const double* Gj = G + (int64_t)op * ngs + kGPad + j * j + j;
-    const cplx* Eop = E + (int64_t)op * (2 * p + 1);
+    const double* Gj = G + (int64_t)op_frame[op] * ngs + kGPad + j * j + j;
+    const cplx* Eop = E + (int64_t)op_phi[op] * (2 * p + 1);
     auto gat = [&](int kk) -> cplx { return Gj[kk] * (kk >= 0 ? Eop[kk] : cconj(Eop[-kk])); };
     cplx acc = gat(m2 - m) * mp;
     if (m2 > 0) {
@@ -836,142 +673,267 @@ __global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfre
   T[t] = v;
 }
 
-// M2L as GEMMs (FP64 form).  A step is one real-form operator T_op (nr x nr,
-// free space or a reaction component) applied to up to 64 gathered source
-// expansions (a missing source is a zero column); the plan's units are
-// operator-major chunks of a few steps for the same target columns.  A
-// unit writes its product to W, and the slot reduction adds each target's
-// partials in order.
-// FP64 on the matrix cores (v_mfma_f64_16x16x4f64, lane layout as in
-// m2l_batch64_kernel): four waves, WR groups of RBW 16-row blocks x 4 / WR
-// groups of WR 16-column blocks.  A wave takes its operator rows straight from
-// global memory into the fragments, batches of kGmKB k-steps one batch ahead; only
-// the gathered sources, which all row groups read, go through LDS (slices of 64
-// coefficients, loads a slice ahead).  A column's source is the same for a whole
-// wave, so its index is a scalar load: a staging loop with per-lane indices
-// waited for them, and by vmcnt's order for every operator load issued before
-// them, in each slice (matrix cores 38 % busy on the million-charge workload).
-// One operand buffer, so that three blocks fit a CU (two buffers, two blocks:
-// 1.42 against 1.30 ms), and the row blocks that (p+1)^2 needs, not a power of two.
-// Alone at p = 10, N = 2^20: 1.95 -> 1.30 ms (matrix cores 62 % busy); p = 8,
-// 16,411 charges: 0.61 -> 0.29 ms.  Measured and not kept: 8 k-steps a batch
-// (2 % to 50 % slower), 2 (the same), an XCD-contiguous unit order (10 % to 35 %
-// slower: units differ in steps).  A 16-column block whose two
-// 8-column groups hold no source in a step is skipped (exact).
+// M2L in operator frames, on the matrix cores, in FP64 or FP32.  In the frame
+// turned to an operator's azimuth its table g is real, so with
+//   a + i b = e^{i m' phi} M_{n'm'}   and   L_nm = e^{-i m phi} (c + i s)
+// the real parts c come from the a by one matrix and the imaginary parts s from
+// the b by another (m' >= 1):
+//   c:  f [g(n+n', m'-m) + (-1)^m g(n+n', m'+m)]   (m' = 0: the first term only),
+//   s:  f [g(n+n', m'-m) - (-1)^m g(n+n', m'+m)],
+// half the multiply-adds of the real form of G, and one operator serves every
+// azimuth: 24,840 pairs of the top levels have 2,812 operators, 330 frames.
+// Pairs (n, m) are taken orders m >= 1 first (pair_dec), so the s matrix is over
+// the first ns of the nc pairs.  build_frame_ops_kernel folds in every constant of
+// eqs. metole, metoleimage1 and the mirror sign, as build_real_ops_kernel does.
+// Layout: column (pair of the source) by column, its RC 16-row blocks of c, then
+// its RS of s; whole k-steps of four columns, zeros past nc.
+__host__ __device__ constexpr int frame_ksteps(int n) { return (n + 3) / 4; }
+
+template <class T>
+__global__ void build_frame_ops_kernel(int p, int nc, int ns, int rc, int rt, int ksteps, int64_t nops, int64_t nfree,
+                                       const int32_t* __restrict__ frame_op, const int32_t* __restrict__ dec,
+                                       const double* __restrict__ G, int ngs, const double* __restrict__ coefA,
+                                       T* __restrict__ A) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int per = 4 * ksteps * rt;
+  if (t >= nops * per) return;
+  const int64_t fo = frame_op[t / per];
+  const int col = (int)(t % per) / rt, row = (int)(t % per) % rt;
+  const bool c = row < 16 * rc;
+  const int r = c ? row : row - 16 * rc;
+  double v = 0.0;
+  if (c ? (r < nc && col < nc) : (r < ns && col < ns)) {
+    const int m = dec[r] >> 16, m2 = dec[col] >> 16;
+    const int n = (int)sqrt((double)(dec[r] & 0xffff) + 0.5), n2 = (int)sqrt((double)(dec[col] & 0xffff) + 0.5);
+    const double* Gj = G + fo * ngs + kGPad + (n + n2) * (n + n2) + n + n2;
+    v = Gj[m2 - m];
+    if (m2 > 0) v += (c ? sgn1(m) : -sgn1(m)) * Gj[m2 + m];
+    double f = sgn1(n + m) * coefA[cidx(n, m)] * (4.0 * kPi / (2.0 * n + 1.0)) * coefA[cidx(n2, m2)];
+    if (fo >= nfree && ((n2 + m2) & 1)) f = -f;
+    v *= f;
+  }
+  A[t] = (T)v;
+}
+
 typedef double doublex4 __attribute__((ext_vector_type(4)));
-constexpr int kGmTB = 64;     // target columns of a unit
-constexpr int kGmKS = 64;     // coefficients of an operand slice
-constexpr int kGmKB = 4;      // k-steps (of 4) of an operator batch
-constexpr int kGmLd = kGmTB + 1;
-template <int RBW, int WR>
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+__device__ inline doublex4 mfma4(double a, double b, doublex4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+__device__ inline floatx4 mfma4(float a, float b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+template <class T>
+struct FrameTypes;
+template <>
+struct FrameTypes<double> {
+  using Acc = doublex4;
+  static __device__ int row(int lk, int v) { return lk + 4 * v; }  // result row of register v
+};
+template <>
+struct FrameTypes<float> {
+  using Acc = floatx4;
+  static __device__ int row(int lk, int v) { return 4 * lk + v; }
+};
+
+// A block takes one unit (64 columns, up to kM2LGroupOps steps), each of its four
+// waves 16 columns.  A k-step's operand fragment wants pair 4 k + l / 16 of column
+// l % 16 on lane l, which that lane gathers (two values of its column's source,
+// always FP64) and turns itself, so the operands need no LDS; the operator, which
+// all waves read, goes through LDS in double-buffered batches of KB k-steps, one
+// barrier each, loads of both a batch ahead.  Waves whose columns are empty only
+// load.
+// A kernel of dense real-form operators took, launch alone, at 2^20 charges,
+// p = 10: FP64 1.30 ms, this one 0.83; 262,144 clustered charges, p = 12: 4.9
+// and 2.6 ms; the top levels' own kernel (24,840 pairs) 0.106 and 0.055 ms.  Now
+// bound by the matrix cores (half their time at p = 10) and the gathers' cache
+// accesses.  Measured on the way: one unit of 16 columns a wave without LDS,
+// operators through the vector cache: 1.67 ms (p = 10); phases read from memory
+// instead of LDS: half again as many cache accesses; results stored straight
+// from the fragments: 32-byte pieces.
+typedef int intx4 __attribute__((ext_vector_type(4)));
+constexpr int kFrCols = 64;
+template <class T, int RC, int RS, int KB>
 __global__ void __launch_bounds__(256, 2)
-m2l_gemm_kernel(int nr, int nrk, int mr, int64_t unit0, const int32_t* __restrict__ unit_s,
-                const int32_t* __restrict__ step_op, const int32_t* __restrict__ step_kind,
-                const int32_t* __restrict__ step_src, const int32_t* __restrict__ step_mask,
-                const int32_t* __restrict__ unit_mask, unsigned parts, const double* __restrict__ T,
-                const double* __restrict__ M, double* __restrict__ W) {
+m2l_frame_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restrict__ step0,
+                 const int32_t* __restrict__ kind, const int32_t* __restrict__ uphi,
+                 const int32_t* __restrict__ step_op, const int32_t* __restrict__ step_src,
+                 const int32_t* __restrict__ dec, unsigned parts, const T* __restrict__ A,
+                 const double* __restrict__ M, const cplx* __restrict__ E, T* __restrict__ W) {
   far_chain_priority();
-  constexpr int CBW = WR;            // 16-column blocks of a wave
-  constexpr int COLS = kGmTB / 4;    // columns a wave stages
-  __shared__ double Bs[kGmKS * kGmLd];
-  const int64_t unit = unit0 + blockIdx.x;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int rb0 = (wave % WR) * RBW, col0 = (wave / WR) * CBW * 16;
-  const int li = lane & 15, lk = lane >> 4;
-  doublex4 acc[RBW][CBW];
+  constexpr int RT = 16 * (RC + RS);
+  constexpr int KV = 4 * RT * (int)sizeof(T) / 16;     // 16-byte vectors of a k-step of the operator
+  constexpr int PER = (KB * KV + 255) / 256;
+  using Acc = typename FrameTypes<T>::Acc;
+  extern __shared__ cplx Es[];  // [p + 1][64] phases of the columns
+  __shared__ intx4 As[2][KB * KV];
+  __shared__ int32_t ds[(kPMax + 1) * (kPMax + 2) / 2];
+  const int64_t u = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), col = 16 * wave + li;
+  const int s0 = step0[u], s1 = (parts & (unsigned)kind[u]) ? step0[u + 1] : s0;  // (off: zeros are stored)
+  const int kc = frame_ksteps(nc), ks = frame_ksteps(ns);
+  for (int i = tid; i < nc; i += 256) ds[i] = dec[i];
+  for (int i = tid; i < (nc - ns) * kFrCols; i += 256)
+    Es[i] = E[(int64_t)uphi[u * kFrCols + i % kFrCols] * ne + i / kFrCols];
+  // (a unit's columns in use come first)
+  const bool work = step_src[(int64_t)step0[u] * kFrCols + 16 * wave] >= 0;
+  Acc ac[RC], as[RS];
 #pragma unroll
-  for (int i = 0; i < RBW; ++i)
+  for (int i = 0; i < RC; ++i) ac[i] = Acc{0, 0, 0, 0};
 #pragma unroll
-    for (int j = 0; j < CBW; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-  const int s0 = unit_s[2 * unit], s1 = unit_s[2 * unit + 1];
-  const int64_t oplen = (int64_t)nrk * mr;
-  // the wave's columns of slice [k0, k0 + 64) of step s (lane = coefficient)
-  double rb[COLS];
-  auto load_b = [&](int s, int k0) {
-    const bool on = (parts & (unsigned)step_kind[s]) != 0;
-    const int32_t* src = step_src + (int64_t)s * kGmTB + wave * COLS;
-    const int k = k0 + lane;
+  for (int i = 0; i < RS; ++i) as[i] = Acc{0, 0, 0, 0};
+  intx4 va[PER];
+  auto load_a = [&](int s, int k0) {
+    const intx4* Ap = reinterpret_cast<const intx4*>(A) + ((int64_t)step_op[s] * kc + k0) * KV;
+    const int n = min(KB, kc - k0) * KV;
 #pragma unroll
-    for (int c = 0; c < COLS; ++c) {
-      const int sb = on ? src[c] : -1;
-      rb[c] = 0.0;
-      if (sb >= 0 && k < nr) rb[c] = M[(int64_t)sb * nr + k];
+    for (int r = 0; r < PER; ++r)
+      if (tid + 256 * r < n) va[r] = Ap[tid + 256 * r];
+  };
+  auto stash_a = [&](int buf) {
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+      if (tid + 256 * r < KB * KV) As[buf][tid + 256 * r] = va[r];
+  };
+  struct __attribute__((packed, aligned(8))) Pair {
+    double re, im;
+  };
+  Pair x[KB];
+  int m[KB];
+  auto load_b = [&](const double* Mj, int k0) {
+#pragma unroll
+    for (int t = 0; t < KB; ++t) {
+      const int d = ds[min(4 * (k0 + t) + lk, nc - 1)];  // (columns from nc on are zero in A)
+      x[t] = *reinterpret_cast<const Pair*>(Mj + (d & 0xffff));  // (order 0: im not used, the s columns are zero there)
+      m[t] = d >> 16;
     }
   };
-  auto stash_b = [&]() {
-#pragma unroll
-    for (int c = 0; c < COLS; ++c) Bs[lane * kGmLd + wave * COLS + c] = rb[c];
-  };
-  // operator batch at Tp (columns k .. k + 15 of a step's operator, this lane's row and column)
-  const int64_t tlane = (int64_t)lk * mr + rb0 * 16 + li;
-  double an[kGmKB][RBW];
-  auto load_a = [&](const double* Tp) {
-#pragma unroll
-    for (int t = 0; t < kGmKB; ++t)
-#pragma unroll
-      for (int i = 0; i < RBW; ++i) an[t][i] = Tp[(int64_t)(4 * t) * mr + 16 * i];
-  };
+  auto source = [&](int s) { return step_src[(int64_t)s * kFrCols + col]; };
+  __syncthreads();  // ds
+  int src = -1, snext = -1;
   if (s0 < s1) {
-    load_a(T + step_op[s0] * oplen + tlane);
-    load_b(s0, 0);
-    stash_b();
+    load_a(s0, 0);
+    src = source(s0);
+    if (work) load_b(M + (int64_t)max(src, 0) * nr, 0);
+    stash_a(0);
   }
   __syncthreads();
+  int buf = 0;
   for (int s = s0; s < s1; ++s) {
-    const double* Ts = T + step_op[s] * oplen + tlane;
-    const double* Tnext = T + step_op[min(s + 1, s1 - 1)] * oplen + tlane;  // (the last one is not used)
-    const unsigned wmsk =
-        ((parts & (unsigned)step_kind[s]) ? (unsigned)step_mask[s] : 0u) >> (col0 >> 3);
-    for (int k0 = 0; k0 < nrk; k0 += kGmKS) {
-      const int kn = min(nrk, k0 + kGmKS);
-      const bool last = kn == nrk;
+    if (s + 1 < s1) snext = source(s + 1);
+    for (int k0 = 0; k0 < kc; k0 += KB) {
+      const bool last = k0 + KB >= kc;
       const bool more = !last || s + 1 < s1;
-      if (more) load_b(last ? s + 1 : s, last ? 0 : kn);
-      const double* Bb = Bs + col0 + li;
-      for (int k = k0; k < kn; k += 4 * kGmKB) {
-        double a[kGmKB][RBW];
+      if (more) load_a(last ? s + 1 : s, last ? 0 : k0 + KB);
+      if (work) {
+        T a[KB], b[KB];
 #pragma unroll
-        for (int t = 0; t < kGmKB; ++t)
+        for (int t = 0; t < KB; ++t) {
+          const cplx v = Es[m[t] * kFrCols + col] * cmk(x[t].re, x[t].im);
+          a[t] = src >= 0 ? (T)v.re : (T)0;
+          b[t] = src >= 0 ? (T)v.im : (T)0;
+        }
+        if (more) load_b(M + (int64_t)max(last ? snext : src, 0) * nr, last ? 0 : k0 + KB);
+        const T* Ab = reinterpret_cast<const T*>(As[buf]) + lk * RT + li;
 #pragma unroll
-          for (int i = 0; i < RBW; ++i) a[t][i] = an[t][i];
-        const int kb = k + 4 * kGmKB;
-        load_a(kb < nrk ? Ts + (int64_t)kb * mr : Tnext);
+        for (int t = 0; t < KB; ++t) {
+          if (k0 + t >= kc) break;
 #pragma unroll
-        for (int t = 0; t < kGmKB; ++t) {
-          // operator columns (and operand rows) from nr on are zero padding
-          if (k + 4 * t >= nr) break;
+          for (int i = 0; i < RC; ++i) ac[i] = mfma4(Ab[4 * t * RT + 16 * i], a[t], ac[i]);
+          if (k0 + t < ks) {
 #pragma unroll
-          for (int j = 0; j < CBW; ++j) {
-            if (!((wmsk >> (2 * j)) & 3u)) continue;
-            const double bv = Bb[(k - k0 + 4 * t + lk) * kGmLd + 16 * j];
-#pragma unroll
-            for (int i = 0; i < RBW; ++i)
-              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t][i], bv, acc[i][j], 0, 0, 0);
+            for (int i = 0; i < RS; ++i) as[i] = mfma4(Ab[4 * t * RT + 16 * (RC + i)], b[t], as[i]);
           }
         }
       }
       if (more) {
+        stash_a(buf ^ 1);  // last read before the previous barrier
         __syncthreads();
-        stash_b();
-        __syncthreads();
+        buf ^= 1;
+      }
+    }
+    src = snext;
+  }
+  // out through LDS, PB row blocks at a time, so that each column's rows leave
+  // contiguous (8-byte stores of four rows a column wrote 4.4 times the bytes)
+  constexpr int PB0 = 2 * KB * KV * 16 / (1024 * (int)sizeof(T)), PB = PB0 < RC + RS ? PB0 : RC + RS;
+  static_assert(PB >= 1, "a row block of every wave must fit the operator's buffers");
+  T* o = reinterpret_cast<T*>(As) + wave * (256 * PB);  // [column][16 PB] of this wave
+#pragma unroll
+  for (int i0 = 0; i0 < RC + RS; i0 += PB) {
+    __syncthreads();  // (the previous batch's, then the previous piece's readers are done)
+#pragma unroll
+    for (int i = i0; i < i0 + PB && i < RC + RS; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        o[li * 16 * PB + 16 * (i - i0) + FrameTypes<T>::row(lk, v)] = i < RC ? ac[i < RC ? i : 0][v] : as[i < RC ? 0 : i - RC][v];
+    __syncthreads();
+    if (!work) continue;
+    T* w = W + (u * kFrCols + 16 * wave) * wr;
+    for (int i = lane; i < 256 * PB; i += 64) {
+      const int c = i / (16 * PB), r = 16 * i0 + i % (16 * PB);
+      if (r < nc) {
+        w[(int64_t)c * wr + r] = o[i];
+      } else if (r >= 16 * RC && r < 16 * RC + ns) {
+        w[(int64_t)c * wr + nc + r - 16 * RC] = o[i];
       }
     }
   }
-  // 16-column blocks holding a group the unit touches are stored (the reduction
-  // reads the touched groups only)
-  const unsigned uwm = (unsigned)unit_mask[unit] >> (col0 >> 3);
-  double* Wu = W + unit * (int64_t)kGmTB * mr;
+}
+
+// Each target box turns its slots' products back (e^{-i m phi}) and sums them in
+// FP64 in a fixed order, scaled by 1/S of its level, into its local expansion.
+// One block per target box: kFrRedThreads / nc groups of nc threads (one a pair)
+// take every so many-th slot, four in flight, and the groups' sums are added in
+// LDS in group order.  Bound by the products' bytes.
+constexpr int kFrRedThreads = 256;
+template <class T>
+__global__ void __launch_bounds__(kFrRedThreads)
+m2l_frame_reduce_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restrict__ boxes,
+                        const int32_t* __restrict__ sptr, const int32_t* __restrict__ slots,
+                        const int32_t* __restrict__ sphi, const int32_t* __restrict__ dec,
+                        const int32_t* __restrict__ blevel, const double* __restrict__ sc,
+                        const T* __restrict__ W, const cplx* __restrict__ E, double* __restrict__ Lx) {
+  far_chain_priority();
+  __shared__ cplx sum[kFrRedThreads];
+  const int b = boxes[blockIdx.x];
+  const int k0 = sptr[blockIdx.x], k1 = sptr[blockIdx.x + 1];
+  const int groups = kFrRedThreads / nc;
+  const int g = threadIdx.x / nc, j = threadIdx.x - g * nc;
+  const int d = dec[j], m = d >> 16;
+  if (g < groups) {
+    const int js = j < ns ? nc + j : j;  // (order 0 has no imaginary part)
+    double re = 0.0, im = 0.0;
+    constexpr int U = 4;
+    for (int k = k0 + g; k < k1; k += U * groups) {
+      T c[U], s[U];
+      cplx e[U];
 #pragma unroll
-  for (int j = 0; j < CBW; ++j) {
-    if (!((uwm >> (2 * j)) & 3u)) continue;
+      for (int q = 0; q < U; ++q) {
+        const int kk = min(k + q * groups, k1 - 1);
+        const T* w = W + (int64_t)slots[kk] * wr;
+        c[q] = w[j];
+        s[q] = w[js];
+        e[q] = E[(int64_t)sphi[kk] * ne + m];
+      }
 #pragma unroll
-    for (int i = 0; i < RBW; ++i) {
-      if (16 * (rb0 + i) >= nr) break;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Wu[(int64_t)(col0 + 16 * j + li) * mr + 16 * (rb0 + i) + lk + 4 * v] = acc[i][j][v];
+      for (int q = 0; q < U; ++q) {
+        if (k + q * groups >= k1) break;
+        re += (double)c[q] * e[q].re + (double)s[q] * e[q].im;
+        im += (double)s[q] * e[q].re - (double)c[q] * e[q].im;
+      }
     }
+    sum[threadIdx.x] = cmk(re, im);
   }
+  __syncthreads();
+  if (g > 0) return;
+  cplx v = sum[j];
+  for (int q = 1; q < groups; ++q) v = v + sum[q * nc + j];
+  const double inv = sc[blevel[b]];
+  double* l = Lx + (int64_t)b * nr + (d & 0xffff);
+  l[0] += v.re * inv;
+  if (m) l[1] += v.im * inv;
 }
 
 // M2M / L2L of a level (eqs. metome, letole as the real-form octant operators
@@ -1075,165 +1037,6 @@ xlate_direct_kernel(int nr, int nrk, int mr, int64_t tile0, int64_t unit0, const
       const int row = 16 * rb + lk + 4 * v;
       if (row < nr) Dt[row] += acc[v];
     }
-  }
-}
-
-// FP32 form of the M2L GEMM on the matrix cores (v_mfma_f32_16x16x4f32).
-// The 64 NW threads are NW wavefronts arranged WR x WC over the tile; each owns
-// RBW x CBW output blocks of 16 x 16.  Operand fragments (lane l):
-// A[row = l % 16][k = l / 16], B[k = l / 16][col = l % 16]; result:
-// D[row = 4 (l / 16) + v][col = l % 16].  A unit is an operator-major chunk:
-// one to a few steps (operators) for the same up to TB target columns, each
-// with its own sources; its product is one FP32 sum on the matrix cores over
-// the steps, stored as it is; the targets' slots are summed in FP64 later.
-// The operator columns go through LDS in slices of KC, double-buffered: slice
-// q + 1 is stored while slice q is multiplied, one barrier a slice, and the
-// global loads of slice q + 2 are in flight meanwhile.  Two blocks fit a CU.
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-template <int RBW, int CBW, int WR, int NW, int KC>
-__global__ void __launch_bounds__(64 * NW, NW / 2)  // two blocks per CU
-m2l_mfma32_kernel(int nr, int nrk, int64_t unit0, int64_t nunit, const int32_t* __restrict__ unit_s,
-                  const int32_t* __restrict__ step_op, const int32_t* __restrict__ step_kind,
-                  const int32_t* __restrict__ step_src, const int32_t* __restrict__ step_mask,
-                  const int32_t* __restrict__ unit_mask, unsigned parts, const float* __restrict__ T,
-                  const float* __restrict__ M, float* __restrict__ W, XcdSplit xs) {
-  far_chain_priority();
-  constexpr int NT = 64 * NW;         // threads
-  constexpr int WC = NW / WR;
-  constexpr int MR = 16 * RBW * WR;   // padded rows of the operator
-  constexpr int TB = 16 * CBW * WC;   // target columns of the tile
-  constexpr int TS = MR + 16;         // LDS row strides, padded against bank conflicts
-  constexpr int BSR = TB + 17;        // (the operand slice is stored transposed)
-  constexpr int NTR = KC * MR / NT;
-  constexpr int NBR = KC * TB / NT;
-  static_assert(NTR * NT == KC * MR && NBR * NT == KC * TB, "slice must split evenly over the threads");
-  // two LDS buffers: slice q + 1 is stored while slice q is multiplied
-  __shared__ __align__(16) float Ts[2][KC * TS];
-  __shared__ float Bs[2][KC * BSR];
-  // XCD-aware order: block b runs on XCD b % 8 (workgroups go to the 8 XCDs in
-  // turn); each XCD takes a contiguous range of units of about equal work, so
-  // consecutive units (chunks of the same operators) share that XCD's L2
-  const int x = blockIdx.x % 8;
-  const int64_t u = xs.off[x] + blockIdx.x / 8;
-  if (u >= xs.off[x + 1] || u >= nunit) return;
-  const int64_t unit = unit0 + u;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int row0 = (wave % WR) * RBW * 16, col0 = (wave / WR) * CBW * 16;
-  const int li = lane & 15, lk = lane >> 4;
-  // a unit is a run of steps (operators applied to up to TB sources each) for
-  // the same target columns: the product is one matrix-core sum over the
-  // steps' K ranges in turn, stored as it is
-  floatx4 part[RBW][CBW];
-#pragma unroll
-  for (int i = 0; i < RBW; ++i)
-#pragma unroll
-    for (int j = 0; j < CBW; ++j) part[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int s0 = unit_s[2 * unit], s1 = unit_s[2 * unit + 1];
-  const int nch = nrk / KC;
-  const int total = (s1 - s0) * nch;
-  // 16-byte loads: the operator slice is contiguous; source rows are padded to
-  // nrk floats (aligned, zero past nr).  UT / UB 16-byte units a slice, NTR4 /
-  // NBR4 a thread (the last round may leave threads idle)
-  constexpr int UT = KC * MR / 4, UB = KC * TB / 4;
-  constexpr int NTR4 = (UT + NT - 1) / NT, NBR4 = (UB + NT - 1) / NT;
-  static_assert(KC % 4 == 0 && MR % 4 == 0 && TS % 4 == 0, "16-byte staging");
-  float4 rt[NTR4], rb[NBR4];
-  // slices are loaded in order: ld_s, ld_k = the next one's step and first column
-  int ld_s = s0, ld_k = 0;
-  auto load = [&]() {
-    const int s = ld_s, k0 = ld_k;
-    if ((ld_k += KC) >= nrk) {
-      ld_k = 0;
-      ++ld_s;
-    }
-    const bool on = (parts & (unsigned)step_kind[s]) != 0;
-    const int32_t* src = step_src + (int64_t)s * TB;
-    const float4* Tc = reinterpret_cast<const float4*>(T + ((int64_t)step_op[s] * nrk + k0) * MR);
-#pragma unroll
-    for (int r = 0; r < NTR4; ++r) {
-      const int u = tid + NT * r;
-      if (u < UT) rt[r] = Tc[u];
-    }
-#pragma unroll
-    for (int r = 0; r < NBR4; ++r) {
-      const int u = tid + NT * r, col = u / (KC / 4), k = k0 + 4 * (u % (KC / 4));
-      const int sb = (on && u < UB) ? src[col] : -1;
-      rb[r] = sb >= 0 ? *reinterpret_cast<const float4*>(M + (int64_t)sb * nrk + k) : float4{0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int r = 0; r < NTR4; ++r) {
-      const int u = tid + NT * r, i = 4 * u;
-      if (u < UT) *reinterpret_cast<float4*>(&Ts[buf][(i / MR) * TS + (i % MR)]) = rt[r];
-    }
-#pragma unroll
-    for (int r = 0; r < NBR4; ++r) {
-      const int u = tid + NT * r, col = u / (KC / 4), k = 4 * (u % (KC / 4));
-      if (u < UB) {
-        Bs[buf][(k + 0) * BSR + col] = rb[r].x;
-        Bs[buf][(k + 1) * BSR + col] = rb[r].y;
-        Bs[buf][(k + 2) * BSR + col] = rb[r].z;
-        Bs[buf][(k + 3) * BSR + col] = rb[r].w;
-      }
-    }
-  };
-  if (total > 0) {
-    load();
-    stash(0);
-    if (total > 1) load();
-  }
-  __syncthreads();
-  // 16-column blocks of this wave that hold a source in step s
-  auto step_wmsk = [&](int s) {
-    return ((parts & (unsigned)step_kind[s]) ? (unsigned)step_mask[s] : 0u) >> (col0 >> 3);
-  };
-  int cs = s0, kq = 0;  // the multiplied slice's step and first column
-  unsigned wmsk = total > 0 ? step_wmsk(s0) : 0u;
-  for (int q = 0; q < total; ++q) {
-    const int buf = q & 1;
-    const float* Tb = Ts[buf];
-    const float* Bb = Bs[buf];
-#pragma unroll
-    for (int ks = 0; ks < KC; ks += 4) {
-      // operator columns (and operand rows) from nr on are zero padding
-      if (kq + ks >= nr) break;
-      float a[RBW];
-#pragma unroll
-      for (int i = 0; i < RBW; ++i) a[i] = Tb[(ks + lk) * TS + row0 + 16 * i + li];
-#pragma unroll
-      for (int j = 0; j < CBW; ++j) {
-        if (!((wmsk >> (2 * j)) & 3u)) continue;
-        const float b = Bb[(ks + lk) * BSR + col0 + 16 * j + li];
-#pragma unroll
-        for (int i = 0; i < RBW; ++i)
-          part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b, part[i][j], 0, 0, 0);
-      }
-    }
-    if ((kq += KC) >= nrk) {
-      kq = 0;
-      if (++cs < s1) wmsk = step_wmsk(cs);
-    }
-    if (q + 1 < total) {
-      // the other buffer was last read before the previous barrier
-      stash(buf ^ 1);
-      if (q + 2 < total) load();
-    }
-    __syncthreads();
-  }
-  // 16-column blocks holding a group the unit touches are stored (the reduction
-  // reads the touched groups only)
-  const unsigned uwm = (unsigned)unit_mask[unit] >> (col0 >> 3);
-  float* Wu = W + unit * (int64_t)TB * MR;
-#pragma unroll
-  for (int j = 0; j < CBW; ++j) {
-    if (!((uwm >> (2 * j)) & 3u)) continue;
-#pragma unroll
-    for (int i = 0; i < RBW; ++i)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        Wu[(int64_t)(col0 + 16 * j + li) * MR + row0 + 16 * i + 4 * lk + v] = part[i][j][v];
   }
 }
 
@@ -1742,67 +1545,6 @@ p2p_reaction_batch_kernel(int g, const int32_t* __restrict__ leaves, const int32
     if (lane < g) phit[lane * np + t0 + ti] += tot;
   }
 }
-
-// Operator-major M2L (both forms): each target box sums its slots' partial
-// products (unit, column) in slot order (deterministic), scaled by 1/S of its
-// level, into its local expansion.  One block per target box, threads over rows.
-template <class TW>
-__global__ void __launch_bounds__(128)
-m2l_slot_reduce_kernel(int nr, int mr, int tb, const int32_t* __restrict__ boxes, const int32_t* __restrict__ sptr,
-                       const int32_t* __restrict__ slots, const int32_t* __restrict__ blevel,
-                       const double* __restrict__ sc, const TW* __restrict__ W, double* __restrict__ Lx) {
-  far_chain_priority();
-  const int b = boxes[blockIdx.x];
-  const int k0 = sptr[blockIdx.x], k1 = sptr[blockIdx.x + 1];
-  const double inv = sc[blevel[b]];
-  for (int row = threadIdx.x; row < nr; row += blockDim.x) {
-    // eight partial sums in a fixed assignment (slot k to sum k mod 8), added
-    // in order; the eight loads of a round are in flight together
-    double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int k = k0;
-    for (; k + 8 <= k1; k += 8) {
-      TW w[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) w[j] = W[(int64_t)slots[k + j] * mr + row];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] += (double)w[j];
-    }
-    for (; k < k1; ++k) v[0] += (double)W[(int64_t)slots[k] * mr + row];
-    Lx[(int64_t)b * nr + row] += (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) * inv;
-  }
-}
-
-// Sum of the units' partials of each tile, in unit order (deterministic),
-// scaled by 1/S of the tile's level (sc null: unscaled), added to the tile's
-// target expansions (local or, for M2M, multipole).  One block
-// per (tile, group of 8 columns); units that do not touch the group are
-// skipped (their partial holds no values there).
-__global__ void __launch_bounds__(256)
-m2l_reduce_kernel(int nr, int mr, int tb, int64_t tile0, const int32_t* __restrict__ tile_unit_ptr,
-                  const int32_t* __restrict__ unit_mask, const int32_t* __restrict__ tile_tgt,
-                  const int32_t* __restrict__ tile_level, const double* __restrict__ sc,
-                  const double* __restrict__ W, double* __restrict__ Lx) {
-  far_chain_priority();
-  const int ngrp = tb >> 3;
-  const int64_t tile = tile0 + blockIdx.x / ngrp;
-  const int g = blockIdx.x % ngrp;
-  const int u0 = tile_unit_ptr[tile], u1 = tile_unit_ptr[tile + 1];
-  bool any = false;
-  for (int u = u0; u < u1 && !any; ++u) any = (unit_mask[u] >> g) & 1;
-  if (!any) return;
-  const double inv = sc ? sc[tile_level[tile]] : 1.0;
-  const int per = tb * mr;
-  for (int e = threadIdx.x; e < 8 * mr; e += blockDim.x) {
-    const int col = 8 * g + e / mr, row = e % mr;
-    const int tg = tile_tgt[tile * tb + col];
-    if (tg < 0 || row >= nr) continue;
-    double v = 0.0;
-    for (int u = u0; u < u1; ++u)
-      if ((unit_mask[u] >> g) & 1) v += W[(int64_t)u * per + (int64_t)col * mr + row];
-    Lx[(int64_t)tg * nr + row] += v * inv;
-  }
-}
-
 
 __global__ void zero_kernel(double* __restrict__ a, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2525,41 +2267,84 @@ p2p_reaction_sum_kernel(const int32_t* __restrict__ leaves, const int32_t* __res
 
 }  // namespace
 
-int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_off, const std::vector<int>& reac_task,
-                  const std::vector<double>& reac_phi, const std::vector<double>& reac_S,
-                  const double* d_tables, hipStream_t st) {
-  const int nfree = (int)(free_off.size() / 3);
-  const int nreac = (int)reac_task.size();
+int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_r2dz, const std::vector<SommTask>& tasks,
+                  const std::vector<int>& dirs, const double* d_tables, hipStream_t st) {
+  const int64_t nfree = P->ng_free, nreac = P->ng_ops - nfree;
   const int p2 = 2 * P->p;
-  if (nfree > 0) {
-    int* doff = nullptr;
-    FMM_HIP_TRY(hipMalloc(&doff, free_off.size() * sizeof(int)));
-    FMM_HIP_TRY(hipMemcpyAsync(doff, free_off.data(), free_off.size() * sizeof(int), hipMemcpyHostToDevice, st));
-    const int64_t tot = (int64_t)nfree * P->ngs;
-    build_free_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(doff, nfree, p2, P->ngs, P->coefA, P->G,
-                                                                         reinterpret_cast<cplx*>(P->E));
-    FMM_HIP_TRY(hipGetLastError());
-    FMM_HIP_TRY(hipStreamSynchronize(st));
-    hipFree(doff);
+  const size_t ni = free_r2dz.size() + dirs.size();
+  int* di = nullptr;
+  double* dS = nullptr;
+  if (ni > 0) {
+    std::vector<int> hi(free_r2dz);
+    hi.insert(hi.end(), dirs.begin(), dirs.end());
+    FMM_HIP_TRY(hipMalloc(&di, ni * sizeof(int)));
+    hipError_t e = hipMemcpyAsync(di, hi.data(), ni * sizeof(int), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && nfree > 0) {
+      const int64_t tot = nfree * P->ngs;
+      build_free_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(di, nfree, p2, P->ngs, P->coefA, P->G);
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess && P->n_phi > 0) {
+      const int64_t tot = P->n_phi * (p2 + 1);
+      build_phases_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(di + free_r2dz.size(), P->n_phi, p2,
+                                                                        reinterpret_cast<cplx*>(P->E));
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    (void)hipFree(di);
+    FMM_HIP_TRY(e);
   }
   if (nreac > 0) {
-    int* dtask = nullptr;
-    double *dphi = nullptr, *dS = nullptr;
-    FMM_HIP_TRY(hipMalloc(&dtask, nreac * sizeof(int)));
-    FMM_HIP_TRY(hipMalloc(&dphi, nreac * sizeof(double)));
+    std::vector<double> S;
+    for (const SommTask& t : tasks) S.push_back(t.S);
     FMM_HIP_TRY(hipMalloc(&dS, nreac * sizeof(double)));
-    FMM_HIP_TRY(hipMemcpyAsync(dtask, reac_task.data(), nreac * sizeof(int), hipMemcpyHostToDevice, st));
-    FMM_HIP_TRY(hipMemcpyAsync(dphi, reac_phi.data(), nreac * sizeof(double), hipMemcpyHostToDevice, st));
-    FMM_HIP_TRY(hipMemcpyAsync(dS, reac_S.data(), nreac * sizeof(double), hipMemcpyHostToDevice, st));
-    const int64_t tot = (int64_t)nreac * P->ngs;
-    build_reaction_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
-        dtask, dphi, dS, nreac, nfree, p2, P->ng, P->ngs, P->coefA, d_tables, P->G, reinterpret_cast<cplx*>(P->E));
-    FMM_HIP_TRY(hipGetLastError());
-    FMM_HIP_TRY(hipStreamSynchronize(st));
-    hipFree(dtask);
-    hipFree(dphi);
-    hipFree(dS);
+    hipError_t e = hipMemcpyAsync(dS, S.data(), nreac * sizeof(double), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) {
+      const int64_t tot = nreac * P->ngs;
+      build_reaction_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
+          dS, nreac, p2, P->ng, P->ngs, P->coefA, d_tables, P->G + nfree * P->ngs);
+      e = hipGetLastError();
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    (void)hipFree(dS);
+    FMM_HIP_TRY(e);
   }
+  return FMMLM_OK;
+}
+
+namespace {
+// 16-row blocks of the two frame matrices
+struct FrameRows {
+  int nc, ns, rc, rs;
+};
+FrameRows frame_rows(int p) {
+  const int nc = ncoef(p), ns = nc - p - 1;
+  return FrameRows{nc, ns, (nc + 15) / 16, (ns + 15) / 16};
+}
+}  // namespace
+
+int64_t frame_op_len(int p, int64_t* row_len) {
+  const FrameRows r = frame_rows(p);
+  const int64_t rt = 16 * (r.rc + r.rs);
+  if (row_len) *row_len = rt;
+  return 4 * frame_ksteps(r.nc) * rt;
+}
+
+int gpu_build_frame_ops(fmmlm_plan_s* P, M2LUnits& U, bool f32, hipStream_t st) {
+  const FrameRows r = frame_rows(P->p);
+  int64_t rt = 0;
+  const int64_t tot = U.nops * frame_op_len(P->p, &rt);
+  if (tot == 0) return FMMLM_OK;
+  const unsigned nb = (unsigned)((tot + 255) / 256);
+  if (f32)
+    build_frame_ops_kernel<<<nb, 256, 0, st>>>(P->p, r.nc, r.ns, r.rc, (int)rt, frame_ksteps(r.nc), U.nops,
+                                               P->ng_free, U.frame_op, P->pair_dec, P->G, P->ngs, P->coefA,
+                                               static_cast<float*>(U.A));
+  else
+    build_frame_ops_kernel<<<nb, 256, 0, st>>>(P->p, r.nc, r.ns, r.rc, (int)rt, frame_ksteps(r.nc), U.nops,
+                                               P->ng_free, U.frame_op, P->pair_dec, P->G, P->ngs, P->coefA,
+                                               static_cast<double*>(U.A));
+  FMM_HIP_TRY(hipGetLastError());
   return FMMLM_OK;
 }
 
@@ -2568,7 +2353,7 @@ int gpu_build_real_ops(fmmlm_plan_s* P, hipStream_t st) {
   const int64_t tot = P->nops * (int64_t)P->nrk * (32 * P->mrt);
   build_real_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
       P->p, P->nrk, 32 * P->mrt, (int)P->nops, (int)P->n_free_ops, P->G, reinterpret_cast<const cplx*>(P->E),
-      P->ngs, P->coefA, P->Tfree);
+      P->op_frame, P->op_phi, P->ngs, P->coefA, P->Tfree);
   FMM_HIP_TRY(hipGetLastError());
   FMM_HIP_TRY(hipStreamSynchronize(st));
   return FMMLM_OK;
@@ -2643,7 +2428,7 @@ int gpu_expand_pairs(fmmlm_plan_s* P, const std::vector<int32_t>& tgt0, const st
 
 int gpu_build_fp32(fmmlm_plan_s* P, hipStream_t st) {
   const int64_t nt = P->nops * (int64_t)P->nrk * (32 * P->mrt);
-  if (nt > 0) to_f32_kernel<<<(unsigned)((nt + 255) / 256), 256, 0, st>>>(P->Tfree, nt, P->Tfree32);
+  if (nt > 0 && P->Tfree32) to_f32_kernel<<<(unsigned)((nt + 255) / 256), 256, 0, st>>>(P->Tfree, nt, P->Tfree32);
   const unsigned nb = (unsigned)((P->NP + 255) / 256);
   split_f32_kernel<<<nb, 256, 0, st>>>(P->px, P->NP, P->pxh, P->pxl);
   split_f32_kernel<<<nb, 256, 0, st>>>(P->py, P->NP, P->pyh, P->pyl);
@@ -2653,69 +2438,79 @@ int gpu_build_fp32(fmmlm_plan_s* P, hipStream_t st) {
   return FMMLM_OK;
 }
 
-// The FP32 matrix-core M2L over units [unit0, unit0 + n) in one of the tile
-// shapes (variant): for (p+1)^2 <= 128, 0: 4 waves of 64 x 64, 1: 8 waves of
-// 32 x 64, 2: 8 waves of 64 x 32, 3: 16 waves of 32 x 32, 4: 16 waves of
-// 64 x 16, 5: 16 waves of 16 x 64 outputs (rows x columns); one shape for the
-// other sizes.
-int m2l_variants(const fmmlm_plan_s* P) { return P->mrt == 4 ? kM2LVariants : 1; }
+// The M2L units of one precision.  Variant v: operator batches of 4, 2 or 8
+// k-steps (v % 3), from v = 3 on with LDS reserved so that two blocks fit a CU
+// (room for the near field's blocks); every variant gives the same sums.
+template <class T, int KB>
+int launch_frame_kb(const fmmlm_plan_s* P, const M2LUnits& U, size_t reserve, unsigned parts, const double* M,
+                    hipStream_t st) {
+  const FrameRows r = frame_rows(P->p);
+#define FR(RC, RS)                                                                                             \
+  if (r.rc == RC && r.rs == RS) {                                                                              \
+    const size_t used = (size_t)(2 * KB * 4 * 16 * (RC + RS)) * sizeof(T) + 1024;                              \
+    const size_t es = (size_t)(P->p + 1) * kFrCols * sizeof(cplx);                                             \
+    m2l_frame_kernel<T, RC, RS, KB><<<(unsigned)U.n, 256, std::max(es, reserve > used ? reserve - used : 0), st>>>( \
+        (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.step0, U.kind, U.phi, U.op, U.src,        \
+        P->pair_dec, parts, static_cast<const T*>(U.A), M, reinterpret_cast<const cplx*>(P->E),                \
+        static_cast<T*>(U.W));                                                                                 \
+    FMM_HIP_TRY(hipGetLastError());                                                                            \
+    return FMMLM_OK;                                                                                           \
+  }
+  if constexpr (KB == 2 || sizeof(T) == 4) {
+    FR(5, 4)
+  }
+  if constexpr (KB == 4) {  // p = 1..16
+    FR(1, 1) FR(2, 1) FR(2, 2) FR(3, 2)
+  }
+  if constexpr (KB == (sizeof(T) == 8 ? 2 : 4)) {
+    FR(3, 3) FR(4, 3) FR(5, 5) FR(6, 5) FR(7, 6)
+  }
+  if constexpr (KB == 2) {
+    FR(8, 7) FR(9, 8) FR(10, 9)
+  }
+#undef FR
+  return FMMLM_EUNSUPPORTED;
+}
 
-int launch_mfma32(const fmmlm_plan_s* P, int variant, int64_t unit0, int64_t n, unsigned parts, hipStream_t st) {
-  if (n <= 0) return FMMLM_OK;
-  // the per-XCD ranges cover exactly the plan's chunk units
-  if (unit0 != P->unit_split || n != P->nunits - P->unit_split) {
-    set_last_error("internal: FP32 M2L launch range differs from the plan's chunk units");
-    return FMMLM_EUNSUPPORTED;
+template <class T>
+int launch_frame(const fmmlm_plan_s* P, const M2LUnits& U, int variant, unsigned parts, const double* M,
+                 hipStream_t st) {
+  if (U.n <= 0) return FMMLM_OK;
+  const size_t reserve = variant >= 3 ? 61440 : 0;
+  // FP64 from p = 8 on: batches of 2 leave registers for a third wave a SIMD
+  // (p = 10 at 2^20 charges: 0.83 against 0.94 ms; p = 12: 2.61 against 2.93 ms;
+  // p = 8: the same); below, a batch of 2 has no room for the epilogue's rows
+  if (P->p > 13 || (sizeof(T) == 8 && P->p >= 8)) return launch_frame_kb<T, 2>(P, U, 0, parts, M, st);
+  if (P->p != 10) return launch_frame_kb<T, 4>(P, U, reserve, parts, M, st);
+  switch (variant % 3) {  // (FP32, p = 10)
+    case 1: return launch_frame_kb<T, 2>(P, U, reserve, parts, M, st);
+    case 2: return launch_frame_kb<T, 8>(P, U, reserve, parts, M, st);
+    default: return launch_frame_kb<T, 4>(P, U, reserve, parts, M, st);
   }
-  const int nr = (P->p + 1) * (P->p + 1);
-#define MF32(RBW, CBW, WR, NW, KC)                                                                             \
-  m2l_mfma32_kernel<RBW, CBW, WR, NW, KC><<<(unsigned)(8 * P->m2l_xcd_len), 64 * NW, 0, st>>>(                   \
-      nr, P->nrk, unit0, n, P->unit_s, P->step_op, P->step_kind, P->step_src, P->step_mask, P->unit_mask, parts, \
-      P->Tfree32, P->M32, P->W32m, P->m2l_xcd)
-  // slices of 32 operator columns where the padded column count allows
-  const bool k32 = P->nrk % 32 == 0;
-  switch (P->mrt) {
-    case 2: MF32(2, 4, 2, 4, 16); break;
-    case 4:
-      switch (variant) {
-        case 1: MF32(2, 4, 4, 8, 16); break;
-        case 2: MF32(4, 2, 2, 8, 16); break;
-        case 3: MF32(2, 2, 4, 16, 16); break;
-        case 4: MF32(4, 1, 2, 16, 16); break;
-        case 5:
-          if (k32)
-            MF32(4, 1, 2, 16, 32);
-          else
-            MF32(4, 1, 2, 16, 16);
-          break;
-        default:
-          if (k32)
-            MF32(2, 2, 4, 16, 32);
-          else
-            MF32(2, 2, 4, 16, 16);
-          break;
-      }
-      break;
-    case 6: MF32(6, 2, 2, 4, 16); break;
-    case 8: MF32(8, 2, 2, 4, 16); break;
-    case 10: MF32(10, 2, 2, 4, 16); break;
-    default: return FMMLM_EUNSUPPORTED;
-  }
-#undef MF32
+}
+
+template <class T>
+int launch_frame_reduce(const fmmlm_plan_s* P, const M2LUnits& U, double* Lx, hipStream_t st) {
+  if (U.nboxes <= 0) return FMMLM_OK;
+  const FrameRows r = frame_rows(P->p);
+  m2l_frame_reduce_kernel<T><<<(unsigned)U.nboxes, kFrRedThreads, 0, st>>>(
+      (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.boxes, U.ptr, U.slots, U.slot_phi, P->pair_dec, P->blevel,
+      P->sc_levels, static_cast<const T*>(U.W), reinterpret_cast<const cplx*>(P->E), Lx);
   FMM_HIP_TRY(hipGetLastError());
   return FMMLM_OK;
 }
 
-// Autotuner of the FP32 M2L tile shape: every variant runs the plan's own
-// units (operands cleared) once to warm up and three times timed with HIP
+int m2l_variants(const fmmlm_plan_s* P) { return P->mrt == 4 ? kM2LVariants : 1; }
+
+// Autotuner of the FP32 M2L launch: every variant runs the plan's own
+// units (sources cleared) once to warm up and three times timed with HIP
 // events; the fastest is kept.  Times go to the plan's stats.
 int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st) {
   P->m2l_variant = 0;
-  const int64_t n32 = P->nunits - P->unit_split;
   const int nv = m2l_variants(P);
-  if (!P->fp32 || n32 <= 0 || nv < 2) return FMMLM_OK;
+  if (!P->fp32 || P->u32.n <= 0 || nv < 2) return FMMLM_OK;
   const int64_t nr = (int64_t)(P->p + 1) * (P->p + 1);
-  FMM_HIP_TRY(hipMemsetAsync(P->M32, 0, (size_t)P->NB * P->nrk * sizeof(float), st));
+  FMM_HIP_TRY(hipMemsetAsync(P->M, 0, (size_t)(P->NB * nr) * sizeof(double), st));
   hipEvent_t e0, e1;
   FMM_HIP_TRY(hipEventCreate(&e0));
   FMM_HIP_TRY(hipEventCreate(&e1));
@@ -2725,7 +2520,7 @@ int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st) {
     double tmin = 1e300;
     for (int rep = 0; rep < 4 && rc == FMMLM_OK; ++rep) {
       (void)hipEventRecord(e0, st);
-      rc = launch_mfma32(P, v, P->unit_split, n32, FMMLM_FREE | FMMLM_REACTION, st);
+      rc = launch_frame<float>(P, P->u32, v, FMMLM_FREE | FMMLM_REACTION, P->M, st);
       (void)hipEventRecord(e1, st);
       if (rc) break;
       if (hipEventSynchronize(e1) != hipSuccess) {
@@ -2757,7 +2552,7 @@ int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st) {
 // following the main M2L launch.
 int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st) {
   const int nv = m2l_variants(P);
-  if (!P->fp32 || P->nunits - P->unit_split <= 0) return FMMLM_OK;
+  if (!P->fp32 || P->u32.n <= 0) return FMMLM_OK;
   double *q = nullptr, *phi = nullptr;
   FMM_HIP_TRY(hipMalloc(&q, (size_t)P->N * sizeof(double)));
   if (hipMalloc(&phi, (size_t)P->N * sizeof(double)) != hipSuccess) {
@@ -2936,36 +2731,6 @@ int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st) {
   (void)hipEventDestroy(e1);
   P->stats.batch_variant = P->batch_variant;
   return rc;
-}
-
-// The FP64 M2L GEMM over the chunk units [unit0, unit0 + n).  The wave grid per
-// number of 16-row blocks: four row groups where they come out even (or nearly),
-// else two, one for three blocks and fewer; an operator's rows have 32 mrt >=
-// 16 RBW WR of them (the blocks past (p+1)^2 are zero rows).
-int launch_gemm64(const fmmlm_plan_s* P, int64_t unit0, int64_t n, unsigned parts, const double* M, double* W,
-                  hipStream_t st) {
-  if (n <= 0) return FMMLM_OK;
-  const int nr = (P->p + 1) * (P->p + 1);
-  if (P->tile_cols != kGmTB) {
-    set_last_error("internal: M2L chunks do not match the FP64 kernel");
-    return FMMLM_EUNSUPPORTED;
-  }
-#define GM(NB, RBW, WR)                                                                                      \
-  case NB:                                                                                                   \
-    static_assert(16 * RBW * WR <= 32 * (((NB + 1) / 2 + 1) / 2 * 2) && RBW * WR >= NB, "operator rows");     \
-    m2l_gemm_kernel<RBW, WR><<<(unsigned)n, 256, 0, st>>>(nr, P->nrk, 32 * P->mrt, unit0, P->unit_s,           \
-                                                          P->step_op, P->step_kind, P->step_src,             \
-                                                          P->step_mask, P->unit_mask, parts, P->Tfree, M, W); \
-    break;
-  switch ((nr + 15) / 16) {
-    GM(1, 1, 1) GM(2, 2, 1) GM(3, 3, 1) GM(4, 2, 2) GM(6, 3, 2) GM(7, 4, 2) GM(8, 2, 4) GM(9, 5, 2)
-    GM(11, 3, 4) GM(13, 7, 2) GM(15, 4, 4) GM(16, 4, 4) GM(19, 5, 4)
-    default:
-      return FMMLM_EUNSUPPORTED;
-  }
-#undef GM
-  FMM_HIP_TRY(hipGetLastError());
-  return FMMLM_OK;
 }
 
 // M2M (up = true, into M) or L2L (into Lx) of one level through the
@@ -3240,41 +3005,25 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
     const int64_t nl = P->NB * (int64_t)(p + 1) * (p + 1);
     zero_kernel<<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(Lx, nl);
   }
-  const int nr = (p + 1) * (p + 1);
-  const int mr = 32 * P->mrt;
-  // the operator-major chunks below the sparse top levels: FP32 products on the
-  // matrix cores in the FP32 form, FP64 ones (the tile GEMM) in the FP64 form
-  const int64_t n64 = P->fp32 ? 0 : P->nunits - P->unit_split;
-  const int64_t n32 = P->fp32 ? P->nunits - P->unit_split : 0;
-  auto gemm64 = [&]() -> int {
-    return launch_gemm64(P, P->unit_split, n64, parts, M, P->Wm2l, st);
-  };
-  // the sparse top levels write other boxes than the tiles: on their own
-  // stream (unprofiled), joined before L2L
-  const bool top_side = overlap && P->n_sp_boxes > 0;
+  // the FP32 form's top levels stay FP64 and write other boxes than the rest: on
+  // their own stream (unprofiled), joined before L2L
+  const bool top = P->fp32 && P->u64.n > 0;
+  const bool top_side = overlap && top && P->u32.n > 0;
   if (top_side) {
     FMM_HIP_TRY(hipEventRecord(P->ev_m, st));
     FMM_HIP_TRY(hipStreamWaitEvent(P->s_top, P->ev_m, 0));
   }
-  if (P->n_sp_boxes > 0) {
+  if (top) {
     hipStream_t ss = top_side ? P->s_top : st;
-    m2l_sparse_kernel<<<(unsigned)P->n_sp_items, P->sp_threads, (size_t)P->sp_ne * P->sp_bytes, ss>>>(
-        p, nc, P->ngs, P->sp_ne, P->sp_tps, P->sp_items, P->m2l_ptr, P->m2l_nfree, P->m2l_src, P->m2l_op, P->G,
-        reinterpret_cast<const cplx*>(P->E), P->coefA, M, parts, reinterpret_cast<cplx*>(P->Psp));
-    m2l_sparse_reduce_kernel<<<(unsigned)P->n_sp_boxes, 128, 0, ss>>>(
-        p, nc, P->sp_boxes, P->sp_item_ptr, reinterpret_cast<const cplx*>(P->Psp), P->blevel, P->sc_levels,
-        P->coefA, Lx);
+    if (int rc = launch_frame<double>(P, P->u64, 0, parts, M, ss)) return rc;
+    if (int rc = launch_frame_reduce<double>(P, P->u64, Lx, ss)) return rc;
   }
   if (top_side) FMM_HIP_TRY(hipEventRecord(P->ev_top, P->s_top));
-  if (n32 > 0) {
-    const int64_t nm = P->NB * (int64_t)P->nrk;
-    to_f32_pad_kernel<<<(unsigned)((nm + 255) / 256), 256, 0, st>>>(M, P->NB, nr, P->nrk, P->M32);
-  }
   mark();
-  if (!P->fp32) {
-    if (int rc = gemm64()) return rc;
-  } else if (n32 > 0) {
-    if (int rc = launch_mfma32(P, P->m2l_variant, P->unit_split, n32, parts, st)) return rc;
+  if (P->fp32) {
+    if (int rc = launch_frame<float>(P, P->u32, P->m2l_variant, parts, M, st)) return rc;
+  } else if (int rc = launch_frame<double>(P, P->u64, 0, parts, M, st)) {
+    return rc;
   }
   if (overlap) {
     FMM_HIP_TRY(hipEventRecord(P->ev_l, st));
@@ -3284,14 +3033,11 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
     FMM_HIP_TRY(hipEventRecord(P->ev_near, P->s_near));
   }
   mark();
-  // each target's chunk products, in slot order
-  if (P->n_slot_boxes > 0) {
-    if (P->fp32)
-      m2l_slot_reduce_kernel<float><<<(unsigned)P->n_slot_boxes, 128, 0, st>>>(
-          nr, mr, P->tile_cols, P->slot_boxes, P->slot_ptr, P->slots, P->blevel, P->sc_levels, P->W32m, Lx);
-    else
-      m2l_slot_reduce_kernel<double><<<(unsigned)P->n_slot_boxes, 128, 0, st>>>(
-          nr, mr, P->tile_cols, P->slot_boxes, P->slot_ptr, P->slots, P->blevel, P->sc_levels, P->Wm2l, Lx);
+  // each target's products, in slot order
+  if (P->fp32) {
+    if (int rc = launch_frame_reduce<float>(P, P->u32, Lx, st)) return rc;
+  } else if (int rc = launch_frame_reduce<double>(P, P->u64, Lx, st)) {
+    return rc;
   }
   mark();
   if (top_side) FMM_HIP_TRY(hipStreamWaitEvent(st, P->ev_top, 0));

@@ -16,14 +16,6 @@ namespace fmmlm {
 constexpr int kMaxL = FMMLM_MAX_INTERFACES;
 constexpr int kPMax = FMMLM_PMAX;
 constexpr int kMaxLevel = 20;  // 21-bit quantisation per axis
-// sparse top-level M2L: threads of a block, rounds of entries per work item
-constexpr int kSpThreads = 512;
-constexpr int kSpItemRounds = 1;
-// zeros before an operator's table (orders down to -N - 3 are read) and after it (up to N + 6)
-constexpr int kGPad = 3;
-constexpr int kGPadEnd = 6;
-// LDS of a sparse top-level block: three fit a CU
-constexpr int kSpLds = 53248;
 // batched FP32 form, FP64 top levels: entries per work item
 constexpr int kBatchTopItem = 24;
 // reaction P2P: target rows per work unit (one wave, 8 lanes a row)
@@ -32,17 +24,13 @@ constexpr int kRPUnitRows = 8;
 // a lane (8 in FP32, 4 in FP64)
 constexpr int kPLUnitTargetsF32 = 128;
 constexpr int kPLUnitTargetsF64 = 64;
-// operator-major M2L: operators grouped into one chunk's steps, and the
-// fewest targets common to a group's operators that make grouped chunks
+// zeros before an operator's table G and after it
+constexpr int kGPad = 3;
+constexpr int kGPadEnd = 6;
+// M2L in operator frames: most steps (operators) of a unit
 constexpr int kM2LGroupOps = 4;
-constexpr int kM2LGroupMinTargets = 64;
-
-// unit ranges of the FP32 M2L launch per XCD (the 8 XCDs take blocks in turn):
-// XCD x runs units [off[x], off[x + 1]) of the launch, ranges of about equal
-// steps
-struct XcdSplit {
-  int32_t off[9];
-};
+// fewest columns for which a list of several operators makes units of its own
+constexpr size_t kM2LFewCols = 32;
 
 // ---- small complex type (device and host) ------------------------------------
 struct cplx {
@@ -119,6 +107,25 @@ struct GraphKey {
            st == o.st;
   }
 };
+// Units of the M2L in operator frames, all in one precision: a unit is `cols`
+// columns (a target box, an azimuth, and per step a source box) that share the
+// steps' operators; column c of unit u is slot u cols + c, whose product the
+// target adds up in slot order
+struct M2LUnits {
+  int cols = 64;
+  int64_t n = 0, nsteps = 0, ncols = 0;  // units, steps, columns in use
+  int32_t *step0 = nullptr;     // [n + 1] first step of each unit
+  int32_t *kind = nullptr;      // [n] FMMLM_FREE or FMMLM_REACTION
+  int32_t *phi = nullptr;       // [n cols] azimuth index of each column
+  int32_t *op = nullptr;        // [nsteps] operator (index into A)
+  int32_t *src = nullptr;       // [nsteps cols] source box, -1: none
+  int64_t nboxes = 0;           // target boxes
+  int32_t *boxes = nullptr, *ptr = nullptr, *slots = nullptr, *slot_phi = nullptr;
+  int64_t nops = 0;
+  int32_t *frame_op = nullptr;  // [nops] operator of G
+  void *A = nullptr;            // [nops] frame operators in the kernel's layout (double or float)
+  void *W = nullptr;            // [n cols][nrk] products (rows of c, then of s)
+};
 }  // namespace fmmlm
 
 struct fmmlm_plan_s {
@@ -157,17 +164,20 @@ struct fmmlm_plan_s {
   int32_t *m2l_ptr = nullptr;      // [NB + 1] ; free entries first, then reaction
   int32_t *m2l_nfree = nullptr;    // [NB] number of free entries per target box
   int32_t *m2l_src = nullptr, *m2l_op = nullptr;  // op < 0 encodes mirrored source: ~op
-  double* G = nullptr;             // operators at azimuth 0 [nops][ngs] (kGPad zeros, rows j of orders -j..j, zeros)
-  double* E = nullptr;             // their phases e^{i k phi} [nops][2p + 1] complex
+  // M2L operators in the frame turned to their azimuth: free space by (rho^2,
+  // dz), reaction by Sommerfeld task; an operator of an entry is one of them and
+  // an azimuth
+  double* G = nullptr;             // [ng_ops][ngs] (kGPad zeros, rows j of orders -j..j, zeros)
+  int64_t ng_ops = 0, ng_free = 0;
   int ngs = 0;                     // stride of G (even)
-  // M2L as GEMMs over operator-major chunks (a chunk is a tile of its own)
-  double* Tfree = nullptr;         // [nops][nrk][32 mrt] real-form operators (free space, then reaction)
-  int nrk = 0, mrt = 0;            // padded inner dimension, rows per thread / 32
-  int tile_cols = 64;              // target boxes per tile (128 when mrt <= 4)
-  int64_t tile_grp[5] = {0};       // target-tile groups (none: all zero, the chunks follow)
-  int m2l_variant = 0;             // FP32 M2L tile shape picked by the autotuner
-  fmmlm::XcdSplit m2l_xcd{};        // FP32 M2L: the chunk units' ranges per XCD
-  int32_t m2l_xcd_len = 0;          //   ... and the longest range (blocks per XCD)
+  double* E = nullptr;             // azimuths: e^{i k phi}, k <= 2p [n_phi][2p + 1] complex
+  int64_t n_phi = 0;
+  int32_t *op_frame = nullptr, *op_phi = nullptr;  // [nops] (batched plans: the dense operators' build)
+  int32_t *pair_dec = nullptr;     // [nc] pair j: offset in the real layout | order << 16 (orders >= 1 first)
+  fmmlm::M2LUnits u64, u32;               // FP64 form: u64 all levels; FP32 form: u64 top levels, u32 the rest
+  double* Tfree = nullptr;         // batched plans: [nops][nrk][32 mrt] real-form operators (free space, then reaction)
+  int nrk = 0, mrt = 0;            // padded inner dimension, padded rows / 32
+  int m2l_variant = 0;             // FP32 M2L launch variant picked by the autotuner
   int batch_variant = 0;           // batched FP32 M2L shape / persistence picked by the autotuner
   // M2M / L2L as GEMMs: 16 real-form operators (8 child octants up, 8 down)
   // and their own tiles; per level (first tile, first unit, end tile, end unit)
@@ -178,31 +188,10 @@ struct fmmlm_plan_s {
   int32_t *xl_step_op = nullptr, *xl_step_src = nullptr;
   int32_t *xl_unit_s = nullptr, *xl_unit_mask = nullptr, *xl_tile_unit_ptr = nullptr, *xl_tile_tgt = nullptr;
   int xl_tile_cols = 32;           // target boxes per translation tile
-  int32_t* sp_boxes = nullptr;     // target boxes of the sparse top levels (no tiles there)
-  // their work items (sparse box, first entry, end entry), per box a run of
-  // items (sp_item_ptr), partial sums per item [n_sp_items][nc] complex
-  int32_t *sp_items = nullptr, *sp_item_ptr = nullptr;
-  int64_t n_sp_items = 0;
-  int sp_ne = 1;                   // entries per round of an item's block ...
-  int sp_threads = 64;             //   ... and its threads (a multiple of 64)
-  int sp_tps = 1;                  //   ... threads of an entry
-  int sp_bytes = 0;                //   ... LDS of an entry
-  double* Psp = nullptr;
-  // FP32 form: operator-major chunks; per target box its slots (unit * tile_cols + column)
-  int32_t *slot_boxes = nullptr, *slot_ptr = nullptr, *slots = nullptr;
-  int64_t n_slot_boxes = 0;
-  int64_t n_sp_boxes = 0;
-  // work units: a tile's steps split into chunks (more blocks in flight)
-  int64_t nunits = 0, unit_split = 0;
-  int32_t *unit_s = nullptr;       // [2 * nunits] step range of each unit
-  int32_t *unit_mask = nullptr;    // [nunits] column groups of 8 that the unit's partial holds
-  int32_t *tile_unit_ptr = nullptr;// [ntiles + 1]
-  double* Wm2l = nullptr;          // [nunits][tile_cols][32 mrt] partial products (FP64 form)
-  float* W32m = nullptr;           // the same in FP32 (FP32 form)
   // FP32 form
   bool fp32 = false;
-  float* Tfree32 = nullptr;        // FP32 copy of Tfree
-  float* M32 = nullptr;            // FP32 copy of the multipole expansions (GEMM operand)
+  float* Tfree32 = nullptr;        // batched FP32 form: FP32 copy of Tfree
+  float* M32 = nullptr;            // batched FP32 form: FP32 copy of the multipole expansions (GEMM operand)
   float *pxh = nullptr, *pxl = nullptr, *pyh = nullptr, *pyl = nullptr, *phh = nullptr, *phl = nullptr;
   float* qt32 = nullptr;
   // batched form (opts.max_rhs > 1): expansions, charges and potentials of up
@@ -221,10 +210,6 @@ struct fmmlm_plan_s {
                                    // the point-major potentials of the combine
   double* qu = nullptr;            // [N][64] point-major charges in user order (batched gather)
   float* qb32 = nullptr;           // [NP][64] (FP32 form)
-  int64_t ntiles = 0, nsteps = 0;
-  int32_t *tile_ptr = nullptr, *tile_tgt = nullptr, *tile_level = nullptr;
-  int32_t *step_op = nullptr, *step_src = nullptr, *step_kind = nullptr;
-  int32_t *step_mask = nullptr;    // per step: bit g set if columns [8 g, 8 g + 8) hold a source
   int64_t nops = 0, n_free_ops = 0;
   // P2P free, CSR over leaves
   int32_t *p2p_ptr = nullptr;      // [nleaves + 1]
@@ -400,14 +385,16 @@ int gpu_interp2d(const TableGrid& g, int nout, const double* d_nodes, int64_t n,
                  const double* d_zeta, double* d_out, hipStream_t st);
 
 // fmm.hip
-int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_off,
-                  const std::vector<int>& reac_task, const std::vector<double>& reac_phi,
-                  const std::vector<double>& reac_S, const double* d_tables, hipStream_t st);
+// G from the free operators' (rho^2, dz) and the tasks' tables; azimuths from (dx, dy)
+int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_r2dz, const std::vector<SommTask>& tasks,
+                  const std::vector<int>& dirs, const double* d_tables, hipStream_t st);
+int gpu_build_frame_ops(fmmlm_plan_s* P, M2LUnits& U, bool f32, hipStream_t st);
+int64_t frame_op_len(int p, int64_t* row_len);  // values of a frame operator, of one of its columns
 int gpu_build_real_ops(fmmlm_plan_s* P, hipStream_t st);
 int gpu_build_xlate_ops(fmmlm_plan_s* P, hipStream_t st);
 int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st);
 int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st);
-constexpr int kM2LVariants = 6;  // FP32 M2L tile shapes the autotuner tries
+constexpr int kM2LVariants = 6;  // FP32 M2L launch variants the autotuner tries
 constexpr int kBatchShapes = 5;  // batched FP32 M2L tile shapes (each also persistent)
 int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st);
 // target point, source point and component of every reaction near-field pair,
