@@ -42,16 +42,15 @@ __device__ __forceinline__ void far_chain_priority() { __builtin_amdgcn_s_setpri
 
 __device__ inline double sgn1(int k) { return (k & 1) ? -1.0 : 1.0; }
 
-// FP64 1/sqrt(r2): hardware estimate refined by two Newton steps.
+// FP64 1/sqrt(r2): hardware estimate y (relative error about 2^-24) and one
+// third-order step: with e = 1 - r2 y^2, y (1 - e)^{-1/2} = y (1 + e/2 + 3 e^2/8 + ..),
+// what is left is 5/16 e^3, below 2^-68.  Five operations, where two Newton
+// steps take eight.
 __device__ inline double rsqrt_nr(double r2) {
-  double y = __builtin_amdgcn_rsq(r2);
-  double h = r2 * y * y;
-  y = y * fma(-0.5, h, 1.5);
-  h = r2 * y * y;
-  y = y * fma(-0.5, h, 1.5);
-  return y;
+  const double y = __builtin_amdgcn_rsq(r2);
+  const double e = fma(-(r2 * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
-
 
 // R_n^m(x, y, z) for one (n, m), m >= 0, by the diagonal then the n recurrence.
 __device__ inline cplx regular_nm(int n, int m, double x, double y, double z) {
@@ -1769,9 +1768,9 @@ __device__ inline double pl_rsqrt<double>(double r2) { return rsqrt_nr(r2); }
 template <class T>
 struct PLCfg;
 template <>
-struct PLCfg<float> { static constexpr int kMaxTPL = 8; };  // a unit covers 128 targets
+struct PLCfg<float> { static constexpr int kMaxTPL = 8, kNS = 4, kWaves = 4; };
 template <>
-struct PLCfg<double> { static constexpr int kMaxTPL = 4; };  // 64 (register pressure)
+struct PLCfg<double> { static constexpr int kMaxTPL = 8, kNS = 2, kWaves = 3; };
 
 // One pair: MASK skips pairs at zero distance (the self pair, or two points at
 // one position, which share a leaf): only sources of the target leaf itself
@@ -1882,24 +1881,27 @@ __device__ inline void pl_mrange(const typename PLVec<T>::type* __restrict__ src
   using V = typename PLVec<T>::type;
   j0 = __builtin_amdgcn_readfirstlane(j0);
   j1 = __builtin_amdgcn_readfirstlane(j1);
+  constexpr int NS = PLCfg<T>::kNS;  // sources of a group in flight
   int j = j0;
-  for (; j + 16 <= j1; j += 16) {
-    const V s0 = src[j + g], s1 = src[j + 4 + g], s2 = src[j + 8 + g], s3 = src[j + 12 + g];
-    T b0 = T(0), b1 = T(0), b2 = T(0), b3 = T(0);
+  for (; j + 4 * NS <= j1; j += 4 * NS) {
+    V s[NS];
+    T b[NS];
 #pragma unroll
-    for (int t = 0; t < TPL; ++t) {
-      pl_two<T, false>(s0, true, x[t], y[t], z[t], q[t], p[t], b0);
-      pl_two<T, false>(s1, true, x[t], y[t], z[t], q[t], p[t], b1);
-      pl_two<T, false>(s2, true, x[t], y[t], z[t], q[t], p[t], b2);
-      pl_two<T, false>(s3, true, x[t], y[t], z[t], q[t], p[t], b3);
+    for (int k = 0; k < NS; ++k) {
+      s[k] = src[j + 4 * k + g];
+      b[k] = T(0);
     }
-    b0 = pl_row_sum(b0);
-    b1 = pl_row_sum(b1);
-    b2 = pl_row_sum(b2);
-    b3 = pl_row_sum(b3);
-    // lane slot k < 4 of group g stores source j + 4 k + g: 16 consecutive values
-    const T bv = sl == 0 ? b0 : (sl == 1 ? b1 : (sl == 2 ? b2 : b3));
-    if (sl < 4) out[oidx[j + 4 * sl + g]] = bv;
+#pragma unroll
+    for (int t = 0; t < TPL; ++t)
+#pragma unroll
+      for (int k = 0; k < NS; ++k) pl_two<T, false>(s[k], true, x[t], y[t], z[t], q[t], p[t], b[k]);
+#pragma unroll
+    for (int k = 0; k < NS; ++k) b[k] = pl_row_sum(b[k]);
+    // lane slot k < NS of group g stores source j + 4 k + g: 4 NS consecutive values
+    T bv = b[NS - 1];
+#pragma unroll
+    for (int k = NS - 2; k >= 0; --k) bv = sl == k ? b[k] : bv;
+    if (sl < NS) out[oidx[j + 4 * sl + g]] = bv;
   }
   for (; j < j1; j += 4) {
     const int jj = j + g;
@@ -2019,7 +2021,7 @@ __device__ void pl_mpass(int tb, int tcp, int t0, int tc, double cx, double cy, 
 }
 
 template <class T>
-__global__ void __launch_bounds__(kPLThreads, 4)
+__global__ void __launch_bounds__(kPLThreads, PLCfg<T>::kWaves)
 p2p_mutual_kernel(int64_t u0, const int32_t* __restrict__ mu_order, const int32_t* __restrict__ mu_leaf,
                   const int32_t* __restrict__ mu_tb,
                   const int32_t* __restrict__ mu_rptr, const int32_t* __restrict__ mu_rng,

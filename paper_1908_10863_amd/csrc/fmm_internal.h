@@ -23,7 +23,7 @@ constexpr int kRPUnitRows = 8;
 // free P2P (single vector): targets of one work unit, 16 lane slots x targets
 // a lane (8 in FP32, 4 in FP64)
 constexpr int kPLUnitTargetsF32 = 128;
-constexpr int kPLUnitTargetsF64 = 64;
+constexpr int kPLUnitTargetsF64 = 128;
 // zeros before an operator's table G and after it
 constexpr int kGPad = 3;
 constexpr int kGPadEnd = 6;
