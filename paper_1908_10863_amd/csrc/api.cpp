@@ -656,6 +656,32 @@ int build_m2l_units(fmmlm_plan_s* P, int64_t b0, int64_t b1, const std::vector<i
     }
     ptr.push_back((int32_t)slots.size());
   }
+  if (P->fp32 && P->opts.max_rhs > 1) {  // the batched FP32 form goes box by box
+    std::vector<int32_t> bptr(1, 0), bop, bphi, bsrc, bkind;
+    for (int64_t b = b0; b < b1; ++b) {
+      ent.clear();
+      for (int32_t e = mptr[b]; e < mptr[b + 1]; ++e) {
+        const OpFrame& f = fr[mop[e] >= 0 ? mop[e] : ~mop[e]];
+        ent.push_back(Ent{0, f.frame, msrc[e], f.phi});
+      }
+      std::sort(ent.begin(), ent.end(), [](const Ent& x, const Ent& y) {
+        return x.phi != y.phi ? x.phi < y.phi : (x.frame != y.frame ? x.frame < y.frame : x.src < y.src);
+      });
+      for (const Ent& e : ent) {
+        bop.push_back(fmap[e.frame]);
+        bphi.push_back(e.phi);
+        bsrc.push_back(e.src);
+        bkind.push_back(e.frame < P->ng_free ? (int32_t)FMMLM_FREE : (int32_t)FMMLM_REACTION);
+      }
+      bptr.push_back((int32_t)bop.size());
+    }
+    U->box0 = b0;
+    int rb;
+    if ((rb = dev_upload(P, &U->bptr, bptr, st)) || (rb = dev_upload(P, &U->be_op, bop, st)) ||
+        (rb = dev_upload(P, &U->be_phi, bphi, st)) || (rb = dev_upload(P, &U->be_src, bsrc, st)) ||
+        (rb = dev_upload(P, &U->be_kind, bkind, st)))
+      return rb;
+  }
   U->n = (int64_t)kind.size();
   U->nsteps = (int64_t)op.size();
   U->nboxes = (int64_t)boxes.size();
@@ -967,7 +993,8 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     P->ng_free = (int64_t)(free_r2dz.size() / 2);
     P->ng_ops = P->ng_free + (int64_t)B.tasks.size();
     P->n_phi = (int64_t)(dirs.size() / 2);
-    if (P->opts.max_rhs > 1) {
+    P->ntop = P->fp32 ? top_end : 0;
+    if (P->opts.max_rhs > 1 && !P->fp32) {
       std::vector<int32_t> of, op;
       for (const OpFrame& f : fr) {
         of.push_back(f.frame);
@@ -1378,16 +1405,13 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     U->W = W;
     if ((rc = gpu_build_frame_ops(P, *U, f32, st))) return rc;
   }
-  if (P->opts.max_rhs > 1) {  // the batched form's dense operators
+  if (P->opts.max_rhs > 1 && !P->fp32) {  // the batched FP64 form's dense operators
     if ((rc = dev_alloc(P, &P->Tfree, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt))) return rc;
     if ((rc = gpu_build_real_ops(P, st))) return rc;
   }
   if ((rc = dev_alloc(P, &P->Txl, (size_t)16 * P->nrk * 32 * P->mrt))) return rc;
   if ((rc = gpu_build_xlate_ops(P, st))) return rc;
   if (P->fp32) {
-    if (P->opts.max_rhs > 1 &&
-        (rc = dev_alloc(P, &P->Tfree32, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt)))
-      return rc;
     if ((rc = dev_alloc(P, &P->qt32, P->NP))) return rc;
     if ((rc = dev_alloc(P, &P->pxh, P->NP)) || (rc = dev_alloc(P, &P->pxl, P->NP)) ||
         (rc = dev_alloc(P, &P->pyh, P->NP)) || (rc = dev_alloc(P, &P->pyl, P->NP)) ||
@@ -1452,8 +1476,12 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     FMM_HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
   if ((rc = dev_alloc(P, &P->M, (size_t)P->NB * nrr * G))) return rc;
   if ((rc = dev_alloc(P, &P->Lx, (size_t)P->NB * nrr * G))) return rc;
-  // FP32 sources of the batched form: [vector][box][nrk] (aligned rows, zero past nr)
-  if (P->fp32 && G > 1 && (rc = dev_alloc(P, &P->M32, (size_t)P->NB * P->nrk * G))) return rc;
+  if (P->fp32 && G > 1) {  // sources of the batched form
+    P->gw = (int)(G + 15) / 16 * 16;
+    if ((rc = dev_alloc(P, &P->M32, (size_t)P->NB * P->nc * P->gw * 2)) ||
+        (rc = dev_alloc(P, &P->M64, (size_t)std::max<int64_t>(P->ntop, 1) * P->nc * P->gw * 2)))
+      return rc;
+  }
   if (P->fp32 && (rc = gpu_tune_m2l(P, st))) return rc;
   if (G > 1) {
     if ((rc = dev_alloc(P, &P->qb64, P->NP * 64))) return rc;
@@ -1467,12 +1495,25 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
       }
     P->nbbox = (int64_t)bb.size();
     if ((rc = dev_upload(P, &P->bbox, bb, st))) return rc;
+    {
+      // the boxes below the FP64 top levels in 8 contiguous ranges of about equal
+      // entries, one per XCD
+      const int64_t s0 = P->bbox_split;
+      int64_t tot = 0, acc = 0, i = s0;
+      for (int64_t k = s0; k < P->nbbox; ++k) tot += mptr[bb[k] + 1] - mptr[bb[k]];
+      P->bbox_xcd.off[0] = 0;
+      for (int x = 1; x <= 8; ++x) {
+        for (; i < P->nbbox && (x == 8 || acc < tot * x / 8); ++i) acc += mptr[bb[i] + 1] - mptr[bb[i]];
+        P->bbox_xcd.off[x] = (int32_t)(i - s0);
+        P->bbox_xcd_len = std::max(P->bbox_xcd_len, P->bbox_xcd.off[x] - P->bbox_xcd.off[x - 1]);
+      }
+    }
     if (P->fp32 && P->bbox_split > 0) {
       // the FP64 top levels of the batched FP32 form: work items of at most
       // kBatchTopItem entries of one box (few boxes, long entry lists)
       std::vector<int32_t> items, iptr(1, 0);
       for (int64_t bi = 0; bi < P->bbox_split; ++bi) {
-        const int32_t b = bb[bi];
+        const int32_t b = bb[bi];  // (the top levels' entries are the first of u64's, box by box)
         for (int32_t e = mptr[b]; e < mptr[b + 1]; e += kBatchTopItem) {
           items.push_back((int32_t)bi);
           items.push_back(e);

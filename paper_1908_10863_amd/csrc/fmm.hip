@@ -883,22 +883,21 @@ m2l_frame_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restri
 
 // Each target box turns its slots' products back (e^{-i m phi}) and sums them in
 // FP64 in a fixed order, scaled by 1/S of its level, into its local expansion.
-// One block per target box: kFrRedThreads / nc groups of nc threads (one a pair)
+// One block per target box: NT / nc groups of nc threads (one a pair)
 // take every so many-th slot, four in flight, and the groups' sums are added in
 // LDS in group order.  Bound by the products' bytes.
-constexpr int kFrRedThreads = 256;
-template <class T>
-__global__ void __launch_bounds__(kFrRedThreads)
+template <class T, int NT>
+__global__ void __launch_bounds__(NT)
 m2l_frame_reduce_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restrict__ boxes,
                         const int32_t* __restrict__ sptr, const int32_t* __restrict__ slots,
                         const int32_t* __restrict__ sphi, const int32_t* __restrict__ dec,
                         const int32_t* __restrict__ blevel, const double* __restrict__ sc,
                         const T* __restrict__ W, const cplx* __restrict__ E, double* __restrict__ Lx) {
   far_chain_priority();
-  __shared__ cplx sum[kFrRedThreads];
+  __shared__ cplx sum[NT];
   const int b = boxes[blockIdx.x];
   const int k0 = sptr[blockIdx.x], k1 = sptr[blockIdx.x + 1];
-  const int groups = kFrRedThreads / nc;
+  const int groups = NT / nc;
   const int g = threadIdx.x / nc, j = threadIdx.x - g * nc;
   const int d = dec[j], m = d >> 16;
   if (g < groups) {
@@ -1055,8 +1054,7 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
                    const int32_t* __restrict__ mptr, const int32_t* __restrict__ msrc,
                    const int32_t* __restrict__ mop, int nfree, unsigned parts,
                    const int32_t* __restrict__ blevel, const double* __restrict__ sc,
-                   const double* __restrict__ T, const double* __restrict__ M, double* __restrict__ Lx,
-                   const int32_t* __restrict__ items = nullptr, double* __restrict__ part = nullptr) {
+                   const double* __restrict__ T, const double* __restrict__ M, double* __restrict__ Lx) {
   far_chain_priority();
   constexpr int KC = (MRT <= 4) ? 16 : 8;
   constexpr int MR = 32 * MRT;
@@ -1068,10 +1066,7 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
   static_assert(NTR * 256 == KC * MR && NBR * 256 == KC * TB, "slice must split evenly over the threads");
   __shared__ double Ts[2][KC * TS];
   __shared__ double Bs[2][KC * BSR];
-  // one box and all its entries, or (items) one work item: a run of a box's
-  // entries, whose unscaled product goes to the item's partial
-  const int64_t item = blockIdx.x;
-  const int b = boxes[box0 + (items ? items[3 * item] : (int)blockIdx.x)];
+  const int b = boxes[box0 + blockIdx.x];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int row0 = (wave & 1) * (MR / 2), col0 = (wave >> 1) * 32;
@@ -1081,7 +1076,7 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
   for (int i = 0; i < MRT; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-  const int s0 = items ? items[3 * item + 1] : mptr[b], s1 = items ? items[3 * item + 2] : mptr[b + 1];
+  const int s0 = mptr[b], s1 = mptr[b + 1];
   const int nch = nrk / KC;
   const int total = (s1 - s0) * nch;
   const int64_t slab = nb * (int64_t)nr;  // one vector's expansions
@@ -1151,10 +1146,7 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
       for (int v = 0; v < 4; ++v) {
         const int row = row0 + 16 * i + lk + 4 * v;
         if (row >= nr) continue;
-        if (items)
-          part[(item * 64 + col) * nr + row] = acc[i][j][v];
-        else
-          Lx[col * slab + (int64_t)b * nr + row] += acc[i][j][v] * inv;
+        Lx[col * slab + (int64_t)b * nr + row] += acc[i][j][v] * inv;
       }
   }
 }
@@ -1177,167 +1169,205 @@ m2l_btop_reduce_kernel(int nr, int g, const int32_t* __restrict__ boxes, const i
   }
 }
 
-// FP32 variant on the matrix cores (same fragment layout as m2l_mfma32_kernel):
-// NW wavefronts arranged WR x WC over the operator rows and the 64 vectors, each
-// owning RBW x CBW blocks of 16 x 16, with the entries combined by compensated
-// summation.  Operator and operand slices of KC columns are double-buffered in
-// LDS (one barrier a slice, global loads two slices ahead).  PERSIST: a grid of
-// resident blocks walks the boxes; block i runs on XCD i mod 8 (workgroups are
-// dispatched to the 8 XCDs in turn), and each XCD takes a contiguous eighth of
-// the boxes so that the source expansions that neighbouring targets share stay
-// in that XCD's L2.  Otherwise one block per box.
-template <int RBW, int CBW, int WR, int NW, bool PERSIST, int KC>
-__global__ void __launch_bounds__(64 * NW)
-m2l_batch32_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict__ boxes, int64_t box0,
-                   int64_t nbox, const int32_t* __restrict__ mptr, const int32_t* __restrict__ msrc,
-                   const int32_t* __restrict__ mop, int nfree, unsigned parts,
-                   const int32_t* __restrict__ blevel, const double* __restrict__ sc,
-                   const float* __restrict__ T, const float* __restrict__ M, double* __restrict__ Lx) {
-  constexpr int NT = 64 * NW;
-  constexpr int WC = NW / WR;
-  constexpr int MR = 16 * RBW * WR;
-  constexpr int TB = 16 * CBW * WC;
-  static_assert(TB == 64, "the 64 vectors of a pass are the tile's columns");
-  constexpr int TS = MR + 16;
-  constexpr int BSR = TB + 17;  // (the operand slice is stored transposed)
-  constexpr int NTR = KC * MR / NT;
-  constexpr int NBR = KC * TB / NT;
-  static_assert(NTR * NT == KC * MR && NBR * NT == KC * TB, "slice must split evenly over the threads");
-  // two LDS buffers: slice q + 1 is stored while slice q is multiplied
-  __shared__ __align__(16) float Ts[2][KC * TS];
-  __shared__ float Bs[2][KC * BSR];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int row0 = (wave % WR) * RBW * 16, col0 = (wave / WR) * CBW * 16;
-  const int li = lane & 15, lk = lane >> 4;
-  const int64_t slab = nb * (int64_t)nr;
-  int64_t i0 = blockIdx.x, i1 = blockIdx.x + 1, istep = 1;
-  if (PERSIST) {
-    const int64_t per_xcd = (gridDim.x + 7) / 8;
-    const int64_t part = (nbox + 7) / 8;
-    const int64_t xcd = blockIdx.x % 8, k = blockIdx.x / 8;
-    i0 = xcd * part + k;
-    i1 = min(nbox, (xcd + 1) * part);
-    istep = per_xcd;
-  }
-  for (int64_t it = i0; it < i1; it += istep) {
-    const int b = boxes[box0 + it];
-    floatx4 acc[RBW][CBW], cmp[RBW][CBW], part[RBW][CBW];
-#pragma unroll
-    for (int i = 0; i < RBW; ++i)
-#pragma unroll
-      for (int j = 0; j < CBW; ++j) {
-        acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        cmp[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        part[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-      }
-    const int s0 = mptr[b], s1 = mptr[b + 1];
-    const int nch = nrk / KC;
-    const int total = (s1 - s0) * nch;
-    // 16-byte loads: operator slices are contiguous and the FP32 sources are
-    // [vector][box][nrk] (aligned rows, zero past nr); UT / UB 16-byte units a
-    // slice (the last round may leave threads idle)
-    constexpr int UT = KC * MR / 4, UB = KC * TB / 4;
-    constexpr int NTR4 = (UT + NT - 1) / NT, NBR4 = (UB + NT - 1) / NT;
-    static_assert(KC % 4 == 0 && MR % 4 == 0 && TS % 4 == 0, "16-byte staging");
-    const int64_t slab32 = nb * (int64_t)nrk;
-    float4 rt[NTR4], rb[NBR4];
-    auto load = [&](int q) {
-      const int s = s0 + q / nch, k0 = (q % nch) * KC;
-      const int op = mop[s] >= 0 ? mop[s] : ~mop[s];
-      const unsigned kind = (op < nfree) ? FMMLM_FREE : FMMLM_REACTION;
-      const float4* Tc = reinterpret_cast<const float4*>(T + ((int64_t)op * nrk + k0) * MR);
-      const int sb = (parts & kind) ? msrc[s] : -1;
-#pragma unroll
-      for (int r = 0; r < NTR4; ++r) {
-        const int u = tid + NT * r;
-        if (u < UT) rt[r] = Tc[u];
-      }
-#pragma unroll
-      for (int r = 0; r < NBR4; ++r) {
-        const int u = tid + NT * r, col = u / (KC / 4), k = k0 + 4 * (u % (KC / 4));
-        rb[r] = (sb >= 0 && u < UB && col < g)
-                    ? *reinterpret_cast<const float4*>(M + col * slab32 + (int64_t)sb * nrk + k)
-                    : float4{0.f, 0.f, 0.f, 0.f};
-      }
-    };
-    auto stash = [&](int buf) {
-#pragma unroll
-      for (int r = 0; r < NTR4; ++r) {
-        const int u = tid + NT * r, i = 4 * u;
-        if (u < UT) *reinterpret_cast<float4*>(&Ts[buf][(i / MR) * TS + (i % MR)]) = rt[r];
-      }
-#pragma unroll
-      for (int r = 0; r < NBR4; ++r) {
-        const int u = tid + NT * r, col = u / (KC / 4), k = 4 * (u % (KC / 4));
-        if (u < UB) {
-          Bs[buf][(k + 0) * BSR + col] = rb[r].x;
-          Bs[buf][(k + 1) * BSR + col] = rb[r].y;
-          Bs[buf][(k + 2) * BSR + col] = rb[r].z;
-          Bs[buf][(k + 3) * BSR + col] = rb[r].w;
-        }
-      }
-    };
-    if (total > 0) {
-      load(0);
-      stash(0);
-      if (total > 1) load(1);
-    }
+// Expansions of all vectors, vector-minor, for the batched M2L: X [box][pair][gw]
+// (re, im) of M [vector][box][(p+1)^2], zeros from vector g on.  One block per box;
+// tiles of 64 coefficients x the vectors are read row by row and turned in LDS
+// (read column by column they took 0.82 ms at 7,571 boxes, p = 10, 64 vectors).
+template <class T>
+__global__ void __launch_bounds__(256)
+vector_minor_kernel(int nr, int nc, int ns, int g, int gw, int64_t slab, const double* __restrict__ M,
+                    T* __restrict__ X) {
+  __shared__ double tile[64][65];
+  const int64_t b = blockIdx.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int c0 = 0; c0 < nr; c0 += 64) {
+    __syncthreads();  // the previous tile's readers are done
+    for (int v = wave; v < gw; v += 4)
+      tile[v][lane] = v < g && c0 + lane < nr ? M[v * slab + b * nr + c0 + lane] : 0.0;
     __syncthreads();
-    for (int q = 0; q < total; ++q) {
-      const float* Tb = Ts[q & 1];
-      const float* Bb = Bs[q & 1];
-#pragma unroll
-      for (int ks = 0; ks < KC; ks += 4) {
-        float a[RBW], bv[CBW];
-#pragma unroll
-        for (int i = 0; i < RBW; ++i) a[i] = Tb[(ks + lk) * TS + row0 + 16 * i + li];
-#pragma unroll
-        for (int j = 0; j < CBW; ++j) bv[j] = Bb[(ks + lk) * BSR + col0 + 16 * j + li];
-#pragma unroll
-        for (int i = 0; i < RBW; ++i)
-#pragma unroll
-          for (int j = 0; j < CBW; ++j)
-            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], bv[j], part[i][j], 0, 0, 0);
-      }
-      if ((q + 1) % nch == 0) {
-#pragma unroll
-        for (int i = 0; i < RBW; ++i)
-#pragma unroll
-          for (int j = 0; j < CBW; ++j) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const float x = part[i][j][v], a0 = acc[i][j][v], t = a0 + x;
-              cmp[i][j][v] += (fabsf(a0) >= fabsf(x)) ? (a0 - t) + x : (x - t) + a0;
-              acc[i][j][v] = t;
-            }
-            part[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-          }
-      }
-      if (q + 1 < total) {
-        // the other buffer was last read before the previous barrier
-        stash((q & 1) ^ 1);
-        if (q + 2 < total) load(q + 2);
-      }
-      __syncthreads();
+    if (lane >= gw) continue;
+    for (int c = c0 + wave; c < min(nr, c0 + 64); c += 4) {
+      int n, m;
+      bool im;
+      rsplit(c, &n, &m, &im);
+      T* x = X + ((b * nc + (m ? cidx(n - 1, m - 1) : ns + n)) * gw + lane) * 2;
+      x[im ? 1 : 0] = (T)tile[lane][c - c0];
+      if (m == 0) x[1] = (T)0;
     }
-    const double inv = sc[blevel[b]];
-#pragma unroll
-    for (int j = 0; j < CBW; ++j) {
-      const int col = col0 + 16 * j + li;
-      if (col >= g) continue;
-#pragma unroll
-      for (int i = 0; i < RBW; ++i)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = row0 + 16 * i + 4 * lk + v;
-          if (row < nr)
-            Lx[col * slab + (int64_t)b * nr + row] += ((double)acc[i][j][v] + (double)cmp[i][j][v]) * inv;
-        }
-    }
-    __syncthreads();  // LDS reuse by the next box
   }
 }
+
+// Batched M2L in operator frames (FP32 form; FP64 on its top levels): a block
+// takes one target box, or a run of its entries (items), and up to 64 vectors,
+// 16 a wave.  Entry by entry the wave turns the source's pairs (one azimuth for
+// all its vectors, rows of 16 vectors contiguous) into the operand fragments; the
+// operator goes through LDS as in m2l_frame_kernel, with the entry's phases.  Each
+// entry's product is turned back and added to FP64 totals by itself (products of
+// one azimuth added up in FP32 first: 15 % faster, but half again the error).  swizzle: each XCD takes a
+// contiguous range of the boxes, whose sources its L2 shares.
+// Bound by the operators' and sources' bytes out of the caches and, at two to three
+// waves a SIMD, their latency (matrix cores about 40 % busy): 604,000 pairs x 64
+// vectors at p = 10, 14.2 ms by the dense operators (box by box, FP32), 11.9 ms;
+// the FP64 top levels (42,708 pairs) 2.18 and 1.47 ms.  At three waves a SIMD
+// (batches of 2) 11.9 ms against 13.9 at two (batches of 4); XCD ranges do not pay
+// at this size (14.2 ms, they end unevenly) but stay among the tuner's choices.
+template <class T, int RC, int RS, int KB>
+__global__ void __launch_bounds__(256, sizeof(T) == 4 && KB == 2 && RC + RS <= 9 ? 3 : 2)
+m2l_frame_batch_kernel(int nr, int nc, int ns, int ne, int g, int gw, int64_t slab, int64_t nblk, int swizzle, XcdSplit xcd,
+                       const int32_t* __restrict__ boxes, const int32_t* __restrict__ items,
+                       const int32_t* __restrict__ bptr, int64_t box0, const int32_t* __restrict__ eop,
+                       const int32_t* __restrict__ ephi, const int32_t* __restrict__ esrc,
+                       const int32_t* __restrict__ ekind, const int32_t* __restrict__ dec, unsigned parts,
+                       const T* __restrict__ A, const T* __restrict__ X, const cplx* __restrict__ E,
+                       const int32_t* __restrict__ blevel, const double* __restrict__ sc, double* __restrict__ Lx,
+                       double* __restrict__ part) {
+  far_chain_priority();
+  constexpr int RT = 16 * (RC + RS);
+  constexpr int KV = 4 * RT * (int)sizeof(T) / 16;  // 16-byte vectors of a k-step of the operator
+  constexpr int PER = (KB * KV + 255) / 256;
+  using Acc = typename FrameTypes<T>::Acc;
+  typedef T Pair __attribute__((ext_vector_type(2)));
+  __shared__ intx4 As[2][KB * KV];
+  // phases of an entry's azimuth, entry e in row e mod 3: a wave may still turn entry
+  // e - 1 back while another stores those of e + 1
+  __shared__ cplx Es[3][kPMax + 1];
+  __shared__ int32_t ds[(kPMax + 1) * (kPMax + 2) / 2];
+  int64_t i = blockIdx.x;
+  if (swizzle) {
+    const int x = (int)(i & 7);
+    i = xcd.off[x] + (i >> 3);
+    if (i >= xcd.off[x + 1]) return;
+  } else if (i >= nblk) {
+    return;
+  }
+  const int b = boxes[items ? items[3 * i] : i];
+  const int e0 = items ? items[3 * i + 1] : bptr[b - box0], e1 = items ? items[3 * i + 2] : bptr[b - box0 + 1];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), vec = 16 * wave + li;
+  const bool work = 16 * wave < g;
+  const int kc = frame_ksteps(nc), ks = frame_ksteps(ns);
+  for (int j = tid; j < nc; j += 256) ds[j] = dec[j];
+  Acc ac[RC], as[RS];
+  double tc[RC][4], ts[RS][4];
+#pragma unroll
+  for (int r = 0; r < RC; ++r) {
+    ac[r] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tc[r][v] = 0.0;
+  }
+#pragma unroll
+  for (int r = 0; r < RS; ++r) {
+    as[r] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) ts[r][v] = 0.0;
+  }
+  intx4 va[PER];
+  cplx ev = cmk(0.0, 0.0);
+  auto load_a = [&](int e, int k0) {
+    const intx4* Ap = reinterpret_cast<const intx4*>(A) + ((int64_t)eop[e] * kc + k0) * KV;
+    const int n = min(KB, kc - k0) * KV;
+    if (k0 == 0 && tid < nc - ns) ev = E[(int64_t)ephi[e] * ne + tid];
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+      if (tid + 256 * r < n) va[r] = Ap[tid + 256 * r];
+  };
+  auto stash_a = [&](int buf, int e, int k0) {
+    if (k0 == 0 && tid < nc - ns) Es[e % 3][tid] = ev;
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+      if (tid + 256 * r < KB * KV) As[buf][tid + 256 * r] = va[r];
+  };
+  Pair x[KB];
+  auto load_b = [&](int e, int k0) {
+    const Pair* Xb = reinterpret_cast<const Pair*>(X) + (int64_t)esrc[e] * nc * gw + vec;
+#pragma unroll
+    for (int t = 0; t < KB; ++t) {
+      const int j = min(4 * (k0 + t) + lk, nc - 1);  // (columns from nc on are zero in A)
+      x[t] = Xb[j * gw];
+    }
+  };
+  // an entry's products turned back (e^{-i m phi}) into the totals
+  auto turn_back = [&](const cplx* Ee) {
+#pragma unroll
+    for (int r = 0; r < RC; ++r)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int j = min(16 * r + FrameTypes<T>::row(lk, v), nc - 1);  // (rows from nc on are dropped)
+        const cplx w = Ee[ds[j] >> 16];
+        const double c = (double)ac[r][v], s = r < RS ? (double)as[r < RS ? r : 0][v] : 0.0;
+        tc[r][v] += c * w.re + s * w.im;
+        if (r < RS) ts[r < RS ? r : 0][v] += s * w.re - c * w.im;
+        if (v & 1) __builtin_amdgcn_sched_barrier(0);  // (two phases in flight: registers)
+      }
+#pragma unroll
+    for (int r = 0; r < RC; ++r) ac[r] = Acc{0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < RS; ++r) as[r] = Acc{0, 0, 0, 0};
+  };
+  __syncthreads();  // ds
+  if (e0 < e1) {
+    load_a(e0, 0);
+    if (work) load_b(e0, 0);
+    stash_a(0, e0, 0);
+  }
+  __syncthreads();
+  int buf = 0;
+  for (int e = e0; e < e1; ++e) {
+    const bool on = (parts & (unsigned)ekind[e]) != 0;
+    for (int k0 = 0; k0 < kc; k0 += KB) {
+      const bool last = k0 + KB >= kc;
+      const bool more = !last || e + 1 < e1;
+      if (more) load_a(last ? e + 1 : e, last ? 0 : k0 + KB);
+      if (work) {
+        T a[KB], c[KB];
+#pragma unroll
+        for (int t = 0; t < KB; ++t) {
+          const int j = min(4 * (k0 + t) + lk, nc - 1);
+          const cplx v = Es[e % 3][ds[j] >> 16] * cmk((double)x[t].x, (double)x[t].y);
+          a[t] = on ? (T)v.re : (T)0;
+          c[t] = on ? (T)v.im : (T)0;
+        }
+        if (more) load_b(last ? e + 1 : e, last ? 0 : k0 + KB);
+        const T* Ab = reinterpret_cast<const T*>(As[buf]) + lk * RT + li;
+#pragma unroll
+        for (int t = 0; t < KB; ++t) {
+          if (k0 + t >= kc) break;
+#pragma unroll
+          for (int r = 0; r < RC; ++r) ac[r] = mfma4(Ab[4 * t * RT + 16 * r], a[t], ac[r]);
+          if (k0 + t < ks) {
+#pragma unroll
+            for (int r = 0; r < RS; ++r) as[r] = mfma4(Ab[4 * t * RT + 16 * (RC + r)], c[t], as[r]);
+          }
+        }
+      }
+      if (more) {
+        stash_a(buf ^ 1, last ? e + 1 : e, last ? 0 : k0 + KB);  // last read before the previous barrier
+        __syncthreads();
+        buf ^= 1;
+      }
+    }
+    if (work) turn_back(Es[e % 3]);
+  }
+  if (vec >= g) return;
+  const double inv = items ? 1.0 : sc[blevel[b]];
+  double* o = items ? part + (i * 64 + vec) * nr : Lx + vec * slab + (int64_t)b * nr;
+#pragma unroll
+  for (int r = 0; r < RC; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int j = 16 * r + FrameTypes<T>::row(lk, v);
+      if (j >= nc) continue;
+      const int d = ds[j], off = d & 0xffff;
+      if (items) {
+        o[off] = tc[r][v];
+        if (d >> 16) o[off + 1] = r < RS ? ts[r < RS ? r : 0][v] : 0.0;
+      } else {
+        o[off] += tc[r][v] * inv;
+        if (d >> 16) o[off + 1] += (r < RS ? ts[r < RS ? r : 0][v] : 0.0) * inv;
+      }
+    }
+}
+
 
 // Batched gather and combine through point-major copies, so that every global
 // access is coalesced: tiles of 64 points x 64 vectors go through LDS.
@@ -1548,22 +1578,6 @@ p2p_reaction_batch_kernel(int g, const int32_t* __restrict__ leaves, const int32
 __global__ void zero_kernel(double* __restrict__ a, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) a[i] = 0.0;
-}
-
-// FP32 copy of per-box rows of nr values into rows of nrk (zero past nr)
-__global__ void to_f32_pad_kernel(const double* __restrict__ a, int64_t nb, int nr, int nrk, float* __restrict__ b) {
-  far_chain_priority();
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nb * nrk) return;
-  const int64_t box = i / nrk;
-  const int k = (int)(i - box * nrk);
-  b[i] = k < nr ? (float)a[box * nr + k] : 0.f;
-}
-
-__global__ void to_f32_kernel(const double* __restrict__ a, int64_t n, float* __restrict__ b) {
-  far_chain_priority();
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = (float)a[i];
 }
 
 // x = hi + lo with hi = (float)x and lo = (float)(x - hi)
@@ -2429,8 +2443,6 @@ int gpu_expand_pairs(fmmlm_plan_s* P, const std::vector<int32_t>& tgt0, const st
 }
 
 int gpu_build_fp32(fmmlm_plan_s* P, hipStream_t st) {
-  const int64_t nt = P->nops * (int64_t)P->nrk * (32 * P->mrt);
-  if (nt > 0 && P->Tfree32) to_f32_kernel<<<(unsigned)((nt + 255) / 256), 256, 0, st>>>(P->Tfree, nt, P->Tfree32);
   const unsigned nb = (unsigned)((P->NP + 255) / 256);
   split_f32_kernel<<<nb, 256, 0, st>>>(P->px, P->NP, P->pxh, P->pxl);
   split_f32_kernel<<<nb, 256, 0, st>>>(P->py, P->NP, P->pyh, P->pyl);
@@ -2495,9 +2507,12 @@ template <class T>
 int launch_frame_reduce(const fmmlm_plan_s* P, const M2LUnits& U, double* Lx, hipStream_t st) {
   if (U.nboxes <= 0) return FMMLM_OK;
   const FrameRows r = frame_rows(P->p);
-  m2l_frame_reduce_kernel<T><<<(unsigned)U.nboxes, kFrRedThreads, 0, st>>>(
-      (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.boxes, U.ptr, U.slots, U.slot_phi, P->pair_dec, P->blevel,
-      P->sc_levels, static_cast<const T*>(U.W), reinterpret_cast<const cplx*>(P->E), Lx);
+#define FRR(NT)                                                                                               \
+  m2l_frame_reduce_kernel<T, NT><<<(unsigned)U.nboxes, NT, 0, st>>>(                                          \
+      (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.boxes, U.ptr, U.slots, U.slot_phi,         \
+      P->pair_dec, P->blevel, P->sc_levels, static_cast<const T*>(U.W), reinterpret_cast<const cplx*>(P->E), Lx)
+  FRR(256);
+#undef FRR
   FMM_HIP_TRY(hipGetLastError());
   return FMMLM_OK;
 }
@@ -2636,61 +2651,56 @@ int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st) {
   return rc;
 }
 
-// Batched FP32 M2L over the boxes [bbox_split, nbbox) for g vectors, in one of
-// the tile shapes over (operator rows x 64 vectors), outputs per wave:
-// shape 0: 4 waves of 64 x 32, 1: 8 of 32 x 32, 2: 8 of 64 x 16, 3: 16 of
-// 32 x 16, 4: 16 of 16 x 32 ((p+1)^2 <= 128; one shape otherwise).  Variant v
-// uses shape v % kBatchShapes, as one block per box (v < kBatchShapes) or as a
-// persistent XCD-aware grid of resident blocks.
+// Batched M2L in operator frames over n boxes (or items) of one precision.
+// Variant v: operator batches of 4, 2 or 8 k-steps, or of 4 or 2 with LDS reserved
+// so that two blocks fit a CU (v % kBatchShapes), boxes in XCD-contiguous order
+// (v < kBatchShapes) or as they come.
 int batch_variants(const fmmlm_plan_s* P) { return P->mrt == 4 ? 2 * kBatchShapes : 2; }
 
-template <int RBW, int CBW, int WR, int NW, bool PS, int KC>
-int launch_batch32_shape(const fmmlm_plan_s* P, int g, int64_t n, unsigned parts, hipStream_t st) {
-  const int nr = (P->p + 1) * (P->p + 1);
-  int64_t grid = n;
-  if (PS) {
-    int per_cu = 0, ncu = 0, dev = 0;
-    FMM_HIP_TRY(hipGetDevice(&dev));
-    FMM_HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    FMM_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, reinterpret_cast<const void*>(&m2l_batch32_kernel<RBW, CBW, WR, NW, PS, KC>), 64 * NW, 0));
-    grid = std::max<int64_t>(8, (int64_t)std::max(per_cu, 1) * ncu / 8 * 8);
-    grid = std::min<int64_t>(grid, (n + 7) / 8 * 8);
+template <class T, int KB>
+int launch_frame_batch_kb(const fmmlm_plan_s* P, const M2LUnits& U, int g, int64_t n, const int32_t* boxes,
+                          const int32_t* items, bool swizzle, size_t reserve, unsigned parts, const T* X,
+                          double* part, hipStream_t st) {
+  const FrameRows r = frame_rows(P->p);
+  const int64_t slab = P->NB * (int64_t)(P->p + 1) * (P->p + 1);
+  const unsigned nb = (unsigned)(swizzle ? 8 * (int64_t)P->bbox_xcd_len : n);
+#define FB(RC, RS)                                                                                              \
+  if (r.rc == RC && r.rs == RS) {                                                                               \
+    const size_t used = (size_t)(2 * KB * 4 * 16 * (RC + RS)) * sizeof(T) + 1024;                               \
+    m2l_frame_batch_kernel<T, RC, RS, KB><<<nb, 256, reserve > used ? reserve - used : 0, st>>>(                \
+        (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, g, P->gw, slab, n, swizzle ? 1 : 0, P->bbox_xcd, boxes, items, \
+        U.bptr, U.box0, U.be_op, U.be_phi, U.be_src, U.be_kind, P->pair_dec, parts,                             \
+        static_cast<const T*>(U.A), X, reinterpret_cast<const cplx*>(P->E), P->blevel, P->sc_levels, P->Lx,     \
+        part);                                                                                                  \
+    FMM_HIP_TRY(hipGetLastError());                                                                             \
+    return FMMLM_OK;                                                                                            \
   }
-  m2l_batch32_kernel<RBW, CBW, WR, NW, PS, KC><<<(unsigned)grid, 64 * NW, 0, st>>>(
-      nr, P->nrk, g, P->NB, P->bbox, P->bbox_split, n, P->m2l_ptr, P->m2l_src, P->m2l_op, (int)P->n_free_ops,
-      parts, P->blevel, P->sc_levels, P->Tfree32, P->M32, P->Lx);
-  FMM_HIP_TRY(hipGetLastError());
-  return FMMLM_OK;
+  if constexpr (KB == 2 || sizeof(T) == 4) {
+    FB(5, 4)
+  }
+  if constexpr (KB == (sizeof(T) == 8 ? 2 : 4)) {  // p = 1..16
+    FB(1, 1) FB(2, 1) FB(2, 2) FB(3, 2) FB(3, 3) FB(4, 3) FB(5, 5) FB(6, 5) FB(7, 6)
+  }
+  if constexpr (KB == 2) {
+    FB(8, 7) FB(9, 8) FB(10, 9)
+  }
+#undef FB
+  return FMMLM_EUNSUPPORTED;
 }
 
 int launch_batch32(const fmmlm_plan_s* P, int variant, int g, int64_t n, unsigned parts, hipStream_t st) {
   if (n <= 0) return FMMLM_OK;
-  const bool ps = variant >= (P->mrt == 4 ? kBatchShapes : 1);
-  const int shape = variant % (P->mrt == 4 ? kBatchShapes : 1);
-  // slices of 32 operator columns where the padded column count allows
-  const bool k32 = P->nrk % 32 == 0;
-#define BS(RBW, CBW, WR, NW)                                                                                  \
-  return k32 ? (ps ? launch_batch32_shape<RBW, CBW, WR, NW, true, 32>(P, g, n, parts, st)                    \
-                   : launch_batch32_shape<RBW, CBW, WR, NW, false, 32>(P, g, n, parts, st))                  \
-             : (ps ? launch_batch32_shape<RBW, CBW, WR, NW, true, 16>(P, g, n, parts, st)                    \
-                   : launch_batch32_shape<RBW, CBW, WR, NW, false, 16>(P, g, n, parts, st))
-  switch (P->mrt) {
-    case 2: BS(2, 2, 2, 4);
-    case 4:
-      switch (shape) {
-        case 1: BS(2, 2, 4, 8);
-        case 2: BS(4, 1, 2, 8);
-        case 3: BS(2, 1, 4, 16);
-        case 4: BS(1, 2, 8, 16);
-        default: BS(4, 2, 2, 4);
-      }
-    case 6: BS(6, 2, 2, 4);
-    case 8: BS(8, 2, 2, 4);
-    case 10: BS(10, 2, 2, 4);
-    default: return FMMLM_EUNSUPPORTED;
-  }
-#undef BS
+  const int nv = P->mrt == 4 ? kBatchShapes : 1;
+  const bool sw = variant < nv;
+  const int32_t* bx = P->bbox + P->bbox_split;
+  const int shape = variant % nv;
+  const size_t reserve = shape >= 3 ? 61440 : 0;
+  if (P->p > 13) return launch_frame_batch_kb<float, 2>(P, P->u32, g, n, bx, nullptr, sw, 0, parts, P->M32, nullptr, st);
+  if (P->p == 10 && (shape == 1 || shape == 4))
+    return launch_frame_batch_kb<float, 2>(P, P->u32, g, n, bx, nullptr, sw, reserve, parts, P->M32, nullptr, st);
+  if (P->p == 10 && shape == 2)
+    return launch_frame_batch_kb<float, 8>(P, P->u32, g, n, bx, nullptr, sw, 0, parts, P->M32, nullptr, st);
+  return launch_frame_batch_kb<float, 4>(P, P->u32, g, n, bx, nullptr, sw, reserve, parts, P->M32, nullptr, st);
 }
 
 // Autotuner of the batched FP32 M2L: each variant runs the plan's boxes for
@@ -2702,7 +2712,7 @@ int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st) {
   const int nv = batch_variants(P);
   if (!P->fp32 || P->gmax < 2 || n32 <= 0) return FMMLM_OK;
   const int64_t nr = (int64_t)(P->p + 1) * (P->p + 1);
-  FMM_HIP_TRY(hipMemsetAsync(P->M32, 0, (size_t)P->NB * P->nrk * P->gmax * sizeof(float), st));
+  FMM_HIP_TRY(hipMemsetAsync(P->M32, 0, (size_t)P->NB * P->nc * P->gw * 2 * sizeof(float), st));
   hipEvent_t e0, e1;
   FMM_HIP_TRY(hipEventCreate(&e0));
   FMM_HIP_TRY(hipEventCreate(&e1));
@@ -2829,35 +2839,33 @@ int gpu_eval_batch(fmmlm_plan_s* P, int g, const double* q, int64_t ldq, double*
     const int64_t nl = slab * g;
     zero_kernel<<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(P->Lx, nl);
     const int64_t n64 = f32 ? P->bbox_split : P->nbbox;
+    const int64_t n32 = f32 ? P->nbbox - P->bbox_split : 0;
     if (!f32) mark();  // the FP64 form has one M2L launch over every level
-    if (n64 > 0) {
-      // the FP32 form's FP64 top levels as work items (few boxes, long entry
-      // lists), then a reduction per box; the FP64 form one block per box
-      const bool it = f32 && P->n_btop_items > 0;
-      const unsigned nblk = (unsigned)(it ? P->n_btop_items : n64);
+    if (f32 && P->ntop > 0 && n64 > 0) {
+      // the FP64 top levels as work items (few boxes, long entry lists), then a
+      // reduction per box
+      vector_minor_kernel<<<(unsigned)P->ntop, 256, 0, st>>>(nr, nc, nc - p - 1, g, P->gw, slab, P->M, P->M64);
+      if (int rc = launch_frame_batch_kb<double, 2>(P, P->u64, g, P->n_btop_items, P->bbox, P->btop_items, false, 0,
+                                                    parts, P->M64, P->Pbtop, st))
+        return rc;
+      m2l_btop_reduce_kernel<<<(unsigned)n64, 256, 0, st>>>(nr, g, P->bbox, P->btop_iptr, P->Pbtop, P->blevel,
+                                                            P->sc_levels, slab, P->Lx);
+    } else if (n64 > 0) {
       switch (P->mrt) {
 #define B64(R)                                                                                               \
   case R:                                                                                                    \
-    m2l_batch64_kernel<R><<<nblk, 256, 0, st>>>(nr, P->nrk, g, P->NB, P->bbox, 0, P->m2l_ptr, P->m2l_src,   \
-                                                P->m2l_op, (int)P->n_free_ops, parts, P->blevel, P->sc_levels, \
-                                                P->Tfree, P->M, P->Lx, it ? P->btop_items : nullptr,       \
-                                                it ? P->Pbtop : nullptr);                                   \
+    m2l_batch64_kernel<R><<<(unsigned)n64, 256, 0, st>>>(nr, P->nrk, g, P->NB, P->bbox, 0, P->m2l_ptr,       \
+                                                         P->m2l_src, P->m2l_op, (int)P->n_free_ops, parts,   \
+                                                         P->blevel, P->sc_levels, P->Tfree, P->M, P->Lx);    \
     break;
         B64(2) B64(4) B64(6) B64(8) B64(10)
 #undef B64
         default:
           return FMMLM_EUNSUPPORTED;
       }
-      if (it)
-        m2l_btop_reduce_kernel<<<(unsigned)n64, 256, 0, st>>>(nr, g, P->bbox, P->btop_iptr, P->Pbtop, P->blevel,
-                                                              P->sc_levels, slab, P->Lx);
     }
-    const int64_t n32 = f32 ? P->nbbox - P->bbox_split : 0;
-    if (f32 && n32 > 0) {
-      const int64_t nm = P->NB * (int64_t)g * P->nrk;
-      to_f32_pad_kernel<<<(unsigned)((nm + 255) / 256), 256, 0, st>>>(P->M, P->NB * (int64_t)g, nr, P->nrk,
-                                                                     P->M32);
-    }
+    if (n32 > 0)
+      vector_minor_kernel<<<(unsigned)P->NB, 256, 0, st>>>(nr, nc, nc - p - 1, g, P->gw, slab, P->M, P->M32);
     if (f32) mark();
     if (n32 > 0) {
       if (int rc = launch_batch32(P, P->batch_variant, g, n32, parts, st)) return rc;

@@ -107,6 +107,11 @@ struct GraphKey {
            st == o.st;
   }
 };
+// block ranges per XCD of a launch (the 8 XCDs take blocks in turn): XCD x runs
+// blocks [off[x], off[x + 1]), ranges of about equal work
+struct XcdSplit {
+  int32_t off[9];
+};
 // Units of the M2L in operator frames, all in one precision: a unit is `cols`
 // columns (a target box, an azimuth, and per step a source box) that share the
 // steps' operators; column c of unit u is slot u cols + c, whose product the
@@ -125,6 +130,10 @@ struct M2LUnits {
   int32_t *frame_op = nullptr;  // [nops] operator of G
   void *A = nullptr;            // [nops] frame operators in the kernel's layout (double or float)
   void *W = nullptr;            // [n cols][nrk] products (rows of c, then of s)
+  // batched plans: entries of every target box by (azimuth, operator), CSR over
+  // the boxes [box0, box0 + ...)
+  int64_t box0 = 0;
+  int32_t *bptr = nullptr, *be_op = nullptr, *be_phi = nullptr, *be_src = nullptr, *be_kind = nullptr;
 };
 }  // namespace fmmlm
 
@@ -172,10 +181,10 @@ struct fmmlm_plan_s {
   int ngs = 0;                     // stride of G (even)
   double* E = nullptr;             // azimuths: e^{i k phi}, k <= 2p [n_phi][2p + 1] complex
   int64_t n_phi = 0;
-  int32_t *op_frame = nullptr, *op_phi = nullptr;  // [nops] (batched plans: the dense operators' build)
+  int32_t *op_frame = nullptr, *op_phi = nullptr;  // [nops] (batched FP64 form: the dense operators' build)
   int32_t *pair_dec = nullptr;     // [nc] pair j: offset in the real layout | order << 16 (orders >= 1 first)
   fmmlm::M2LUnits u64, u32;               // FP64 form: u64 all levels; FP32 form: u64 top levels, u32 the rest
-  double* Tfree = nullptr;         // batched plans: [nops][nrk][32 mrt] real-form operators (free space, then reaction)
+  double* Tfree = nullptr;         // batched FP64 form: [nops][nrk][32 mrt] real-form operators (free space, then reaction)
   int nrk = 0, mrt = 0;            // padded inner dimension, padded rows / 32
   int m2l_variant = 0;             // FP32 M2L launch variant picked by the autotuner
   int batch_variant = 0;           // batched FP32 M2L shape / persistence picked by the autotuner
@@ -190,8 +199,10 @@ struct fmmlm_plan_s {
   int xl_tile_cols = 32;           // target boxes per translation tile
   // FP32 form
   bool fp32 = false;
-  float* Tfree32 = nullptr;        // batched FP32 form: FP32 copy of Tfree
-  float* M32 = nullptr;            // batched FP32 form: FP32 copy of the multipole expansions (GEMM operand)
+  float* M32 = nullptr;            // batched FP32 form: expansions [NB][nc][gw] (re, im) in FP32 ...
+  double* M64 = nullptr;           //   ... and the top levels' in FP64
+  int gw = 16;                     // vectors of a row (a multiple of 16)
+  int64_t ntop = 0;                // boxes of the FP64 top levels (they come first)
   float *pxh = nullptr, *pxl = nullptr, *pyh = nullptr, *pyl = nullptr, *phh = nullptr, *phl = nullptr;
   float* qt32 = nullptr;
   // batched form (opts.max_rhs > 1): expansions, charges and potentials of up
@@ -199,6 +210,8 @@ struct fmmlm_plan_s {
   int gmax = 1;
   int batch_min = 2;               // batched passes narrower than this run vector by vector
   int64_t nbbox = 0, bbox_split = 0;
+  fmmlm::XcdSplit bbox_xcd{};      // FP32 form: the boxes [bbox_split, nbbox) per XCD ...
+  int32_t bbox_xcd_len = 0;        //   ... and the longest range
   int32_t* bbox = nullptr;         // target boxes with M2L entries, level order
   // batched M2M / L2L through the batched FP64 GEMM: per box CSR of its
   // translation entries (M2M: children, operator = octant; L2L: the parent,
