@@ -2511,7 +2511,13 @@ int launch_frame_reduce(const fmmlm_plan_s* P, const M2LUnits& U, double* Lx, hi
   m2l_frame_reduce_kernel<T, NT><<<(unsigned)U.nboxes, NT, 0, st>>>(                                          \
       (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.boxes, U.ptr, U.slots, U.slot_phi,         \
       P->pair_dec, P->blevel, P->sc_levels, static_cast<const T*>(U.W), reinterpret_cast<const cplx*>(P->E), Lx)
-  FRR(256);
+  // few boxes (long slot lists, top levels): twice the groups a box.  20,011
+  // charges 187 -> 180 us, GMRES solve 11.4 -> 11.2 ms; 1,024 threads no better
+  if (U.nboxes < 2048) {
+    FRR(512);
+  } else {
+    FRR(256);
+  }
 #undef FRR
   FMM_HIP_TRY(hipGetLastError());
   return FMMLM_OK;
