@@ -946,7 +946,7 @@ m2l_frame_reduce_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* _
 // k runs in order, so the products do not depend on the batch size.
 // UP (M2M): block (tile, rb, cb), wave w = the tile's unit w (one per child
 // octant present, at most 8); the units' blocks meet in LDS and are added in
-// unit order, as m2l_reduce_kernel adds them, into the parents' expansions.
+// unit order into the parents' expansions.
 // L2L: block (unit, group of 8 row blocks, cb), wave w = row block 8 y + w; a
 // level's tiles hold each child once, so each wave adds its block directly.
 constexpr int kXlDirectKB = 4;  // k-steps (of 4) a load batch
@@ -1591,63 +1591,86 @@ __global__ void split_f32_kernel(const double* __restrict__ a, int64_t n, float*
 }
 
 
-// L2P: one block per leaf, one thread per particle (strided).
-__global__ void l2p_kernel(int p, int nc, const int32_t* __restrict__ leaves,
-                           const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
-                           const int32_t* __restrict__ blevel, const double* __restrict__ bcx,
-                           const double* __restrict__ bcy, const double* __restrict__ bch,
-                           const double* __restrict__ sc, const double* __restrict__ px,
-                           const double* __restrict__ py, const double* __restrict__ ph,
-                           const double* __restrict__ Lx, const double* __restrict__ coefR,
-                           double* __restrict__ phit, int64_t lstride = 0, int64_t pstride = 0) {
+// Batched L2P: one block per leaf, 16 vectors a wave.  A chunk of points' harmonics
+// (with the weight 2 of orders m > 0, signs of the real layout) go to LDS once for
+// all vectors, and the FP64 matrix cores multiply them with the leaf's local
+// expansions, which each wave holds in its fragments: D [vector][point], so that
+// 16 consecutive points of a vector leave together.  A block per leaf and vector
+// computed the harmonics 64 times over: 1.06 ms at 131,072 charges, p = 10, 64
+// vectors; now 0.22 ms.  KN: k-steps the fragments hold.
+template <int KN>
+__global__ void __launch_bounds__(256)
+l2p_batch_kernel(int p, int g, const int32_t* __restrict__ leaves, const int32_t* __restrict__ bstart,
+                 const int32_t* __restrict__ bcount, const int32_t* __restrict__ blevel,
+                 const double* __restrict__ bcx, const double* __restrict__ bcy, const double* __restrict__ bch,
+                 const double* __restrict__ sc, const double* __restrict__ px, const double* __restrict__ py,
+                 const double* __restrict__ ph, const double* __restrict__ Lx, const double* __restrict__ coefR,
+                 double* __restrict__ phit, int64_t lstride, int64_t pstride) {
   far_chain_priority();
-  extern __shared__ char smem[];
-  Lx += blockIdx.y * lstride;
-  phit += blockIdx.y * pstride;
-  cplx* Ls = reinterpret_cast<cplx*>(smem);
+  extern __shared__ double w[];  // [PT][ld]
+  constexpr int PT = KN <= 31 ? 32 : 16;
+  const int np1 = p + 1, nr = np1 * np1, nks = (nr + 3) / 4, ld = 4 * nks + 1;
   const int b = leaves[blockIdx.x];
-  for (int i = threadIdx.x; i < nc; i += blockDim.x) {
-    const int nn = isqrt_row(i), mm = i - cidx(nn, 0);
-    Ls[i] = rload(Lx + (int64_t)b * (p + 1) * (p + 1), nn, mm);
-  }
-  __syncthreads();
   const double inv = sc[blevel[b]];
   const double cx = bcx[b], cy = bcy[b], ch = bch[b];
   const int s0 = bstart[b], cnt = bcount[b];
-  for (int j = threadIdx.x; j < cnt; j += blockDim.x) {
-    const int g = s0 + j;
-    const double x = (px[g] - cx) * inv, y = (py[g] - cy) * inv, z = (ph[g] - ch) * inv;
-    const double r2 = x * x + y * y + z * z;
-    const cplx w = cmk(x, y);
-    const int ncp = ncoef(p);
-    cplx Rmm = cmk(0.28209479177387814, 0.0);
-    double acc = 0.0;
-    for (int m = 0; m <= p; ++m) {
-      if (m > 0) Rmm = coefR[2 * ncp + m] * (w * Rmm);
-      const double wgt = (m == 0) ? 1.0 : 2.0;
-      cplx Rm2 = Rmm;
-      cplx L = Ls[cidx(m, m)];
-      acc += wgt * (L.re * Rmm.re - L.im * Rmm.im);
-      if (m + 1 > p) continue;
-      cplx Rm1 = (coefR[2 * ncp + p + 1 + m] * z) * Rmm;
-      L = Ls[cidx(m + 1, m)];
-      acc += wgt * (L.re * Rm1.re - L.im * Rm1.im);
-      for (int n = m + 2; n <= p; ++n) {
-        const double a = coefR[cidx(n, m)], bb = coefR[ncp + cidx(n, m)];
-        const cplx Rn = a * (z * Rm1 - (bb * r2) * Rm2);
-        L = Ls[cidx(n, m)];
-        acc += wgt * (L.re * Rn.re - L.im * Rn.im);
-        Rm2 = Rm1;
-        Rm1 = Rn;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
+  const int ncp = ncoef(p);
+  double a[KN];
+#pragma unroll
+  for (int ks = 0; ks < KN; ++ks) {
+    const int vec = 16 * wave + li, k = 4 * ks + lk;
+    a[ks] = vec < g && k < nr ? Lx[vec * lstride + (int64_t)b * nr + k] : 0.0;
+  }
+  for (int i = tid; i < PT * (ld - nr); i += 256) w[i / (ld - nr) * ld + nr + i % (ld - nr)] = 0.0;
+  for (int c0 = 0; c0 < cnt; c0 += PT) {
+    const int np = min(PT, cnt - c0);
+    __syncthreads();  // the previous chunk is consumed
+    for (int i = tid; i < PT * np1; i += 256) {
+      const int j = i / np1, m = i % np1;
+      double* wj = w + j * ld;
+      const int gp = s0 + c0 + min(j, np - 1);  // (rows past the last point are not stored)
+      const double x = (px[gp] - cx) * inv, y = (py[gp] - cy) * inv, z = (ph[gp] - ch) * inv;
+      const double r2 = x * x + y * y + z * z;
+      cplx Rmm = cmk(0.28209479177387814, 0.0);
+      for (int mm = 1; mm <= m; ++mm) Rmm = coefR[2 * ncp + mm] * (cmk(x, y) * Rmm);
+      cplx Rm2 = cmk(0.0, 0.0), Rm1 = Rmm;
+      for (int n = m; n <= p; ++n) {
+        if (n > m) {
+          const cplx Rn = n == m + 1 ? (coefR[2 * ncp + np1 + m] * z) * Rmm
+                                     : coefR[cidx(n, m)] * (z * Rm1 - (coefR[ncp + cidx(n, m)] * r2) * Rm2);
+          Rm2 = Rm1;
+          Rm1 = Rn;
+        }
+        if (m == 0) {
+          wj[n * n] = Rm1.re;
+        } else {
+          wj[n * n + 2 * m - 1] = 2.0 * Rm1.re;
+          wj[n * n + 2 * m] = -2.0 * Rm1.im;
+        }
       }
     }
-    phit[g] = acc;
+    __syncthreads();
+    if (16 * wave >= g) continue;
+    for (int p0 = 0; p0 < np; p0 += 16) {
+      doublex4 acc = {0.0, 0.0, 0.0, 0.0};
+      const double* wp = w + (p0 + li) * ld + lk;
+#pragma unroll
+      for (int ks = 0; ks < KN; ++ks)
+        if (ks < nks) acc = mfma4(a[ks], wp[4 * ks], acc);
+      if (p0 + li < np)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int vec = 16 * wave + lk + 4 * v;
+          if (vec < g) phit[vec * pstride + s0 + c0 + p0 + li] = acc[v];
+        }
+    }
   }
 }
 
 // L2P of the single-vector evaluation with the order P fixed at compile time,
 // so the recurrence over (n, m) unrolls and its coefficients become scalar
-// loads at fixed offsets: the same harmonics and sum as l2p_kernel, with the
+// loads at fixed offsets: the same harmonics and sum as the batched form's, with the
 // weight 2 of the m > 0 terms folded into the local expansion in LDS.
 template <int P>
 __global__ void __launch_bounds__(64)
@@ -2885,9 +2908,17 @@ int gpu_eval_batch(fmmlm_plan_s* P, int g, const double* q, int64_t ldq, double*
                                        P->bd_src, P->bd_op, P->Txl, P->Lx, P->Lx, st))
         return rc;
   mark();
-  l2p_kernel<<<dim3((unsigned)P->nleaves, (unsigned)g), 64, nc * sizeof(cplx), st>>>(
-      p, nc, P->leaves, P->bstart, P->bcount, P->blevel, P->bcx, P->bcy, P->bch, P->sc_levels, P->px, P->py, P->ph,
-      P->Lx, P->coefR, P->phit, slab, P->NP);
+  {
+    const int nks = (nr + 3) / 4;
+#define L2PB(KN)                                                                                             \
+  if (nks <= KN) {                                                                                           \
+    l2p_batch_kernel<KN><<<(unsigned)P->nleaves, 256, (size_t)(KN <= 31 ? 32 : 16) * (4 * nks + 1) * 8, st>>>( \
+        p, g, P->leaves, P->bstart, P->bcount, P->blevel, P->bcx, P->bcy, P->bch, P->sc_levels, P->px, P->py, \
+        P->ph, P->Lx, P->coefR, P->phit, slab, P->NP);                                                       \
+  } else
+    L2PB(9) L2PB(21) L2PB(31) L2PB(43) L2PB(73) return FMMLM_EUNSUPPORTED;
+#undef L2PB
+  }
   mark();
   if ((parts & FMMLM_FREE) && f32 && P->n_pl_leaves > 0) {
     p2p_batch32_kernel<<<(unsigned)P->n_pl_leaves, 256, 0, st>>>(
