@@ -26,13 +26,13 @@ if ROOT not in sys.path:
 METRIC = "FMM matvecs/sec at N=1M 3-layer p=10 vs plain FP64 GPU FMM at <=1e-5 rel error"
 # PMC summaries of HBM traffic per stage's kernel (see measured_traffic)
 TRAFFIC_FILES = {
-    "m2l": os.path.join(ROOT, "profiles", "m2l_mfma32_3layer_N1048576_p10_traffic.md"),
+    "m2l": os.path.join(ROOT, "profiles", "m2l_frame_3layer_N1048576_p10_traffic.md"),
     "p2p_free": os.path.join(ROOT, "profiles", "p2p_mutual_3layer_N1048576_p10_traffic.md"),
-    "m2l_batch": os.path.join(ROOT, "profiles", "m2l_batch32_4layer_N524288_p10_rhs64_traffic.md"),
+    "m2l_batch": os.path.join(ROOT, "profiles", "m2l_frame_batch_4layer_N524288_p10_rhs64_traffic.md"),
 }
 KERNEL_SRC = os.path.join(ROOT, "paper_1908_10863_amd", "csrc", "fmm.hip")
 # kernel that carries each stage of the FP32 form (one launch per evaluation)
-STAGE_KERNEL = {"m2l": "m2l_mfma32_kernel", "p2p_free": "p2p_mutual_kernel<float> + p2p_combine_kernel<float>"}
+STAGE_KERNEL = {"m2l": "m2l_frame_kernel<float>", "p2p_free": "p2p_mutual_kernel<float> + p2p_combine_kernel<float>"}
 CALIB_BYTES = 256 << 20  # plain device-to-device copy that scales the PMC byte counters
 PEAK_FP64 = 78.6e12  # MI355X FP64, vector and dense matrix (published), FLOP/s
 PEAK_FP32 = 157.3e12  # MI355X FP32, vector and dense matrix (published), FLOP/s
@@ -53,18 +53,20 @@ ISSUE_CEILING = {"p2p_free": VALU_LANE_RATE / P2P_INSTR_PER_PAIR * P2P_FLOPS_PER
 
 def stage_flops(stats, p, stage, rhs=1):
     """Algorithmic floating-point work of one evaluation of a stage over `rhs` charge vectors:
-    the dense real-form operator counts (p+1)^2 x (p+1)^2 multiply-adds per box pair and vector."""
+    an M2L counts the multiply-adds of its operator turned to its azimuth, nc^2 + ns^2 per box pair
+    and vector (nc = (p+1)(p+2)/2 real parts, ns = p(p+1)/2 imaginary parts)."""
     return rhs * _stage_flops1(stats, p, stage)
 
 
 def _stage_flops1(stats, p, stage):
     full = (p + 1) ** 2
     pairs = stats["m2l_free_pairs"] + stats["m2l_reaction_pairs"]
+    turned = ((p + 1) * (p + 2) // 2) ** 2 + (p * (p + 1) // 2) ** 2
     if stage == "m2l":
-        # the main M2L GEMM launch: every pair below the levels kept in FP64
-        return 2.0 * full * full * (pairs - stats["m2l_top_pairs"])
+        # the main M2L launch: every pair below the levels the FP32 form keeps in FP64
+        return 2.0 * turned * (pairs - stats["m2l_top_pairs"])
     if stage == "m2l_top":
-        return 2.0 * full * full * stats["m2l_top_pairs"]
+        return 2.0 * turned * stats["m2l_top_pairs"]
     if stage == "p2p_free":
         return float(P2P_FLOPS_PER_PAIR) * stats["p2p_free_pairs"]
     if stage == "p2p_reaction":
@@ -243,7 +245,7 @@ def _batched_form(fmmlm, workloads, oracle, dev, steps):
     bst = b["stats"]
     dom = "m2l"
     roof = stage_roofline(bst, 10, dom, b["stages"][dom], True, 64)
-    roof["kernel"] = "m2l_batch32_kernel"
+    roof["kernel"] = "m2l_frame_batch_kernel<float>"
     roof["traffic"] = measured_traffic("m2l_batch")
     res["batched"] = {"workload": w4["name"], "rhs": 64, "value": b["value"], "unit": "matvec/s",
                       "ms_per_pass": b["ms"], "leaf_cap": 128, "mac_d2": 4,

@@ -64,7 +64,7 @@ typedef struct fmmlm_surrogate_s* fmmlm_surrogate_t;
 typedef struct {
   int32_t leaf_cap;        /* a box is split while it holds more points (default 64) */
   int32_t precision;       /* FMMLM_FP64 (default) or FMMLM_FP32_COMPENSATED */
-  int32_t fp64_top_levels; /* tree levels 0..k-1 whose M2L runs in the sparse FP64 kernel
+  int32_t fp64_top_levels; /* tree levels 0..k-1 whose M2L the FP32 form runs in FP64
                               (default 3); the FP32 form keeps these levels in FP64 */
   int32_t max_rhs;         /* largest nrhs accepted by eval (default 1).  Above 1 the plan
                               holds expansions for G = min(max_rhs, 64) charge vectors and
@@ -269,31 +269,28 @@ typedef struct {
                                     |difference of S^N I_{N,M}|, R1 = |(rho, z + zinf)| (the error
                                     relative to the interaction 1/R1 that the operator carries).
                                     Above 1e-5 the plan rejects the form (surrogate_rejected) */
-  int64_t m2l_steps;           /* M2L GEMM steps (one operator applied to one chunk's sources) ... */
+  int64_t m2l_steps;           /* M2L steps (one operator applied to one unit's sources) ... */
   int32_t m2l_tile_cols;       /*   ... of this many target columns: the fill of the steps is
                                     (m2l_free_pairs + m2l_reaction_pairs - m2l_top_pairs)
                                     / (steps * cols) */
-  int32_t m2l_variant;         /* FP32 form: M2L tile shape picked by the plan's autotuner (see m2l_eval_ms) */
-  int64_t m2l_top_pairs;       /* M2L pairs on the top levels (fp64_top_levels), run by the
-                                    sparse FP64 kernel in the "M2L top" stage */
-  double m2l_variant_ms[6];    /* autotuner: time of one M2L launch alone in each tile shape (outputs
-                                  per wave, rows x columns, operator columns per LDS slice; 0: 16
-                                  waves of 32 x 32, slices of 32; 1: 8 of 32 x 64; 2: 8 of 64 x 32;
-                                  3: 16 of 32 x 32; 4: 16 of 64 x 16; 5: 16 of 64 x 16, slices of
-                                  32; slices of 16 otherwise, and where the padded column count is
-                                  not a multiple of 32; (p+1)^2 <= 128 only, else unused) */
+  int32_t m2l_variant;         /* FP32 form: M2L launch variant picked by the plan's autotuner (see m2l_eval_ms) */
+  int64_t m2l_top_pairs;       /* M2L pairs on the top levels (fp64_top_levels), which the
+                                    FP32 form runs in FP64 in the "M2L top" stage */
+  double m2l_variant_ms[6];    /* autotuner: time of one M2L launch alone in each variant (operator
+                                  batches of 4, 2 or 8 k-steps, variants 3..5 the same with LDS
+                                  reserved; 81 <= (p+1)^2 <= 128, else unused; the batches differ
+                                  at p = 10) */
   int32_t batch_variant;       /* batched FP32 form: M2L variant picked by the autotuner ... */
   int32_t surrogate_rejected;  /* 1 when the plan's surrogate (network or tables) missed
                                     surrogate_check <= 1e-5 on the plan's sampled tasks and the
                                     quadrature served the whole plan instead */
-  double batch_variant_ms[10]; /*   ... and one launch's time in each: variant v has the tile shape
-                                  v % 5 (outputs per wave over operator rows x 64 vectors; 0: 4 waves
-                                  of 64 x 32, 1: 8 of 32 x 32, 2: 8 of 64 x 16, 3: 16 of 32 x 16,
-                                  4: 16 of 16 x 32) as one block per target box (v < 5) or as a
-                                  persistent XCD-aware grid (v >= 5); (p+1)^2 <= 128 only */
+  double batch_variant_ms[10]; /*   ... and one launch's time in each: variant v has operator batches
+                                  of 4, 2 or 8 k-steps, or of 4 or 2 with LDS reserved (v % 5), one
+                                  block per target box in ranges per XCD (v < 5) or in box order
+                                  (v >= 5); 81 <= (p+1)^2 <= 128, else the order alone (v < 2) */
   double m2l_eval_ms[6];       /* FP32 form: time of a whole unprofiled evaluation (near field and
-                                  sparse top levels on their streams beside the main M2L) with
-                                  each tile shape; m2l_variant is the fastest of these */
+                                  top levels on their streams beside the main M2L) with
+                                  each variant; m2l_variant is the fastest of these */
   double p2p_split_ms[5];      /* FP32 form: the same time with 100, 75, 50, 25 and 0 percent of
                                   the free P2P leaves launched at the fork and the rest after the
                                   main M2L launch ... */
@@ -307,16 +304,16 @@ typedef struct {
                                   p2p_reserve_ms; it bounds the P2P blocks a CU holds and leaves
                                   room for far-field blocks beside them */
   double p2p_reserve_ms[3];    /*   ... whole-evaluation times with 28672, 40960 and 0 bytes */
-  int64_t m2l_chunks;          /* M2L chunks below the top levels: each holds up to m2l_tile_cols
-                                  targets and one step per operator of its group (up to 4
-                                  operators that reach the same targets), and stores one partial
-                                  sum per target for all its steps */
+  int64_t m2l_chunks;          /* M2L units (FP32 form: below the FP64 top levels): each holds up to
+                                  m2l_tile_cols columns (a target box and an azimuth) and one step
+                                  per operator of its list (up to 4), and stores one product a
+                                  column for all its steps */
 } fmmlm_stats;
 
 int fmm_layered_plan_stats(fmmlm_plan_t plan, fmmlm_stats* out);
 
 /* Overrides the autotuner's choices (tests, benchmarks): m2l_variant selects the
- * FP32 M2L tile shape (0..5, see m2l_variant_ms), batch_variant the batched FP32
+ * FP32 M2L launch variant (0..5, see m2l_variant_ms), batch_variant the batched FP32
  * M2L variant (0..9, see batch_variant_ms), batch_min_rhs the narrowest pass that
  * runs batched (2..65, see fmmlm_stats.batch_min_rhs; 65 runs every vector on its
  * own); -1 leaves a choice unchanged.  FMMLM_EINVAL for a value out of range or a
@@ -590,12 +587,10 @@ int fmm_layered_density(int32_t n_interfaces, const double* z_interfaces, const 
  * next max_evals evaluations of the plan record a HIP event on their stream
  * before the first stage and after every stage (FMMLM_NSTAGES stages, in the
  * order gather, P2M, M2M, M2L top, M2L, M2L reduce, L2L, L2P, P2P free,
- * P2P reaction, combine).  "M2L" is one kernel launch: the operator-major M2L
- * chunks of the levels below the top ones (FP32 matrix cores in the FP32 form,
- * FP64 matrix cores in the FP64 form); "M2L top" clears the local expansions,
- * runs the top levels (sparse FP64 kernel) and, in the FP32 form, converts the
- * multipole expansions to FP32; "M2L reduce" adds each target's chunk
- * products.
+ * P2P reaction, combine).  "M2L" is one kernel launch: the M2L units on the
+ * FP32 matrix cores (FP32 form, below the FP64 top levels) or the FP64 ones (FP64
+ * form, every level); "M2L top" clears the local expansions and, in the FP32 form,
+ * runs the top levels in FP64; "M2L reduce" adds each target's products.
  * profile_end synchronises the device, writes the summed milliseconds of each
  * stage over the recorded evaluations to stage_ms[FMMLM_NSTAGES] (host), the
  * number of recorded evaluations to *n_evals, and stops recording.
