@@ -31,7 +31,6 @@
 #include <cstring>
 #include <map>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <tuple>
 #include <unordered_map>
@@ -133,7 +132,7 @@ hipError_t download(void* dst, const void* src, size_t bytes, hipStream_t st) {
   for (size_t i = 1; i < kParts; ++i) {
     try {
       th[i] = std::thread(part, i);
-    } catch (const std::system_error&) {
+    } catch (...) {
       part(i);
     }
   }
@@ -656,7 +655,7 @@ int build_m2l_units(fmmlm_plan_s* P, int64_t b0, int64_t b1, const std::vector<i
     }
     ptr.push_back((int32_t)slots.size());
   }
-  if (P->fp32 && P->opts.max_rhs > 1) {  // the batched FP32 form goes box by box
+  if (P->opts.max_rhs > 1) {  // the batched form goes box by box
     std::vector<int32_t> bptr(1, 0), bop, bphi, bsrc, bkind;
     for (int64_t b = b0; b < b1; ++b) {
       ent.clear();
@@ -993,16 +992,7 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     P->ng_free = (int64_t)(free_r2dz.size() / 2);
     P->ng_ops = P->ng_free + (int64_t)B.tasks.size();
     P->n_phi = (int64_t)(dirs.size() / 2);
-    P->ntop = P->fp32 ? top_end : 0;
-    if (P->opts.max_rhs > 1 && !P->fp32) {
-      std::vector<int32_t> of, op;
-      for (const OpFrame& f : fr) {
-        of.push_back(f.frame);
-        op.push_back(f.phi);
-      }
-      int rc0;
-      if ((rc0 = dev_upload(P, &P->op_frame, of, st)) || (rc0 = dev_upload(P, &P->op_phi, op, st))) return rc0;
-    }
+    P->ntop = P->fp32 ? top_end : P->NB;
     int rc0 = build_m2l_units(P, 0, P->fp32 ? top_end : P->NB, mptr, msrc, mop, fr, &P->u64, st);
     if (rc0 == FMMLM_OK && P->fp32) rc0 = build_m2l_units(P, top_end, P->NB, mptr, msrc, mop, fr, &P->u32, st);
     if (rc0) return rc0;
@@ -1405,10 +1395,6 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     U->W = W;
     if ((rc = gpu_build_frame_ops(P, *U, f32, st))) return rc;
   }
-  if (P->opts.max_rhs > 1 && !P->fp32) {  // the batched FP64 form's dense operators
-    if ((rc = dev_alloc(P, &P->Tfree, (size_t)std::max<int64_t>(P->nops, 1) * P->nrk * 32 * P->mrt))) return rc;
-    if ((rc = gpu_build_real_ops(P, st))) return rc;
-  }
   if ((rc = dev_alloc(P, &P->Txl, (size_t)16 * P->nrk * 32 * P->mrt))) return rc;
   if ((rc = gpu_build_xlate_ops(P, st))) return rc;
   if (P->fp32) {
@@ -1476,9 +1462,9 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     FMM_HIP_TRY(hipEventCreateWithFlags(e, hipEventDisableTiming));
   if ((rc = dev_alloc(P, &P->M, (size_t)P->NB * nrr * G))) return rc;
   if ((rc = dev_alloc(P, &P->Lx, (size_t)P->NB * nrr * G))) return rc;
-  if (P->fp32 && G > 1) {  // sources of the batched form
+  if (G > 1) {  // sources of the batched form
     P->gw = (int)(G + 15) / 16 * 16;
-    if ((rc = dev_alloc(P, &P->M32, (size_t)P->NB * P->nc * P->gw * 2)) ||
+    if ((P->fp32 && (rc = dev_alloc(P, &P->M32, (size_t)P->NB * P->nc * P->gw * 2))) ||
         (rc = dev_alloc(P, &P->M64, (size_t)std::max<int64_t>(P->ntop, 1) * P->nc * P->gw * 2)))
       return rc;
   }

@@ -631,47 +631,6 @@ __global__ void build_xlate_ops_kernel(int p, int nrk, int mr, const double* __r
 }
 
 
-// Real-form M2L operator: T[k][row] maps the real layout of a source expansion
-// (index k) to the real layout of the local expansion (row), including every
-// constant of eq. metole / eq. metoleimage1 and, for reaction operators, the
-// mirror sign (-1)^{n'+m'} of the polarization-source expansion; rows padded to
-// mr and columns to nrk with zeros.
-__global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfree, const double* __restrict__ G,
-                                      const cplx* __restrict__ E, const int32_t* __restrict__ op_frame,
-                                      const int32_t* __restrict__ op_phi, int ngs, const double* __restrict__ coefA,
-                                      double* __restrict__ T) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t per = (int64_t)nrk * mr;
-  if (t >= (int64_t)nops * per) return;
-  const int op = (int)(t / per);
-  const int k = (int)((t % per) / mr), row = (int)(t % mr);
-  const int nr = (p + 1) * (p + 1);
-  double v = 0.0;
-  if (k < nr && row < nr) {
-    int n2, m2, n, m;
-    bool im2, im;
-    rsplit(k, &n2, &m2, &im2);
-    rsplit(row, &n, &m, &im);
-    // unit input in the real layout -> complex M_{n2,m2} and M_{n2,-m2}
-    const cplx mp = im2 ? cmk(0.0, 1.0) : cmk(1.0, 0.0);
-    const int j = n + n2;
-    const double* Gj = G + (int64_t)op_frame[op] * ngs + kGPad + j * j + j;
-    const cplx* Eop = E + (int64_t)op_phi[op] * (2 * p + 1);
-    auto gat = [&](int kk) -> cplx { return Gj[kk] * (kk >= 0 ? Eop[kk] : cconj(Eop[-kk])); };
-    cplx acc = gat(m2 - m) * mp;
-    if (m2 > 0) {
-      // M_{n2,-m2} = (-1)^m2 conj(M_{n2,m2})
-      const cplx mm = (m2 & 1) ? cmk(-mp.re, mp.im) : cmk(mp.re, -mp.im);
-      acc = acc + gat(-m2 - m) * mm;
-    }
-    double f = sgn1(n + m) * coefA[cidx(n, m)] * (4.0 * kPi / (2.0 * n + 1.0)) * coefA[cidx(n2, m2)];
-    // reaction operators act on the mirrored (polarization-source) expansion
-    if (op >= nfree && ((n2 + m2) & 1)) f = -f;
-    v = f * (im ? acc.im : acc.re);
-  }
-  T[t] = v;
-}
-
 // M2L in operator frames, on the matrix cores, in FP64 or FP32.  In the frame
 // turned to an operator's azimuth its table g is real, so with
 //   a + i b = e^{i m' phi} M_{n'm'}   and   L_nm = e^{-i m phi} (c + i s)
@@ -683,7 +642,7 @@ __global__ void build_real_ops_kernel(int p, int nrk, int mr, int nops, int nfre
 // azimuth: 24,840 pairs of the top levels have 2,812 operators, 330 frames.
 // Pairs (n, m) are taken orders m >= 1 first (pair_dec), so the s matrix is over
 // the first ns of the nc pairs.  build_frame_ops_kernel folds in every constant of
-// eqs. metole, metoleimage1 and the mirror sign, as build_real_ops_kernel does.
+// eqs. metole, metoleimage1 and the mirror sign, into the matrices.
 // Layout: column (pair of the source) by column, its RC 16-row blocks of c, then
 // its RS of s; whole k-steps of four columns, zeros past nc.
 __host__ __device__ constexpr int frame_ksteps(int n) { return (n + 3) / 4; }
@@ -1197,7 +1156,7 @@ vector_minor_kernel(int nr, int nc, int ns, int g, int gw, int64_t slab, const d
   }
 }
 
-// Batched M2L in operator frames (FP32 form; FP64 on its top levels): a block
+// Batched M2L in operator frames (FP32; FP64 form and top levels in FP64): a block
 // takes one target box, or a run of its entries (items), and up to 64 vectors,
 // 16 a wave.  Entry by entry the wave turns the source's pairs (one azimuth for
 // all its vectors, rows of 16 vectors contiguous) into the operand fragments; the
@@ -2387,17 +2346,6 @@ int gpu_build_frame_ops(fmmlm_plan_s* P, M2LUnits& U, bool f32, hipStream_t st) 
   return FMMLM_OK;
 }
 
-int gpu_build_real_ops(fmmlm_plan_s* P, hipStream_t st) {
-  if (P->nops == 0) return FMMLM_OK;
-  const int64_t tot = P->nops * (int64_t)P->nrk * (32 * P->mrt);
-  build_real_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
-      P->p, P->nrk, 32 * P->mrt, (int)P->nops, (int)P->n_free_ops, P->G, reinterpret_cast<const cplx*>(P->E),
-      P->op_frame, P->op_phi, P->ngs, P->coefA, P->Tfree);
-  FMM_HIP_TRY(hipGetLastError());
-  FMM_HIP_TRY(hipStreamSynchronize(st));
-  return FMMLM_OK;
-}
-
 int gpu_build_xlate_ops(fmmlm_plan_s* P, hipStream_t st) {
   const int mr = 32 * P->mrt, nr = (P->p + 1) * (P->p + 1);
   FMM_HIP_TRY(hipMemsetAsync(P->Txl, 0, (size_t)16 * P->nrk * mr * sizeof(double), st));
@@ -2870,28 +2818,17 @@ int gpu_eval_batch(fmmlm_plan_s* P, int g, const double* q, int64_t ldq, double*
     const int64_t n64 = f32 ? P->bbox_split : P->nbbox;
     const int64_t n32 = f32 ? P->nbbox - P->bbox_split : 0;
     if (!f32) mark();  // the FP64 form has one M2L launch over every level
-    if (f32 && P->ntop > 0 && n64 > 0) {
-      // the FP64 top levels as work items (few boxes, long entry lists), then a
-      // reduction per box
+    if (n64 > 0) {
+      // the FP32 form's FP64 top levels as work items (few boxes, long entry
+      // lists), then a reduction per box; the FP64 form one block per box
       vector_minor_kernel<<<(unsigned)P->ntop, 256, 0, st>>>(nr, nc, nc - p - 1, g, P->gw, slab, P->M, P->M64);
-      if (int rc = launch_frame_batch_kb<double, 2>(P, P->u64, g, P->n_btop_items, P->bbox, P->btop_items, false, 0,
-                                                    parts, P->M64, P->Pbtop, st))
+      if (int rc = launch_frame_batch_kb<double, 2>(P, P->u64, g, f32 ? P->n_btop_items : n64, P->bbox,
+                                                    f32 ? P->btop_items : nullptr, false, 0, parts, P->M64, P->Pbtop,
+                                                    st))
         return rc;
-      m2l_btop_reduce_kernel<<<(unsigned)n64, 256, 0, st>>>(nr, g, P->bbox, P->btop_iptr, P->Pbtop, P->blevel,
-                                                            P->sc_levels, slab, P->Lx);
-    } else if (n64 > 0) {
-      switch (P->mrt) {
-#define B64(R)                                                                                               \
-  case R:                                                                                                    \
-    m2l_batch64_kernel<R><<<(unsigned)n64, 256, 0, st>>>(nr, P->nrk, g, P->NB, P->bbox, 0, P->m2l_ptr,       \
-                                                         P->m2l_src, P->m2l_op, (int)P->n_free_ops, parts,   \
-                                                         P->blevel, P->sc_levels, P->Tfree, P->M, P->Lx);    \
-    break;
-        B64(2) B64(4) B64(6) B64(8) B64(10)
-#undef B64
-        default:
-          return FMMLM_EUNSUPPORTED;
-      }
+      if (f32)
+        m2l_btop_reduce_kernel<<<(unsigned)n64, 256, 0, st>>>(nr, g, P->bbox, P->btop_iptr, P->Pbtop, P->blevel,
+                                                              P->sc_levels, slab, P->Lx);
     }
     if (n32 > 0)
       vector_minor_kernel<<<(unsigned)P->NB, 256, 0, st>>>(nr, nc, nc - p - 1, g, P->gw, slab, P->M, P->M32);

@@ -181,10 +181,8 @@ struct fmmlm_plan_s {
   int ngs = 0;                     // stride of G (even)
   double* E = nullptr;             // azimuths: e^{i k phi}, k <= 2p [n_phi][2p + 1] complex
   int64_t n_phi = 0;
-  int32_t *op_frame = nullptr, *op_phi = nullptr;  // [nops] (batched FP64 form: the dense operators' build)
   int32_t *pair_dec = nullptr;     // [nc] pair j: offset in the real layout | order << 16 (orders >= 1 first)
   fmmlm::M2LUnits u64, u32;               // FP64 form: u64 all levels; FP32 form: u64 top levels, u32 the rest
-  double* Tfree = nullptr;         // batched FP64 form: [nops][nrk][32 mrt] real-form operators (free space, then reaction)
   int nrk = 0, mrt = 0;            // padded inner dimension, padded rows / 32
   int m2l_variant = 0;             // FP32 M2L launch variant picked by the autotuner
   int batch_variant = 0;           // batched FP32 M2L shape / persistence picked by the autotuner
@@ -199,10 +197,10 @@ struct fmmlm_plan_s {
   int xl_tile_cols = 32;           // target boxes per translation tile
   // FP32 form
   bool fp32 = false;
-  float* M32 = nullptr;            // batched FP32 form: expansions [NB][nc][gw] (re, im) in FP32 ...
-  double* M64 = nullptr;           //   ... and the top levels' in FP64
+  float* M32 = nullptr;            // batched form: expansions [NB][nc][gw] (re, im) in FP32 (FP32 form) ...
+  double* M64 = nullptr;           //   ... and in FP64 (its top levels; FP64 form: every box)
   int gw = 16;                     // vectors of a row (a multiple of 16)
-  int64_t ntop = 0;                // boxes of the FP64 top levels (they come first)
+  int64_t ntop = 0;                // boxes whose M2L runs in FP64 (they come first)
   float *pxh = nullptr, *pxl = nullptr, *pyh = nullptr, *pyl = nullptr, *phh = nullptr, *phl = nullptr;
   float* qt32 = nullptr;
   // batched form (opts.max_rhs > 1): expansions, charges and potentials of up
@@ -403,7 +401,6 @@ int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_r2dz, const std:
                   const std::vector<int>& dirs, const double* d_tables, hipStream_t st);
 int gpu_build_frame_ops(fmmlm_plan_s* P, M2LUnits& U, bool f32, hipStream_t st);
 int64_t frame_op_len(int p, int64_t* row_len);  // values of a frame operator, of one of its columns
-int gpu_build_real_ops(fmmlm_plan_s* P, hipStream_t st);
 int gpu_build_xlate_ops(fmmlm_plan_s* P, hipStream_t st);
 int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st);
 int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st);
