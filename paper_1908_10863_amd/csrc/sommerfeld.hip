@@ -1113,9 +1113,10 @@ CompInfo make_comp(const Medium& md, int lt, int ls, int a, int b) {
   }
   const double aq = std::fabs(c.imgq);
   const double n = aq > 0.0 ? std::ceil(std::log(0x1.0p-56 * (1.0 - aq)) / std::log(aq)) : 0.0;
+  if (!(aq < 1.0)) return c;  // the terms do not decay (|q| rounds to 1: contrasts from 1e16 on at both interfaces)
   if (c.img1 == 0.0) {
     c.nimg = 0;
-  } else if (n + 1.0 <= kImagesMost) {  // false too where |q| rounds to 1
+  } else if (n + 1.0 <= kImagesMost) {
     c.nimg = (int)std::max(n, 0.0) + 1;
   }
   return c;
