@@ -1104,10 +1104,10 @@ CompInfo make_comp(const Medium& md, int lt, int ls, int a, int b) {
   const double rup0 = (e1 - e0) / (e1 + e0), rdn1 = (e1 - e2) / (e1 + e2);
   c.imgq = rup0 * rdn1;
   c.imgd = 2.0 * (md.d[0] - md.d[1]);
-  if (lt == ls && lt == 0) {
-    c.img1 = (4.0 * e0 * e1 / ((e0 + e1) * (e0 + e1))) * rdn1;
+  if (lt == ls && lt == 0) {  // (each factor at most 2: products of permittivities overflow from 1e154 on)
+    c.img1 = (2.0 * e0 / (e0 + e1)) * (2.0 * e1 / (e0 + e1)) * rdn1;
   } else if (lt == ls && lt == 2) {
-    c.img1 = (4.0 * e1 * e2 / ((e1 + e2) * (e1 + e2))) * rup0;
+    c.img1 = (2.0 * e1 / (e1 + e2)) * (2.0 * e2 / (e1 + e2)) * rup0;
   } else {
     c.img1 = c.sinf * c.imgq;
   }

@@ -120,3 +120,14 @@ def test_reflection_of_plus_one(eps):
         use = rho <= z + zi
         got = F.sommerfeld(D, eps, 1, 1, a, b, S, rho, z, 0)
         assert not np.isfinite(got[use]).any()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** 540, 2.0 ** -540])
+def test_permittivities_whose_products_leave_the_range(scale):
+    """Only ratios of permittivities enter: a common factor, a power of two, changes nothing."""
+    from paper_1908_10863_amd import fmmlm as F
+    rho, z = _points()
+    eps = np.array([2.0, 1.0, 3.0])
+    for comp in COMPS:
+        np.testing.assert_array_equal(F.sommerfeld(D, eps * scale, *comp, S, rho, z, NMAX),
+                                      F.sommerfeld(D, eps, *comp, S, rho, z, NMAX))
