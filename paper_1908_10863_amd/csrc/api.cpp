@@ -623,7 +623,10 @@ int build_m2l_units(fmmlm_plan_s* P, int64_t b0, int64_t b1, const std::vector<i
     std::stable_sort(cols[g].begin(), cols[g].end(), [](const Col& x, const Col& y) { return x.tgt < y.tgt; });
     for (size_t c0 = 0; c0 < cols[g].size(); c0 += C) {
       const int64_t u = (int64_t)kind.size();
-      if ((u + 1) * C >= ((int64_t)1 << 31)) return FMMLM_ENOMEM;
+      if ((u + 1) * C >= ((int64_t)1 << 31)) {
+        set_last_error("M2L: more than 2^31 products");
+        return FMMLM_ENOMEM;
+      }
       const size_t nc = std::min<size_t>(C, cols[g].size() - c0);
       U->ncols += (int64_t)nc;
       kind.push_back(sigs[g][0] < P->ng_free ? (int32_t)FMMLM_FREE : (int32_t)FMMLM_REACTION);
@@ -978,12 +981,6 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     const int nr0 = (P->p + 1) * (P->p + 1);
     P->mrt = ((nr0 + 31) / 32 + 1) / 2 * 2;
     P->nrk = (nr0 + 15) / 16 * 16;
-    // operator tables must fit a budget (FP64 + FP32 copies)
-    const double tbytes = (double)P->nops * P->nrk * 32.0 * P->mrt * (P->fp32 ? 12.0 : 8.0);
-    if (tbytes > 32.0 * (1 << 30)) {
-      set_last_error("M2L operator tables exceed 32 GiB");
-      return FMMLM_ENOMEM;
-    }
     const int ksp = P->opts.fp64_top_levels;  // FP32 form: the levels above stay FP64
     const int64_t top_end = P->lev_off[std::min(ksp, P->maxlev + 1)];
     for (int64_t b = 0; b < top_end; ++b) P->stats.m2l_top_pairs += mptr[b + 1] - mptr[b];
@@ -996,6 +993,14 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     int rc0 = build_m2l_units(P, 0, P->fp32 ? top_end : P->NB, mptr, msrc, mop, fr, &P->u64, st);
     if (rc0 == FMMLM_OK && P->fp32) rc0 = build_m2l_units(P, top_end, P->NB, mptr, msrc, mop, fr, &P->u32, st);
     if (rc0) return rc0;
+    // operator tables must fit a budget: G and the frame operators A of both precisions (the
+    // products W grow with the points, not with the operators, and are left to the allocation)
+    const double tbytes = (double)P->ng_ops * P->ngs * 8.0 +
+                          (double)frame_op_len(P->p, nullptr) * ((double)P->u64.nops * 8.0 + (double)P->u32.nops * 4.0);
+    if (tbytes > 32.0 * (1 << 30)) {
+      set_last_error("M2L operator tables exceed 32 GiB");
+      return FMMLM_ENOMEM;
+    }
     const M2LUnits& U = P->fp32 ? P->u32 : P->u64;
     P->stats.m2l_steps = U.nsteps;
     P->stats.m2l_chunks = U.n;
