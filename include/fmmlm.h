@@ -275,7 +275,8 @@ typedef struct {
                                     / (steps * cols) */
   int32_t m2l_variant;         /* FP32 form: M2L launch variant picked by the plan's autotuner (see m2l_eval_ms) */
   int64_t m2l_top_pairs;       /* M2L pairs on the top levels (fp64_top_levels), which the
-                                    FP32 form runs in FP64 in the "M2L top" stage */
+                                    FP32 form runs in FP64 in the "M2L top" stage (FP64
+                                    form: 0, its main launch runs every level) */
   double m2l_variant_ms[6];    /* autotuner: time of one M2L launch alone in each variant (operator
                                   batches of 4, 2 or 8 k-steps, variants 3..5 the same with LDS
                                   reserved; 81 <= (p+1)^2 <= 128, else unused; the batches differ

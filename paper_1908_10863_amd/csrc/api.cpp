@@ -983,7 +983,7 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
     P->nrk = (nr0 + 15) / 16 * 16;
     const int ksp = P->opts.fp64_top_levels;  // FP32 form: the levels above stay FP64
     const int64_t top_end = P->lev_off[std::min(ksp, P->maxlev + 1)];
-    for (int64_t b = 0; b < top_end; ++b) P->stats.m2l_top_pairs += mptr[b + 1] - mptr[b];
+    if (P->fp32) P->stats.m2l_top_pairs = mptr[top_end];  // (the top levels' boxes come first)
     std::vector<OpFrame> fr;
     op_frames(B, (int)P->n_free_ops, P->nops, &fr, &free_r2dz, &dirs);
     P->ng_free = (int64_t)(free_r2dz.size() / 2);
