@@ -279,8 +279,7 @@ typedef struct {
                                     form: 0, its main launch runs every level) */
   double m2l_variant_ms[6];    /* autotuner: time of one M2L launch alone in each variant (operator
                                   batches of 4, 2 or 8 k-steps, variants 3..5 the same with LDS
-                                  reserved; 81 <= (p+1)^2 <= 128, else unused; the batches differ
-                                  at p = 10) */
+                                  reserved; 81 <= (p+1)^2 <= 128, else unused) */
   int32_t batch_variant;       /* batched FP32 form: M2L variant picked by the autotuner ... */
   int32_t surrogate_rejected;  /* 1 when the plan's surrogate (network or tables) missed
                                     surrogate_check <= 1e-5 on the plan's sampled tasks and the

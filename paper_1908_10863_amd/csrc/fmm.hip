@@ -2441,14 +2441,14 @@ int launch_frame_kb(const fmmlm_plan_s* P, const M2LUnits& U, size_t reserve, un
     FMM_HIP_TRY(hipGetLastError());                                                                            \
     return FMMLM_OK;                                                                                           \
   }
-  if constexpr (KB == 2 || sizeof(T) == 4) {
-    FR(5, 4)
-  }
   if constexpr (KB == 4) {  // p = 1..16
     FR(1, 1) FR(2, 1) FR(2, 2) FR(3, 2)
   }
+  if constexpr (KB == 2 || sizeof(T) == 4) {  // the tuner's orders (m2l_variants)
+    FR(3, 3) FR(4, 3) FR(5, 4)
+  }
   if constexpr (KB == (sizeof(T) == 8 ? 2 : 4)) {
-    FR(3, 3) FR(4, 3) FR(5, 5) FR(6, 5) FR(7, 6)
+    FR(5, 5) FR(6, 5) FR(7, 6)
   }
   if constexpr (KB == 2) {
     FR(8, 7) FR(9, 8) FR(10, 9)
@@ -2466,8 +2466,7 @@ int launch_frame(const fmmlm_plan_s* P, const M2LUnits& U, int variant, unsigned
   // (p = 10 at 2^20 charges: 0.83 against 0.94 ms; p = 12: 2.61 against 2.93 ms;
   // p = 8: the same); below, a batch of 2 has no room for the epilogue's rows
   if (P->p > 13 || (sizeof(T) == 8 && P->p >= 8)) return launch_frame_kb<T, 2>(P, U, 0, parts, M, st);
-  if (P->p != 10) return launch_frame_kb<T, 4>(P, U, reserve, parts, M, st);
-  switch (variant % 3) {  // (FP32, p = 10)
+  switch (variant % 3) {  // (0 where there are no variants)
     case 1: return launch_frame_kb<T, 2>(P, U, reserve, parts, M, st);
     case 2: return launch_frame_kb<T, 8>(P, U, reserve, parts, M, st);
     default: return launch_frame_kb<T, 4>(P, U, reserve, parts, M, st);
@@ -2652,11 +2651,11 @@ int launch_frame_batch_kb(const fmmlm_plan_s* P, const M2LUnits& U, int g, int64
     FMM_HIP_TRY(hipGetLastError());                                                                             \
     return FMMLM_OK;                                                                                            \
   }
-  if constexpr (KB == 2 || sizeof(T) == 4) {
-    FB(5, 4)
+  if constexpr (KB == 2 || sizeof(T) == 4) {  // the tuner's orders (batch_variants)
+    FB(3, 3) FB(4, 3) FB(5, 4)
   }
   if constexpr (KB == (sizeof(T) == 8 ? 2 : 4)) {  // p = 1..16
-    FB(1, 1) FB(2, 1) FB(2, 2) FB(3, 2) FB(3, 3) FB(4, 3) FB(5, 5) FB(6, 5) FB(7, 6)
+    FB(1, 1) FB(2, 1) FB(2, 2) FB(3, 2) FB(5, 5) FB(6, 5) FB(7, 6)
   }
   if constexpr (KB == 2) {
     FB(8, 7) FB(9, 8) FB(10, 9)
@@ -2673,9 +2672,9 @@ int launch_batch32(const fmmlm_plan_s* P, int variant, int g, int64_t n, unsigne
   const int shape = variant % nv;
   const size_t reserve = shape >= 3 ? 61440 : 0;
   if (P->p > 13) return launch_frame_batch_kb<float, 2>(P, P->u32, g, n, bx, nullptr, sw, 0, parts, P->M32, nullptr, st);
-  if (P->p == 10 && (shape == 1 || shape == 4))
+  if (shape == 1 || shape == 4)
     return launch_frame_batch_kb<float, 2>(P, P->u32, g, n, bx, nullptr, sw, reserve, parts, P->M32, nullptr, st);
-  if (P->p == 10 && shape == 2)
+  if (shape == 2)
     return launch_frame_batch_kb<float, 8>(P, P->u32, g, n, bx, nullptr, sw, 0, parts, P->M32, nullptr, st);
   return launch_frame_batch_kb<float, 4>(P, P->u32, g, n, bx, nullptr, sw, reserve, parts, P->M32, nullptr, st);
 }

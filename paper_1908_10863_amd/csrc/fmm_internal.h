@@ -405,7 +405,7 @@ int gpu_build_xlate_ops(fmmlm_plan_s* P, hipStream_t st);
 int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st);
 int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st);
 constexpr int kM2LVariants = 6;  // FP32 M2L launch variants the autotuner tries
-constexpr int kBatchShapes = 5;  // batched FP32 M2L tile shapes (each also persistent)
+constexpr int kBatchShapes = 5;  // batched FP32 M2L launch variants (each in two orders of the boxes)
 int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st);
 // target point, source point and component of every reaction near-field pair,
 // in the order of rp_val (entry by entry, rows of sources); tgt0, comp: per entry
