@@ -179,7 +179,6 @@ struct Builder {
   std::map<std::tuple<int, int, int, int, int>, int> reac_op_id;  // (comp, level, dx, dy, dz)
   std::map<std::tuple<int, int, int, int>, int> task_id;          // (comp, level, r2, dz)
   std::vector<int> reac_task;
-  std::vector<double> reac_phi, reac_S;
   std::vector<SommTask> tasks;
   // P2P
   std::vector<std::vector<std::pair<int, int>>> p2p_free;   // per box (leaf) : (start, count)
@@ -286,8 +285,6 @@ struct Builder {
             op = (int)reac_task.size();
             reac_op_id[key] = op;
             reac_task.push_back(tid);
-            reac_phi.push_back(std::atan2((double)dy, (double)dx));
-            reac_S.push_back(S);
           } else {
             op = it->second;
           }
@@ -628,7 +625,6 @@ int build_m2l_units(fmmlm_plan_s* P, int64_t b0, int64_t b1, const std::vector<i
         return FMMLM_ENOMEM;
       }
       const size_t nc = std::min<size_t>(C, cols[g].size() - c0);
-      U->ncols += (int64_t)nc;
       kind.push_back(sigs[g][0] < P->ng_free ? (int32_t)FMMLM_FREE : (int32_t)FMMLM_REACTION);
       for (size_t c = 0; c < (size_t)C; ++c) {
         phi.push_back(c < nc ? cols[g][c0 + c].phi : 0);
@@ -1303,7 +1299,7 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
   UP(px, px); UP(py, py); UP(ph, ph); UP(puser, puser); UP(user_pos, upos); UP(pleaf, pleaf);
   UP(bcx, bcx); UP(bcy, bcy); UP(bch, bch); UP(blevel, blevel); UP(bstart, bstart); UP(bcount, bcount);
   UP(bparent, bparent); UP(bchild0, bchild0); UP(bnchild, bnchild); UP(leaves, leaves);
-  UP(m2l_ptr, mptr); UP(m2l_nfree, mnfree); UP(m2l_src, msrc); UP(m2l_op, mop);
+  UP(m2l_ptr, mptr); UP(m2l_nfree, mnfree); UP(m2l_src, msrc);
   UP(p2p_ptr, pptr); UP(p2p_src, psrc); UP(pl_leaves, plv); UP(rp_ptr, rptr); UP(rp_src, rsrc); UP(rp_voff, rvoff);
   UP(mu_order, morder); UP(mu_leaf, mleaf); UP(mu_tb, mtb); UP(mu_rptr, mrptr); UP(mu_rng, mrng); UP(mu_boff, mboff);
   UP(mu_bidx, mbidx); UP(cb_base, cbbase); UP(cb_n, cbn);
@@ -1781,8 +1777,7 @@ static int plan_impl(int32_t n_interfaces, const double* z_interfaces, const dou
   P->p = p;
   P->nc = ncoef(p);
   P->ng = ncoef(2 * p);
-  P->ngs = kGPad + (2 * p + 1) * (2 * p + 1) + kGPadEnd;
-  P->ngs += P->ngs & 1;
+  P->ngs = (2 * p + 1) * (2 * p + 1);
   P->opts = o;
   P->fp32 = (o.precision == FMMLM_FP32_COMPENSATED);
   try {

@@ -100,7 +100,6 @@ __device__ inline cplx full_at(const cplx* X, int n, int m) {
 
 // Real layout of an expansion with real sources: (p+1)^2 doubles per box,
 // row n holds Re X_n0, then (Re X_nm, Im X_nm) for m = 1..n.
-__device__ inline int rre(int n, int m) { return n * n + (m ? 2 * m - 1 : 0); }
 __device__ inline cplx rload(const double* X, int n, int m) {
   return m ? cmk(X[n * n + 2 * m - 1], X[n * n + 2 * m]) : cmk(X[n * n], 0.0);
 }
@@ -134,38 +133,32 @@ __device__ inline int isqrt_row(int t) {
 // ---------------------------------------------------------------- operators
 // An operator's table in the frame turned so that its offset has azimuth 0: the
 // real g(j, k) = G(j, k) e^{-i k phi} of eqs. metole, metoleimage1 for
-// -j <= k <= j (g(j, -k) = (-1)^k g(j, k)) at [kGPad + j j + j + k], j <= 2p, with
-// zeros before and after.
-__device__ inline bool g_index(int i, int p2, int* j, int* k) {
-  i -= kGPad;
-  if (i < 0 || i >= (p2 + 1) * (p2 + 1)) return false;
+// -j <= k <= j (g(j, -k) = (-1)^k g(j, k)) at [j j + j + k], j <= 2p.
+__device__ inline void g_index(int i, int* j, int* k) {
   int r = (int)sqrt((double)i);
   while (r * r > i) --r;
   while ((r + 1) * (r + 1) <= i) ++r;
   *j = r;
   *k = i - r * r - r;
-  return true;
 }
 
 // free operators: r2dz [nops][2]
-__global__ void build_free_ops_kernel(const int* __restrict__ r2dz, int64_t nops, int p2, int ngs,
+__global__ void build_free_ops_kernel(const int* __restrict__ r2dz, int64_t nops, int ngs,
                                       const double* __restrict__ coefA, double* __restrict__ G) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nops * ngs) return;
   const int64_t op = t / ngs;
   const int c = (int)(t % ngs);
   int j, k;
-  double g = 0.0;
-  if (g_index(c, p2, &j, &k)) {
-    const int ak = abs(k);
-    g = (kInv4Pi / coefA[cidx(j, ak)]) * irregular_nm(j, ak, sqrt((double)r2dz[2 * op]), 0.0, r2dz[2 * op + 1]).re;
-    if (k < 0) g *= sgn1(k);
-  }
-  G[t] = g;
+  g_index(c, &j, &k);
+  const int ak = abs(k);
+  const double g =
+      (kInv4Pi / coefA[cidx(j, ak)]) * irregular_nm(j, ak, sqrt((double)r2dz[2 * op]), 0.0, r2dz[2 * op + 1]).re;
+  G[t] = k < 0 ? g * sgn1(k) : g;
 }
 
 // reaction operators: one per Sommerfeld task
-__global__ void build_reaction_ops_kernel(const double* __restrict__ Sl, int64_t nops, int p2, int ng, int ngs,
+__global__ void build_reaction_ops_kernel(const double* __restrict__ Sl, int64_t nops, int ng, int ngs,
                                           const double* __restrict__ coefA, const double* __restrict__ tables,
                                           double* __restrict__ G) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -173,15 +166,12 @@ __global__ void build_reaction_ops_kernel(const double* __restrict__ Sl, int64_t
   const int64_t op = t / ngs;
   const int c = (int)(t % ngs);
   int j, k;
-  double g = 0.0;
-  if (g_index(c, p2, &j, &k)) {
-    const int ak = abs(k);
-    const double SI = tables[op * ng + cidx(j, ak)];
-    const double cj = sqrt((2.0 * j + 1.0) / (4.0 * kPi));
-    g = Sl[op] * cj * SI * kInv4Pi / coefA[cidx(j, ak)];
-    if (k < 0) g *= sgn1(k);
-  }
-  G[t] = g;
+  g_index(c, &j, &k);
+  const int ak = abs(k);
+  const double SI = tables[op * ng + cidx(j, ak)];
+  const double cj = sqrt((2.0 * j + 1.0) / (4.0 * kPi));
+  const double g = Sl[op] * cj * SI * kInv4Pi / coefA[cidx(j, ak)];
+  G[t] = k < 0 ? g * sgn1(k) : g;
 }
 
 // e^{i k phi}, k <= p2, of the directions (dx, dy)
@@ -663,7 +653,7 @@ __global__ void build_frame_ops_kernel(int p, int nc, int ns, int rc, int rt, in
   if (c ? (r < nc && col < nc) : (r < ns && col < ns)) {
     const int m = dec[r] >> 16, m2 = dec[col] >> 16;
     const int n = (int)sqrt((double)(dec[r] & 0xffff) + 0.5), n2 = (int)sqrt((double)(dec[col] & 0xffff) + 0.5);
-    const double* Gj = G + fo * ngs + kGPad + (n + n2) * (n + n2) + n + n2;
+    const double* Gj = G + fo * ngs + (n + n2) * (n + n2) + n + n2;
     v = Gj[m2 - m];
     if (m2 > 0) v += (c ? sgn1(m) : -sgn1(m)) * Gj[m2 + m];
     double f = sgn1(n + m) * coefA[cidx(n, m)] * (4.0 * kPi / (2.0 * n + 1.0)) * coefA[cidx(n2, m2)];
@@ -999,21 +989,20 @@ xlate_direct_kernel(int nr, int nrk, int mr, int64_t tile0, int64_t unit0, const
 
 // ---------------------------------------------------------------- batched form
 // Many charge vectors in one evaluation: expansions are stored RHS-major
-// ([rhs][box][(p+1)^2]), and M2L runs one block per target box whose columns
-// are the charge vectors: each interaction-list entry is one operator applied
-// to the source box's expansions of all G <= 64 vectors.
-// FP64 variant on the matrix cores (v_mfma_f64_16x16x4f64; lane l: A[row
+// ([rhs][box][(p+1)^2]).  The translations (M2M, L2L) run one block per target
+// box whose columns are the charge vectors: each entry is one octant operator
+// applied to the source box's expansions of all G <= 64 vectors, in FP64 on the
+// matrix cores (v_mfma_f64_16x16x4f64; lane l: A[row
 // l % 16][k l / 16], B[k l / 16][column l % 16], result D[row l / 16 + 4 v]
 // [column l % 16], verified on the GPU by an in-bounds probe).  Four waves, 2 x 2
 // over the tile of 32 MRT operator rows x 64 vectors, each owning MRT x 2 blocks
 // of 16 x 16; operator and operand slices of KC columns double-buffered in LDS.
 template <int MRT>
 __global__ void __launch_bounds__(256)
-m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict__ boxes, int64_t box0,
-                   const int32_t* __restrict__ mptr, const int32_t* __restrict__ msrc,
-                   const int32_t* __restrict__ mop, int nfree, unsigned parts,
-                   const int32_t* __restrict__ blevel, const double* __restrict__ sc,
-                   const double* __restrict__ T, const double* __restrict__ M, double* __restrict__ Lx) {
+xlate_batch_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict__ boxes, int64_t box0,
+                   const int32_t* __restrict__ ptr, const int32_t* __restrict__ src,
+                   const int32_t* __restrict__ op, const double* __restrict__ T, const double* __restrict__ X,
+                   double* __restrict__ dst) {
   far_chain_priority();
   constexpr int KC = (MRT <= 4) ? 16 : 8;
   constexpr int MR = 32 * MRT;
@@ -1035,23 +1024,21 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
   for (int i = 0; i < MRT; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-  const int s0 = mptr[b], s1 = mptr[b + 1];
+  const int s0 = ptr[b], s1 = ptr[b + 1];
   const int nch = nrk / KC;
   const int total = (s1 - s0) * nch;
   const int64_t slab = nb * (int64_t)nr;  // one vector's expansions
   double rt[NTR], rb[NBR];
   auto load = [&](int q) {
     const int s = s0 + q / nch, k0 = (q % nch) * KC;
-    const int op = mop[s] >= 0 ? mop[s] : ~mop[s];
-    const unsigned kind = (op < nfree) ? FMMLM_FREE : FMMLM_REACTION;
-    const double* Tc = T + ((int64_t)op * nrk + k0) * MR;
-    const int sb = (parts & kind) ? msrc[s] : -1;
+    const double* Tc = T + ((int64_t)op[s] * nrk + k0) * MR;
+    const int sb = src[s];
 #pragma unroll
     for (int r = 0; r < NTR; ++r) rt[r] = Tc[tid + 256 * r];
 #pragma unroll
     for (int r = 0; r < NBR; ++r) {
       const int i = tid + 256 * r, col = i / KC, k = k0 + i % KC;
-      rb[r] = (sb >= 0 && col < g && k < nr) ? M[col * slab + (int64_t)sb * nr + k] : 0.0;
+      rb[r] = (col < g && k < nr) ? X[col * slab + (int64_t)sb * nr + k] : 0.0;
     }
   };
   auto stash = [&](int buf) {
@@ -1094,7 +1081,6 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
     }
     __syncthreads();
   }
-  const double inv = sc ? sc[blevel[b]] : 1.0;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int col = col0 + 16 * j + li;
@@ -1105,7 +1091,7 @@ m2l_batch64_kernel(int nr, int nrk, int g, int64_t nb, const int32_t* __restrict
       for (int v = 0; v < 4; ++v) {
         const int row = row0 + 16 * i + lk + 4 * v;
         if (row >= nr) continue;
-        Lx[col * slab + (int64_t)b * nr + row] += acc[i][j][v] * inv;
+        dst[col * slab + (int64_t)b * nr + row] += acc[i][j][v];
       }
   }
 }
@@ -2279,7 +2265,7 @@ int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_r2dz, const std:
     hipError_t e = hipMemcpyAsync(di, hi.data(), ni * sizeof(int), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && nfree > 0) {
       const int64_t tot = nfree * P->ngs;
-      build_free_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(di, nfree, p2, P->ngs, P->coefA, P->G);
+      build_free_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(di, nfree, P->ngs, P->coefA, P->G);
       e = hipGetLastError();
     }
     if (e == hipSuccess && P->n_phi > 0) {
@@ -2300,7 +2286,7 @@ int gpu_build_ops(fmmlm_plan_s* P, const std::vector<int>& free_r2dz, const std:
     if (e == hipSuccess) {
       const int64_t tot = nreac * P->ngs;
       build_reaction_ops_kernel<<<(unsigned)((tot + 255) / 256), 256, 0, st>>>(
-          dS, nreac, p2, P->ng, P->ngs, P->coefA, d_tables, P->G + nfree * P->ngs);
+          dS, nreac, P->ng, P->ngs, P->coefA, d_tables, P->G + nfree * P->ngs);
       e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -2687,7 +2673,6 @@ int gpu_tune_batch(fmmlm_plan_s* P, hipStream_t st) {
   const int64_t n32 = P->nbbox - P->bbox_split;
   const int nv = batch_variants(P);
   if (!P->fp32 || P->gmax < 2 || n32 <= 0) return FMMLM_OK;
-  const int64_t nr = (int64_t)(P->p + 1) * (P->p + 1);
   FMM_HIP_TRY(hipMemsetAsync(P->M32, 0, (size_t)P->NB * P->nc * P->gw * 2 * sizeof(float), st));
   hipEvent_t e0, e1;
   FMM_HIP_TRY(hipEventCreate(&e0));
@@ -2747,21 +2732,18 @@ int launch_xlate_level(const fmmlm_plan_s* P, const std::array<int64_t, 4>& r, b
   return FMMLM_OK;
 }
 
-// The batched FP64 GEMM over an entry list (translations): targets
-// boxes[b0, b0 + nb), per target the entries [ptr[b], ptr[b + 1]) of (source
-// box, operator of T); dst[vector][box] += sum of T[op] X[vector][source].
-int launch_batch64_list(const fmmlm_plan_s* P, int g, const int32_t* boxes, int64_t b0, int64_t nb,
+// The batched translations over an entry list: targets boxes[b0, b0 + nb), per
+// target the entries [ptr[b], ptr[b + 1]) of (source box, operator of T);
+// dst[vector][box] += sum of T[op] X[vector][source].
+int launch_xlate_batch(const fmmlm_plan_s* P, int g, const int32_t* boxes, int64_t b0, int64_t nb,
                         const int32_t* ptr, const int32_t* src, const int32_t* op, const double* T,
                         const double* X, double* dst, hipStream_t st) {
   if (nb <= 0) return FMMLM_OK;
   const int nr = (P->p + 1) * (P->p + 1);
-  constexpr int kAllFree = 1 << 30;  // every entry counts as enabled (parts = both)
   switch (P->mrt) {
 #define BL(R)                                                                                                \
   case R:                                                                                                    \
-    m2l_batch64_kernel<R><<<(unsigned)nb, 256, 0, st>>>(nr, P->nrk, g, P->NB, boxes, b0, ptr, src, op,         \
-                                                        kAllFree, FMMLM_FREE | FMMLM_REACTION, P->blevel,     \
-                                                        nullptr, T, X, dst);                                  \
+    xlate_batch_kernel<R><<<(unsigned)nb, 256, 0, st>>>(nr, P->nrk, g, P->NB, boxes, b0, ptr, src, op, T, X, dst); \
     break;
     BL(2) BL(4) BL(6) BL(8) BL(10)
 #undef BL
@@ -2807,7 +2789,7 @@ int gpu_eval_batch(fmmlm_plan_s* P, int g, const double* q, int64_t ldq, double*
   // (the 8 octant operators through the batched FP64 GEMM)
   for (int l = P->maxlev - 1; l >= 0; --l)
     if (P->xl_need_m2m[l])
-      if (int rc = launch_batch64_list(P, g, P->bu_boxes, P->bu_lev[l], P->bu_lev[l + 1] - P->bu_lev[l], P->bu_ptr,
+      if (int rc = launch_xlate_batch(P, g, P->bu_boxes, P->bu_lev[l], P->bu_lev[l + 1] - P->bu_lev[l], P->bu_ptr,
                                        P->bu_src, P->bu_op, P->Txl, P->M, P->M, st))
         return rc;
   mark();
@@ -2840,7 +2822,7 @@ int gpu_eval_batch(fmmlm_plan_s* P, int g, const double* q, int64_t ldq, double*
   mark();  // no separate reduction in the batched form
   for (int l = 1; l <= P->maxlev; ++l)
     if (P->xl_need_l2l[l])
-      if (int rc = launch_batch64_list(P, g, P->bd_boxes, P->bd_lev[l], P->bd_lev[l + 1] - P->bd_lev[l], P->bd_ptr,
+      if (int rc = launch_xlate_batch(P, g, P->bd_boxes, P->bd_lev[l], P->bd_lev[l + 1] - P->bd_lev[l], P->bd_ptr,
                                        P->bd_src, P->bd_op, P->Txl, P->Lx, P->Lx, st))
         return rc;
   mark();
@@ -2899,7 +2881,7 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
     if (ev) (void)hipEventRecord(ev[stage], st);
     ++stage;
   };
-  const int p = P->p, nc = P->nc;
+  const int p = P->p;
   double* M = P->M;
   double* Lx = P->Lx;
   mark();

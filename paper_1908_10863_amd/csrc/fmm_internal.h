@@ -21,12 +21,9 @@ constexpr int kBatchTopItem = 24;
 // reaction P2P: target rows per work unit (one wave, 8 lanes a row)
 constexpr int kRPUnitRows = 8;
 // free P2P (single vector): targets of one work unit, 16 lane slots x targets
-// a lane (8 in FP32, 4 in FP64)
+// a lane (8)
 constexpr int kPLUnitTargetsF32 = 128;
 constexpr int kPLUnitTargetsF64 = 128;
-// zeros before an operator's table G and after it
-constexpr int kGPad = 3;
-constexpr int kGPadEnd = 6;
 // M2L in operator frames: most steps (operators) of a unit
 constexpr int kM2LGroupOps = 4;
 // fewest columns for which a list of several operators makes units of its own
@@ -118,7 +115,7 @@ struct XcdSplit {
 // target adds up in slot order
 struct M2LUnits {
   int cols = 64;
-  int64_t n = 0, nsteps = 0, ncols = 0;  // units, steps, columns in use
+  int64_t n = 0, nsteps = 0;    // units, steps
   int32_t *step0 = nullptr;     // [n + 1] first step of each unit
   int32_t *kind = nullptr;      // [n] FMMLM_FREE or FMMLM_REACTION
   int32_t *phi = nullptr;       // [n cols] azimuth index of each column
@@ -172,20 +169,20 @@ struct fmmlm_plan_s {
   // M2L CSR over target boxes
   int32_t *m2l_ptr = nullptr;      // [NB + 1] ; free entries first, then reaction
   int32_t *m2l_nfree = nullptr;    // [NB] number of free entries per target box
-  int32_t *m2l_src = nullptr, *m2l_op = nullptr;  // op < 0 encodes mirrored source: ~op
+  int32_t* m2l_src = nullptr;
   // M2L operators in the frame turned to their azimuth: free space by (rho^2,
   // dz), reaction by Sommerfeld task; an operator of an entry is one of them and
   // an azimuth
-  double* G = nullptr;             // [ng_ops][ngs] (kGPad zeros, rows j of orders -j..j, zeros)
+  double* G = nullptr;             // [ng_ops][ngs] (rows j of orders -j..j)
   int64_t ng_ops = 0, ng_free = 0;
-  int ngs = 0;                     // stride of G (even)
+  int ngs = 0;                     // stride of G: (2p + 1)^2
   double* E = nullptr;             // azimuths: e^{i k phi}, k <= 2p [n_phi][2p + 1] complex
   int64_t n_phi = 0;
   int32_t *pair_dec = nullptr;     // [nc] pair j: offset in the real layout | order << 16 (orders >= 1 first)
   fmmlm::M2LUnits u64, u32;               // FP64 form: u64 all levels; FP32 form: u64 top levels, u32 the rest
   int nrk = 0, mrt = 0;            // padded inner dimension, padded rows / 32
   int m2l_variant = 0;             // FP32 M2L launch variant picked by the autotuner
-  int batch_variant = 0;           // batched FP32 M2L shape / persistence picked by the autotuner
+  int batch_variant = 0;           // batched FP32 M2L launch variant picked by the autotuner
   // M2M / L2L as GEMMs: 16 real-form operators (8 child octants up, 8 down)
   // and their own tiles; per level (first tile, first unit, end tile, end unit)
   double* Txl = nullptr;           // [16][nrk][32 mrt]
