@@ -692,10 +692,12 @@ struct FrameTypes<float> {
 // barrier each, loads of both a batch ahead.  Waves whose columns are empty only
 // load.
 // A kernel of dense real-form operators took, launch alone, at 2^20 charges,
-// p = 10: FP64 1.30 ms, this one 0.83; 262,144 clustered charges, p = 12: 4.9
-// and 2.6 ms; the top levels' own kernel (24,840 pairs) 0.106 and 0.055 ms.  Now
-// bound by the matrix cores (half their time at p = 10) and the gathers' cache
-// accesses.  Measured on the way: one unit of 16 columns a wave without LDS,
+// p = 10: FP64 1.30 ms, this one 0.77; 262,144 clustered charges, p = 12: 4.9
+// and 2.44 ms; the top levels' own kernel (24,840 pairs) 0.106 and 0.054 ms.  Now
+// bound by the matrix cores (busy 0.50 of the FP64 launch's time, 0.45 of the FP32
+// one's, 0.43 ms) and the gathers' cache accesses (54 and 41 M requests to the L2,
+// 0.72 of them hits); the top levels, 431 units, by latency (matrix cores 0.10
+// busy).  Measured on the way: one unit of 16 columns a wave without LDS,
 // operators through the vector cache: 1.67 ms (p = 10); phases read from memory
 // instead of LDS: half again as many cache accesses; results stored straight
 // from the fragments: 32-byte pieces.
@@ -834,7 +836,10 @@ m2l_frame_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restri
 // FP64 in a fixed order, scaled by 1/S of its level, into its local expansion.
 // One block per target box: NT / nc groups of nc threads (one a pair)
 // take every so many-th slot, four in flight, and the groups' sums are added in
-// LDS in group order.  Bound by the products' bytes.
+// LDS in group order.  Bound by the latency of the slots' indirect rows and phases
+// (waves wait 0.84 to 0.89 of their life): at 2^20 charges, p = 10, 0.295 GB in
+// 0.12 ms (FP32) and 0.58 GB in 0.165 ms (FP64), 2.5 and 3.5 TB/s where a copy
+// reaches 5.4.
 template <class T, int NT>
 __global__ void __launch_bounds__(NT)
 m2l_frame_reduce_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restrict__ boxes,
@@ -1148,10 +1153,12 @@ vector_minor_kernel(int nr, int nc, int ns, int g, int gw, int64_t slab, const d
 // all its vectors, rows of 16 vectors contiguous) into the operand fragments; the
 // operator goes through LDS as in m2l_frame_kernel, with the entry's phases.  Each
 // entry's product is turned back and added to FP64 totals by itself (products of
-// one azimuth added up in FP32 first: 15 % faster, but half again the error).  swizzle: each XCD takes a
-// contiguous range of the boxes, whose sources its L2 shares.
+// one azimuth added up in FP32 first: 11.1 against 11.9 ms, but half again the
+// error).  swizzle: each XCD takes a contiguous range of the boxes, whose sources
+// its L2 shares.
 // Bound by the operators' and sources' bytes out of the caches and, at two to three
-// waves a SIMD, their latency (matrix cores about 40 % busy): 604,000 pairs x 64
+// waves a SIMD, their latency (1.69 M pairs x 64 vectors, batches of 2: 30.8 ms,
+// matrix cores 0.40 busy, 0.44 of 1.16 G requests to the L2 hit): 604,000 pairs x 64
 // vectors at p = 10, 14.2 ms by the dense operators (box by box, FP32), 11.9 ms;
 // the FP64 top levels (42,708 pairs) 2.18 and 1.47 ms.  At three waves a SIMD
 // (batches of 2) 11.9 ms against 13.9 at two (batches of 4); XCD ranges do not pay
@@ -2448,9 +2455,14 @@ int launch_frame(const fmmlm_plan_s* P, const M2LUnits& U, int variant, unsigned
                  hipStream_t st) {
   if (U.n <= 0) return FMMLM_OK;
   const size_t reserve = variant >= 3 ? 61440 : 0;
-  // FP64 from p = 8 on: batches of 2 leave registers for a third wave a SIMD
-  // (p = 10 at 2^20 charges: 0.83 against 0.94 ms; p = 12: 2.61 against 2.93 ms;
-  // p = 8: the same); below, a batch of 2 has no room for the epilogue's rows
+  // k-steps of a batch, at 262,144 charges, leaf cap 64, launch in ms with 2 / 4.
+  // FP64 from p = 8 on 2, which leaves registers for a third wave a SIMD: p = 8
+  // 0.378 / 0.409, 10 0.727 / 0.818, 12 1.086 / 1.220, 13 1.569 / 1.516; below p = 8
+  // 4 (p = 6 0.198 / 0.204, 7 0.279 / 0.298; up to p = 5 a batch of 2 has no room for
+  // the epilogue's rows).  FP32 from p = 14 on 2 (14 0.885 / 0.935, 16 1.414 / 1.591),
+  // at the orders with variants the tuner's choice (8 0.188 / 0.203, 9 0.242 / 0.277,
+  // 10 0.375 / 0.379), elsewhere 4 (6 0.107 / 0.115, 7 0.143 / 0.188, 11 0.450 /
+  // 0.432, 12 0.554 / 0.545, 13 0.704 / 0.774)
   if (P->p > 13 || (sizeof(T) == 8 && P->p >= 8)) return launch_frame_kb<T, 2>(P, U, 0, parts, M, st);
   switch (variant % 3) {  // (0 where there are no variants)
     case 1: return launch_frame_kb<T, 2>(P, U, reserve, parts, M, st);
@@ -2467,8 +2479,12 @@ int launch_frame_reduce(const fmmlm_plan_s* P, const M2LUnits& U, double* Lx, hi
   m2l_frame_reduce_kernel<T, NT><<<(unsigned)U.nboxes, NT, 0, st>>>(                                          \
       (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.boxes, U.ptr, U.slots, U.slot_phi,         \
       P->pair_dec, P->blevel, P->sc_levels, static_cast<const T*>(U.W), reinterpret_cast<const cplx*>(P->E), Lx)
-  // few boxes (long slot lists, top levels): twice the groups a box.  20,011
-  // charges 187 -> 180 us, GMRES solve 11.4 -> 11.2 ms; 1,024 threads no better
+  // few boxes (long slot lists, top levels): twice the groups a box; 1,024 threads
+  // no better.  This launch with 256 / 512 threads, FP64, us, p = 5, 8, 10, 12: 227
+  // boxes of the tree 11.1 / 8.8, 18.6 / 12.7, 26.3 / 15.9, 35.1 / 19.7; 1,897 boxes
+  // 13.8 / 13.2, 22.8 / 19.0, 32.4 / 24.0, 44.9 / 31.5; 4,526 boxes 14.4 / 16.2,
+  // 24.5 / 22.5, 35.4 / 28.5, 59.5 / 44.5; 11,810 boxes 36.0 / 43.7, 86.4 / 89.9,
+  // 131 / 125, 179 / 169: the line is where p = 5 starts to lose
   if (U.nboxes < 2048) {
     FRR(512);
   } else {
@@ -2523,8 +2539,8 @@ int gpu_tune_m2l(fmmlm_plan_s* P, hipStream_t st) {
 }
 
 // Second stage of the FP32 M2L choice: the main M2L shares the GPU with the
-// near field and the sparse top levels in an unprofiled evaluation, so the
-// shape that is fastest alone need not be fastest there.  Every shape times
+// near field and the FP64 top levels in an unprofiled evaluation, so the
+// variant that is fastest alone need not be fastest there.  Every variant times
 // whole evaluations (zero charges: the arithmetic does not depend on them),
 // one to warm up and three timed; the fastest evaluation decides.  Then the
 // same timing picks how much of the free P2P starts at the fork, the rest
@@ -2561,7 +2577,7 @@ int gpu_tune_eval(fmmlm_plan_s* P, hipStream_t st) {
     }
     return tmin;
   };
-  // the main M2L's tile shape, with the whole free P2P at the fork
+  // the main M2L's variant, with the whole free P2P at the fork
   P->pl_split = P->n_mu_units;
   double best = 1e300;
   int pick = P->m2l_variant;
@@ -2657,6 +2673,11 @@ int launch_batch32(const fmmlm_plan_s* P, int variant, int g, int64_t n, unsigne
   const int32_t* bx = P->bbox + P->bbox_split;
   const int shape = variant % nv;
   const size_t reserve = shape >= 3 ? 61440 : 0;
+  // k-steps of a batch at the orders without variants, launch in ms with 2 / 4 at
+  // 131,072 charges, 64 vectors, leaf cap 64: 4 up to p = 13 (p = 4 2.94 / 2.67, 5
+  // 5.07 / 5.00, 6 7.34 / 6.22, 7 10.0 / 10.5, 11 44.1 / 36.9, 12 54.6 / 46.2, 13
+  // 67.8 / 62.2); from p = 14 on, where they are equal (60,000 charges: 14 26.0 / 26.0,
+  // 16 51.1 / 50.9), 2 for its smaller LDS
   if (P->p > 13) return launch_frame_batch_kb<float, 2>(P, P->u32, g, n, bx, nullptr, sw, 0, parts, P->M32, nullptr, st);
   if (shape == 1 || shape == 4)
     return launch_frame_batch_kb<float, 2>(P, P->u32, g, n, bx, nullptr, sw, reserve, parts, P->M32, nullptr, st);

@@ -26,7 +26,11 @@ constexpr int kPLUnitTargetsF32 = 128;
 constexpr int kPLUnitTargetsF64 = 128;
 // M2L in operator frames: most steps (operators) of a unit
 constexpr int kM2LGroupOps = 4;
-// fewest columns for which a list of several operators makes units of its own
+// fewest columns for which a list of several operators makes units of its own: units
+// have 64 columns, empty ones are padding.  M2L launch + reduction, us, at 2, 16, 32,
+// 64, 128: 1,200 charges, p = 8, FP64 51, 52, 56, 59, 50; 131,071, p = 5 355, 353, 357,
+// 357, 363; 262,144 clustered, p = 12 2961, 2895, 2927, 2906, 2989; 2^20, p = 10, FP64
+// 915, 931, 936, 932, 942: flat within 3 % but for the smallest, 10 % better at either end
 constexpr size_t kM2LFewCols = 32;
 
 // ---- small complex type (device and host) ------------------------------------
@@ -268,8 +272,8 @@ struct fmmlm_plan_s {
   double *qt = nullptr, *phit = nullptr;
   double *M = nullptr, *Lx = nullptr;  // [NB][(p+1)^2] real layout
   double *sc_levels = nullptr;     // 1/S_l per level
-  // single-vector evaluations: the near field (into phin) and the sparse top
-  // levels run on their own streams, joined to the caller's stream by events
+  // single-vector evaluations: the near field (into phin) and the FP32 form's FP64
+  // top levels run on their own streams, joined to the caller's stream by events
   double* phin = nullptr;          // near-field potentials, tree order [NP]
   hipStream_t s_near = nullptr, s_top = nullptr;
   hipEvent_t ev_q = nullptr, ev_m = nullptr, ev_near = nullptr, ev_top = nullptr;

@@ -187,8 +187,9 @@ __device__ double max_thickness(const Medium& md) {
 // What bounds it: a task is a serial chain of 100 to 200 panels, each node a
 // density, Bessel functions and 2 (nmax + 1) sums.  One thread a task ran that
 // chain 16 times as long with its order sums in scratch memory and left most of
-// the chip idle (10,007 points at nmax = 20 are 157 waves): 16.7 ms, now 2.1 ms
-// by the quadrature and 0.033 ms by the image series of two interfaces (34 images).
+// the chip idle (10,007 points at nmax = 20 are 157 waves): 16.7 ms for two
+// interfaces, now 0.034 ms by their image series (34 images) and 2.1 ms by the
+// quadrature (three interfaces; five: 3.7 ms).
 constexpr int kTaskLanes = kGL;
 constexpr int kTaskBlock = 128;
 constexpr int kBlockTasks = kTaskBlock / kTaskLanes;
@@ -1089,10 +1090,10 @@ double sigma_inf(const Medium& md, int lt, int ls, int a, int b) {
 // ends where what is left, |q|^n / (1 - |q|) of its first term, falls under
 // 2^-56.  Up to kImagesMost terms it is taken instead of the quadrature, which
 // stays for |q| closer to 1 and for other stacks.  Measured on tables of 10,007
-// points, nmax 10 / 20 / 32: 34 terms 0.028 / 0.035 / 0.08 ms, 785 terms
-// 0.11 / 0.15 / 0.36 ms, the quadrature 1.4 / 1.6 / 1.9 ms at best; the costs
-// would meet at about 5,000 terms, the limit stays under half of that since a
-// series' rounding grows with its length.
+// points, nmax 10 / 20 / 32: 34 terms 0.023 / 0.034 / 0.082 ms, 2,029 terms
+// 0.22 / 0.28 / 0.74 ms, the quadrature of three interfaces 1.9 / 2.1 / 2.4 ms; the
+// costs would meet at 7,000 to 20,000 terms, the limit stays well under that since
+// a series' rounding grows with its length.
 constexpr int kImagesMost = 2048;
 
 CompInfo make_comp(const Medium& md, int lt, int ls, int a, int b) {
