@@ -1161,8 +1161,9 @@ vector_minor_kernel(int nr, int nc, int ns, int g, int gw, int64_t slab, const d
 // matrix cores 0.40 busy, 0.44 of 1.16 G requests to the L2 hit): 604,000 pairs x 64
 // vectors at p = 10, 14.2 ms by the dense operators (box by box, FP32), 11.9 ms;
 // the FP64 top levels (42,708 pairs) 2.18 and 1.47 ms.  At three waves a SIMD
-// (batches of 2) 11.9 ms against 13.9 at two (batches of 4); XCD ranges do not pay
-// at this size (14.2 ms, they end unevenly) but stay among the tuner's choices.
+// (batches of 2) 11.9 ms against 13.9 at two (batches of 4), in XCD ranges 14.2 (they
+// end unevenly); 1.69 M pairs in box order / XCD ranges: batches of 2 30.8 / 38.4, of 4
+// 35.2 / 36.6, of 8 32.1 / 31.5 ms, so both orders are among the tuner's choices.
 template <class T, int RC, int RS, int KB>
 __global__ void __launch_bounds__(256, sizeof(T) == 4 && KB == 2 && RC + RS <= 9 ? 3 : 2)
 m2l_frame_batch_kernel(int nr, int nc, int ns, int ne, int g, int gw, int64_t slab, int64_t nblk, int swizzle, XcdSplit xcd,
