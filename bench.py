@@ -4,7 +4,7 @@ Workload (default): three-layer medium d = (0, -1), eps = (1, 5, 2), N = 1,048,5
 charges uniform in the three layer boxes, p = 10, one charge vector; inputs are
 resident in HBM before the timed region.  A step is one fmm_layered_eval (free
 space + all 16 reaction components).  The K timed steps run as in production
-(near field and sparse top levels on their own streams); a second pass of K
+(near field and FP64 top levels on their own streams); a second pass of K
 profiled steps, whose stages run in order on one stream, gives the per-stage
 times and the dominant kernel's time.  The line also carries `solve`: restarted
 GMRES on a capacitance-style system (conductor panels in the same medium, about
