@@ -1165,7 +1165,28 @@ int build_plan(fmmlm_plan_s* P, const std::vector<double>& X, const std::vector<
   std::vector<std::array<int64_t, 3>> segs;
   int64_t npos = 0;
   {
-    const int tpb = P->fp32 ? kPLUnitTargetsF32 : kPLUnitTargetsF64;
+    // FP64: units of 64 targets where the launch would end on its longest unit of 128
+    // (more than 1.3 times a CU's share of the pairs), or where no leaf needs more.
+    // FP64 near field in us, units of 64 / 128: ratio 1.4 and up (12,000 charges, leaf
+    // cap 192: 76 / 108; 40,000: 128 / 179) 64 is up to 1.46 times as fast; 1.23 (60,000:
+    // 79 / 78) the same; below, 128 is (100,000: 224 / 211; 2^20: 1291 / 1141).  Leaves
+    // of at most 64 charges (262,144, cap 64): 178 / 182
+    if (!P->fp32) {
+      int64_t total = 0, longest = 0, largest = 0;
+      for (int64_t li = 0; li < P->nleaves; ++li) {
+        const HBox& A = B.boxes[leaves[li]];
+        if (A.count <= 0 || pptr[li + 1] == pptr[li]) continue;
+        int64_t srcs = A.count;
+        for (auto& pr : B.p2p_free[leaves[li]])
+          if (pr.first > A.start) srcs += pr.second;
+        total += A.count * srcs;
+        longest = std::max(longest, std::min<int64_t>(A.count, kPLUnitTargets) * srcs);
+        largest = std::max(largest, A.count);
+      }
+      const bool ends_late = 10 * 256 * longest > 13 * total && total < ((int64_t)1 << 36);
+      if (ends_late || largest <= kPLUnitTargetsFew) P->pl_targets = kPLUnitTargetsFew;
+    }
+    const int tpb = P->pl_targets;
     std::vector<std::pair<int64_t, int32_t>> lstart;  // (first point, leaf list index)
     for (int64_t li = 0; li < P->nleaves; ++li)
       if (B.boxes[leaves[li]].count > 0) lstart.push_back({B.boxes[leaves[li]].start, (int32_t)li});

@@ -1755,12 +1755,11 @@ __device__ inline double pl_rsqrt<double>(double r2) { return rsqrt_nr(r2); }
 // wave's share of each staged chunk.  A leaf of tc targets then wastes fewer
 // than 16 lane slots per source (instead of up to 63 with one target a lane),
 // and every source read from LDS serves TPL targets.
-template <class T>
-struct PLCfg;
-template <>
-struct PLCfg<float> { static constexpr int kMaxTPL = 8, kNS = 4, kWaves = 4; };
-template <>
-struct PLCfg<double> { static constexpr int kMaxTPL = 8, kNS = 2, kWaves = 3; };
+// MT: most targets a lane, kNS: sources of a group in flight, kWaves a SIMD.
+template <class T, int MT>
+struct PLCfg {
+  static constexpr int kNS = sizeof(T) == 4 || MT <= 4 ? 4 : 2, kWaves = sizeof(T) == 4 ? 4 : 3;
+};
 
 // One pair: MASK skips pairs at zero distance (the self pair, or two points at
 // one position, which share a leaf): only sources of the target leaf itself
@@ -1864,14 +1863,13 @@ __device__ inline void pl_two(const typename PLVec<T>::type& sv, bool ok, T x, T
 // Sources [j0, j1) (wave-uniform) of the staged chunk, both ways: group g
 // takes j0 + g + 4 i; the source-side sum of chunk source j goes to
 // out[oidx[j]].
-template <class T, int TPL>
+template <class T, int TPL, int NS>
 __device__ inline void pl_mrange(const typename PLVec<T>::type* __restrict__ src, int j0, int j1, int g, int sl,
                                  const T* x, const T* y, const T* z, const T* q, T* p, const int* oidx,
                                  T* __restrict__ out) {
   using V = typename PLVec<T>::type;
   j0 = __builtin_amdgcn_readfirstlane(j0);
   j1 = __builtin_amdgcn_readfirstlane(j1);
-  constexpr int NS = PLCfg<T>::kNS;  // sources of a group in flight
   int j = j0;
   for (; j + 4 * NS <= j1; j += 4 * NS) {
     V s[NS];
@@ -1907,7 +1905,7 @@ __device__ inline void pl_mrange(const typename PLVec<T>::type* __restrict__ src
 
 // One unit: targets [tb, tb + tcp) of the leaf at t0 (tc points); ranges
 // [e0, e1) of mu_rng, the first the leaf itself.
-template <class T, int TPL>
+template <class T, int TPL, int MT>
 __device__ void pl_mpass(int tb, int tcp, int t0, int tc, double cx, double cy, double ch, int e0, int e1,
                          const int32_t* __restrict__ rng, const double* __restrict__ px,
                          const double* __restrict__ py, const double* __restrict__ ph,
@@ -1915,7 +1913,7 @@ __device__ void pl_mpass(int tb, int tcp, int t0, int tc, double cx, double cy, 
                          double* __restrict__ abuf, T* __restrict__ bbuf, typename PLVec<T>::type* src, int* oidx,
                          int* rs, int* rpre, double* red) {
   using V = typename PLVec<T>::type;
-  constexpr int RW = 16 * PLCfg<T>::kMaxTPL;
+  constexpr int RW = 16 * MT;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int sl = lane & 15, g = lane >> 4;
   // idle target slots sit far away with zero charge: they add nothing to a
@@ -1988,7 +1986,7 @@ __device__ void pl_mpass(int tb, int tcp, int t0, int tc, double cx, double cy, 
       for (int t = 0; t < TPL; ++t) pp[t] = T(0);
       const int ja = min(j1, ns), jb = max(j0, ns);
       if (j0 < ja) pl_range<T, TPL, true>(src, j0, ja, g, x, y, z, pp);
-      if (jb < j1) pl_mrange<T, TPL>(src, jb, j1, g, sl, x, y, z, q, pp, oidx, bbuf);
+      if (jb < j1) pl_mrange<T, TPL, PLCfg<T, MT>::kNS>(src, jb, j1, g, sl, x, y, z, q, pp, oidx, bbuf);
 #pragma unroll
       for (int t = 0; t < TPL; ++t) {
         if constexpr (sizeof(T) == 4)
@@ -2010,8 +2008,8 @@ __device__ void pl_mpass(int tb, int tcp, int t0, int tc, double cx, double cy, 
   if (tid < tcp) abuf[t0 + tb + tid] = (red[tid] + red[RW + tid]) + (red[2 * RW + tid] + red[3 * RW + tid]);
 }
 
-template <class T>
-__global__ void __launch_bounds__(kPLThreads, PLCfg<T>::kWaves)
+template <class T, int MT>
+__global__ void __launch_bounds__(kPLThreads, (PLCfg<T, MT>::kWaves))
 p2p_mutual_kernel(int64_t u0, const int32_t* __restrict__ mu_order, const int32_t* __restrict__ mu_leaf,
                   const int32_t* __restrict__ mu_tb,
                   const int32_t* __restrict__ mu_rptr, const int32_t* __restrict__ mu_rng,
@@ -2022,8 +2020,6 @@ p2p_mutual_kernel(int64_t u0, const int32_t* __restrict__ mu_order, const int32_
                   const double* __restrict__ py, const double* __restrict__ ph, const double* __restrict__ qt,
                   double* __restrict__ abuf, T* __restrict__ bbuf) {
   using V = typename PLVec<T>::type;
-  constexpr int MT = PLCfg<T>::kMaxTPL;
-  static_assert(16 * MT == (sizeof(T) == 4 ? kPLUnitTargetsF32 : kPLUnitTargetsF64), "unit targets");
   __shared__ V src[kPLChunk];
   __shared__ int oidx[kPLChunk];
   __shared__ int rs[kPLRanges], rpre[kPLRanges + 1];
@@ -2036,7 +2032,7 @@ p2p_mutual_kernel(int64_t u0, const int32_t* __restrict__ mu_order, const int32_
 #define PM_CASE(k)                                                                                        \
   case k:                                                                                                 \
     if constexpr (k <= MT)                                                                                \
-      pl_mpass<T, k>(tb, tcp, t0, tc, bcx[b], bcy[b], bch[b], mu_rptr[u], mu_rptr[u + 1], mu_rng, px, py, \
+      pl_mpass<T, k, MT>(tb, tcp, t0, tc, bcx[b], bcy[b], bch[b], mu_rptr[u], mu_rptr[u + 1], mu_rng, px, py, \
                      ph, qt, mu_boff[u], mu_bidx, abuf, bbuf, src, oidx, rs, rpre, red);                  \
     break;
   switch (tpl) {
@@ -2920,16 +2916,17 @@ int gpu_eval_one(fmmlm_plan_s* P, const double* q, double* phi, uint32_t parts, 
     if (!(parts & FMMLM_FREE)) return;
     if (u1 > u0) {
       const unsigned nb = (unsigned)(u1 - u0);
+#define PL_LAUNCH(T, MT, PAD)                                                                                       \
+  p2p_mutual_kernel<T, MT><<<nb, kPLThreads, PAD, sn>>>(                                                            \
+      u0, P->mu_order, P->mu_leaf, P->mu_tb, P->mu_rptr, P->mu_rng, P->mu_boff, P->mu_bidx, P->leaves, P->bstart,   \
+      P->bcount, P->bcx, P->bcy, P->bch, P->px, P->py, P->ph, P->qt, P->mu_a, static_cast<T*>(P->mu_b))
       if (P->fp32)
-        p2p_mutual_kernel<float><<<nb, kPLThreads, pad, sn>>>(
-            u0, P->mu_order, P->mu_leaf, P->mu_tb, P->mu_rptr, P->mu_rng, P->mu_boff, P->mu_bidx, P->leaves,
-            P->bstart, P->bcount, P->bcx, P->bcy, P->bch, P->px, P->py, P->ph, P->qt, P->mu_a,
-            static_cast<float*>(P->mu_b));
+        PL_LAUNCH(float, kPLUnitTargets / 16, pad);
+      else if (P->pl_targets == kPLUnitTargetsFew)
+        PL_LAUNCH(double, kPLUnitTargetsFew / 16, 0);
       else
-        p2p_mutual_kernel<double><<<nb, kPLThreads, 0, sn>>>(
-            u0, P->mu_order, P->mu_leaf, P->mu_tb, P->mu_rptr, P->mu_rng, P->mu_boff, P->mu_bidx, P->leaves,
-            P->bstart, P->bcount, P->bcx, P->bcy, P->bch, P->px, P->py, P->ph, P->qt, P->mu_a,
-            static_cast<double*>(P->mu_b));
+        PL_LAUNCH(double, kPLUnitTargets / 16, 0);
+#undef PL_LAUNCH
     }
     if (last && P->n_mu_units > 0) {
       if (P->fp32)

@@ -20,10 +20,10 @@ constexpr int kMaxLevel = 20;  // 21-bit quantisation per axis
 constexpr int kBatchTopItem = 24;
 // reaction P2P: target rows per work unit (one wave, 8 lanes a row)
 constexpr int kRPUnitRows = 8;
-// free P2P (single vector): targets of one work unit, 16 lane slots x targets
-// a lane (8)
-constexpr int kPLUnitTargetsF32 = 128;
-constexpr int kPLUnitTargetsF64 = 128;
+// free P2P (single vector): most targets of one work unit, 16 lane slots x targets
+// a lane (8; few units in FP64: 4)
+constexpr int kPLUnitTargets = 128;
+constexpr int kPLUnitTargetsFew = 64;
 // M2L in operator frames: most steps (operators) of a unit
 constexpr int kM2LGroupOps = 4;
 // fewest columns for which a list of several operators makes units of its own: units
@@ -228,13 +228,14 @@ struct fmmlm_plan_s {
   int32_t *p2p_src = nullptr;      // [2 * entries] (start, count)
   int32_t *pl_leaves = nullptr;    // leaf list indices with free-space P2P entries (batched form)
   int64_t n_pl_leaves = 0;
-  // single-vector free P2P, mutual form: a unit is up to kPLUnitTargets(form)
+  // single-vector free P2P, mutual form: a unit is up to pl_targets
   // targets of one leaf against the leaf itself (one way) and the ranges after
   // it in tree order (both ways).  Target-side sums go to mu_a (per point);
   // source-side sums to mu_b, where leaf c holds cb_n[c] rows of its count of
   // values from cb_base[c] (one row per unit that covers it, in unit order),
   // at the index mu_bidx gives for each position of a unit's ranges after the
   // first; a combine pass adds a point's values in that order
+  int pl_targets = fmmlm::kPLUnitTargets;
   int64_t n_mu_units = 0;
   int32_t *mu_order = nullptr;     // [n_mu_units] launch order (most pairs first)
   int32_t *mu_leaf = nullptr, *mu_tb = nullptr;  // [n_mu_units] leaf list index, first target
