@@ -278,7 +278,7 @@ struct fmmlm_plan_s {
   double* phin = nullptr;          // near-field potentials, tree order [NP]
   hipStream_t s_near = nullptr, s_top = nullptr;
   hipEvent_t ev_q = nullptr, ev_m = nullptr, ev_near = nullptr, ev_top = nullptr;
-  hipEvent_t ev_l = nullptr;       // main M2L launched (the rest of the near field may start)
+  hipEvent_t ev_l = nullptr;       // FP32 main M2L done (the rest of the near field may start)
   int64_t pl_split = 0;            // free P2P units launched at the fork; the rest after the main M2L
   size_t pl_pad = 28672;           // LDS a free P2P block reserves beside the far field (tuned)
   // graph mode: the captured evaluation and its arguments
