@@ -2476,13 +2476,16 @@ int launch_frame_reduce(const fmmlm_plan_s* P, const M2LUnits& U, double* Lx, hi
   m2l_frame_reduce_kernel<T, NT><<<(unsigned)U.nboxes, NT, 0, st>>>(                                          \
       (P->p + 1) * (P->p + 1), r.nc, r.ns, 2 * P->p + 1, P->nrk, U.boxes, U.ptr, U.slots, U.slot_phi,         \
       P->pair_dec, P->blevel, P->sc_levels, static_cast<const T*>(U.W), reinterpret_cast<const cplx*>(P->E), Lx)
-  // few boxes (long slot lists, top levels): twice the groups a box; 1,024 threads
-  // no better.  This launch with 256 / 512 threads, FP64, us, p = 5, 8, 10, 12: 227
-  // boxes of the tree 11.1 / 8.8, 18.6 / 12.7, 26.3 / 15.9, 35.1 / 19.7; 1,897 boxes
-  // 13.8 / 13.2, 22.8 / 19.0, 32.4 / 24.0, 44.9 / 31.5; 4,526 boxes 14.4 / 16.2,
-  // 24.5 / 22.5, 35.4 / 28.5, 59.5 / 44.5; 11,810 boxes 36.0 / 43.7, 86.4 / 89.9,
-  // 131 / 125, 179 / 169: the line is where p = 5 starts to lose
-  if (U.nboxes < 2048) {
+  // few boxes (long slot lists, top levels): more groups a box, 512 threads, from p = 10
+  // on (7 groups and fewer at 512) 1,024.  This launch, FP64, us, with 256 / 512 / 1,024
+  // threads, 227 boxes in the tree: p = 5 11.1 / 8.8 / 8.0, 8 18.6 / 12.7 / 10.0, 10 26.3 /
+  // 15.9 / 11.8, 16 69.5 / 32.4 / 21.5; 1,897 boxes: p = 2 - / 10.4 / 15.3, 5 13.8 / 13.2 / 16.8,
+  // 8 22.8 / 19.0 / 20.0, 10 32.4 / 24.0 / 23.9, 16 116 / 66 / 58.  More boxes, with 256 / 512:
+  // 4,526 p = 5 14.4 / 16.2, 8 24.5 / 22.5, 10 35.4 / 28.5; 11,810 p = 5 36.0 / 43.7, 8 86.4 /
+  // 89.9, 10 131 / 125: the line is where p = 5 starts to lose
+  if (U.nboxes < 2048 && r.nc > 64) {
+    FRR(1024);
+  } else if (U.nboxes < 2048) {
     FRR(512);
   } else {
     FRR(256);
