@@ -2653,14 +2653,20 @@ int launch_frame_batch_kb(const fmmlm_plan_s* P, const M2LUnits& U, int g, int64
     FMM_HIP_TRY(hipGetLastError());                                                                             \
     return FMMLM_OK;                                                                                            \
   }
-  if constexpr (KB == 2 || sizeof(T) == 4) {  // the tuner's orders (batch_variants)
-    FB(3, 3) FB(4, 3) FB(5, 4)
-  }
-  if constexpr (KB == (sizeof(T) == 8 ? 2 : 4)) {  // p = 1..16
-    FB(1, 1) FB(2, 1) FB(2, 2) FB(3, 2) FB(5, 5) FB(6, 5) FB(7, 6)
-  }
-  if constexpr (KB == 2) {
-    FB(8, 7) FB(9, 8) FB(10, 9)
+  if constexpr (sizeof(T) == 4) {
+    if constexpr (KB == 4) {  // p = 1..16
+      FB(1, 1) FB(2, 1) FB(2, 2) FB(3, 2) FB(5, 5) FB(6, 5) FB(7, 6)
+    }
+    FB(3, 3) FB(4, 3) FB(5, 4)  // the tuner's orders (batch_variants)
+    if constexpr (KB == 2) {
+      FB(8, 7) FB(9, 8) FB(10, 9)
+    }
+  } else if constexpr (KB == 2) {  // (launch_batch64)
+    FB(1, 1) FB(4, 3) FB(5, 4) FB(5, 5) FB(6, 5) FB(7, 6) FB(8, 7) FB(9, 8) FB(10, 9)
+  } else if constexpr (KB == 3) {
+    FB(1, 1) FB(2, 1) FB(3, 2)
+  } else {
+    FB(1, 1) FB(2, 2) FB(3, 3)
   }
 #undef FB
   return FMMLM_EUNSUPPORTED;
@@ -2684,6 +2690,22 @@ int launch_batch32(const fmmlm_plan_s* P, int variant, int g, int64_t n, unsigne
   if (shape == 2)
     return launch_frame_batch_kb<float, 8>(P, P->u32, g, n, bx, nullptr, sw, 0, parts, P->M32, nullptr, st);
   return launch_frame_batch_kb<float, 4>(P, P->u32, g, n, bx, nullptr, sw, reserve, parts, P->M32, nullptr, st);
+}
+
+// The batched M2L in FP64: n boxes, or n work items.  Up to p = 8 an entry's k-steps go
+// in as few batches as batches of at most 4 allow, evenly (p = 3, 5, 7: 3; 4, 6, 8: 4):
+// with batches of 2 the barriers and the turn back kept it behind the dense operators,
+// which fit their tiles at p = 3 and 7.  M2L of 6,000 charges' 64 vectors, us, dense / 2 /
+// these: p = 3 216 / 292 / 211, 5 628 / 516 / 460, 7 851 / 961 / 797, 8 2051 / 1224 / 977;
+// p = 9 2394 / 1586 / 1595 (4), so from there on 2 and its registers.
+int launch_batch64(const fmmlm_plan_s* P, int g, int64_t n, const int32_t* items, unsigned parts, double* part,
+                   hipStream_t st) {
+  const int kc = frame_ksteps(P->nc), batches = (kc + 3) / 4, kb = (kc + batches - 1) / batches;
+  if (P->p > 8 || kb <= 2)
+    return launch_frame_batch_kb<double, 2>(P, P->u64, g, n, P->bbox, items, false, 0, parts, P->M64, part, st);
+  if (kb == 3)
+    return launch_frame_batch_kb<double, 3>(P, P->u64, g, n, P->bbox, items, false, 0, parts, P->M64, part, st);
+  return launch_frame_batch_kb<double, 4>(P, P->u64, g, n, P->bbox, items, false, 0, parts, P->M64, part, st);
 }
 
 // Autotuner of the batched FP32 M2L: each variant runs the plan's boxes for
@@ -2824,9 +2846,7 @@ int gpu_eval_batch(fmmlm_plan_s* P, int g, const double* q, int64_t ldq, double*
       // the FP32 form's FP64 top levels as work items (few boxes, long entry
       // lists), then a reduction per box; the FP64 form one block per box
       vector_minor_kernel<<<(unsigned)P->ntop, 256, 0, st>>>(nr, nc, nc - p - 1, g, P->gw, slab, P->M, P->M64);
-      if (int rc = launch_frame_batch_kb<double, 2>(P, P->u64, g, f32 ? P->n_btop_items : n64, P->bbox,
-                                                    f32 ? P->btop_items : nullptr, false, 0, parts, P->M64, P->Pbtop,
-                                                    st))
+      if (int rc = launch_batch64(P, g, f32 ? P->n_btop_items : n64, f32 ? P->btop_items : nullptr, parts, P->Pbtop, st))
         return rc;
       if (f32)
         m2l_btop_reduce_kernel<<<(unsigned)n64, 256, 0, st>>>(nr, g, P->bbox, P->btop_iptr, P->Pbtop, P->blevel,
