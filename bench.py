@@ -32,7 +32,7 @@ TRAFFIC_FILES = {
 }
 KERNEL_SRC = os.path.join(ROOT, "paper_1908_10863_amd", "csrc", "fmm.hip")
 # kernel that carries each stage of the FP32 form (one launch per evaluation)
-STAGE_KERNEL = {"m2l": "m2l_frame_kernel<float>", "p2p_free": "p2p_mutual_kernel<float> + p2p_combine_kernel<float>"}
+STAGE_KERNEL = {"m2l": "m2l_frame_kernel<float>", "p2p_free": "p2p_mutual_kernel<float, 8> + p2p_combine_kernel<float>"}
 CALIB_BYTES = 256 << 20  # plain device-to-device copy that scales the PMC byte counters
 PEAK_FP64 = 78.6e12  # MI355X FP64, vector and dense matrix (published), FLOP/s
 PEAK_FP32 = 157.3e12  # MI355X FP32, vector and dense matrix (published), FLOP/s

@@ -837,7 +837,7 @@ m2l_frame_kernel(int nr, int nc, int ns, int ne, int wr, const int32_t* __restri
 // One block per target box: NT / nc groups of nc threads (one a pair)
 // take every so many-th slot, four in flight, and the groups' sums are added in
 // LDS in group order.  Bound by the latency of the slots' indirect rows and phases
-// (waves wait 0.84 to 0.89 of their life): at 2^20 charges, p = 10, 0.295 GB in
+// (waves wait 0.84 to 0.93 of their life): at 2^20 charges, p = 10, 0.295 GB in
 // 0.12 ms (FP32) and 0.58 GB in 0.165 ms (FP64), 2.5 and 3.5 TB/s where a copy
 // reaches 5.4.
 template <class T, int NT>
@@ -1755,7 +1755,9 @@ __device__ inline double pl_rsqrt<double>(double r2) { return rsqrt_nr(r2); }
 // wave's share of each staged chunk.  A leaf of tc targets then wastes fewer
 // than 16 lane slots per source (instead of up to 63 with one target a lane),
 // and every source read from LDS serves TPL targets.
-// MT: most targets a lane, kNS: sources of a group in flight, kWaves a SIMD.
+// MT: most targets a lane, kNS: sources of a group in flight, kWaves a SIMD.  FP64 at
+// 8 targets keeps 124 bytes a lane in scratch memory and at 4 none, but reads each
+// source and adds its row for half the targets: the plan chooses (pl_targets).
 template <class T, int MT>
 struct PLCfg {
   static constexpr int kNS = sizeof(T) == 4 || MT <= 4 ? 4 : 2, kWaves = sizeof(T) == 4 ? 4 : 3;
