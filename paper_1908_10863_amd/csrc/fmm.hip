@@ -2484,8 +2484,11 @@ int launch_frame_reduce(const fmmlm_plan_s* P, const M2LUnits& U, double* Lx, hi
   // 15.9 / 11.8, 16 69.5 / 32.4 / 21.5; 1,897 boxes: p = 2 - / 10.4 / 15.3, 5 13.8 / 13.2 / 16.8,
   // 8 22.8 / 19.0 / 20.0, 10 32.4 / 24.0 / 23.9, 16 116 / 66 / 58.  More boxes, with 256 / 512:
   // 4,526 p = 5 14.4 / 16.2, 8 24.5 / 22.5, 10 35.4 / 28.5; 11,810 p = 5 36.0 / 43.7, 8 86.4 /
-  // 89.9, 10 131 / 125: the line is where p = 5 starts to lose
-  if (U.nboxes < 2048 && r.nc > 64) {
+  // 89.9, 10 131 / 125: the line is where p = 5 starts to lose.  Top levels beside an FP32
+  // launch keep 512: blocks of 16 waves wait for room there (six layers, 524,288 charges,
+  // 1,598 against 1,610 us an evaluation)
+  const bool beside = P->fp32 && P->u32.n > 0;
+  if (U.nboxes < 2048 && r.nc > 64 && !beside) {
     FRR(1024);
   } else if (U.nboxes < 2048) {
     FRR(512);
